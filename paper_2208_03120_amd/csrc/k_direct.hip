@@ -1,52 +1,122 @@
 // Direct Gaussian-kernel products (a7), the plain O(n_t n_s) path:
 //   out_i = sum_j v_j exp(-|x_i - y_j|^2 / eta)      (Sec. 5, eq. fastsum-sum)
 //
+// Both precisions split a job's sources into dsplit equal ranges, so that products with few
+// targets still spread over the chip: an item is a group of targets and one range; with
+// dsplit > 1 it writes its partial sums to the job's partial buffer, and
+// direct_reduce_kernel adds the ranges in order.
+//
 // FP64 variant: one target per lane, a block's four wavefronts summing quarters of a
 // source range in ascending source order, the quarters (and ranges) then added in order
 // (details at direct_fp64_kernel).
 //
-// Mixed variant: FP32 transcendental with FP64 accumulation across tiles.  With
-// c = log2(e) / eta and coordinates taken relative to the point cloud's centre,
-//   exp(-|x - y|^2 / eta) = exp2(a_x + a_y + x'.y'),  a_x = -c|x|^2, a_y = -c|y|^2,
-//   y' = 2 c y,
-// so each pair costs d FMAs, one add, one v_exp_f32 and one FMA.  The exponent is a sum
-// of terms up to c r^2 (r the cloud's radius) that cancel to -c|x - y|^2, so its FP32
-// rounding error grows like 6e-8 c r^2; when c r^2 exceeds 8 (small eta) the kernel
-// forms the same exponent in FP64 (gfx950 issues FP64 adds and FMAs at the unpacked FP32
-// rate) and rounds only the result to FP32 for v_exp_f32: one conversion more per pair,
-// and the error is the rounding of the exponent itself.  Source values are scaled by
-// 2^-e (e = exponent of max v) so FP32 never under- or overflows; partial sums over 64
-// sources are added into FP64 accumulators.  Each thread owns R targets to reuse every
-// LDS read R times.  This kernel is bound by the transcendental and vector issue rates.
+// Mixed variant: FP32 transcendental with FP64 accumulation.  With c = log2(e) / eta and
+// coordinates taken relative to the point cloud's centre,
+//   exp(-|x - y|^2 / eta) = exp2(a_x + x.y' + a_y),  a_x = -c|x|^2, a_y = -c|y|^2, y' = 2 c y,
+// and x.y' + a_y is a contraction of length four, one MFMA for 16 sources x 16 targets
+// (details at direct_mixed_kernel).  The exponent is a sum of terms up to c r^2 (r the
+// cloud's radius) that cancel to -c|x - y|^2, so its FP32 rounding error grows like
+// 6e-8 c r^2; when c r^2 exceeds 8 (small eta) the kernel forms the same exponent on the FP64
+// MFMA and rounds only the result to FP32 for v_exp_f32.  Source values are scaled by 2^-e
+// (e = exponent of max v) so FP32 never under- or overflows.
 #include <algorithm>
+#include <cfloat>
 #include <type_traits>
 
 #include "mot_internal.h"
 
 namespace mot {
 
-// FP64 variant: an item is 64 targets (one per lane) and one of the job's dsplit equal
-// source ranges; the block's four wavefronts take the four quarters of that range, each
-// summing its sources in ascending order, and the quarters are added in order.  With
-// dsplit > 1 the item writes its partial sums to the job's partial buffer and
-// direct_fp64_reduce_kernel adds the ranges in order; dsplit grows as the targets get
-// fewer, so that small products still spread over the chip.
-constexpr int kDirectT = 64;
+// Uniform reads through the scalar unit: the sources of a product are written by earlier
+// launches only.
+#define MOT_CONST __attribute__((address_space(4)))
 
-int direct_source_split(int64_t nt, int64_t ns)
+constexpr int kDirectT = 64;    // targets per FP64 item
+constexpr int kMixedT = 256;    // targets per mixed item, 64 per wavefront
+constexpr int kMixedS = 256;    // sources staged in LDS at a time
+
+int direct_targets_per_item(int precision) { return precision == MOT_PREC_FP64 ? kDirectT : kMixedT; }
+
+// Items a job is split into at least, while its sources last: two 256-thread blocks per CU in
+// mixed precision, four in FP64.  Without the split a star of four 3-D marginals of 3000
+// points ran a mixed product on 3 blocks: 760 us per sweep against 74 us with it (20000
+// points: 5.3 ms against 0.53 ms); 1024 mixed items measured the same as 512, 2048 FP64 items
+// the same as 1024.
+int direct_items_wanted(int precision) { return precision == MOT_PREC_FP64 ? 1024 : 512; }
+
+int direct_source_split(int64_t nt, int64_t ns, int precision)
 {
-    const int64_t groups = (nt + kDirectT - 1) / kDirectT;
-    const int64_t want = (1024 + groups - 1) / groups;  // about a thousand items per launch
-    const int64_t most = (ns + 63) / 64;               // at least 16 sources per wavefront
+    const int tpi = direct_targets_per_item(precision);
+    const int64_t groups = (nt + tpi - 1) / tpi;
+    const int64_t items = direct_items_wanted(precision), want = (items + groups - 1) / groups;
+    const int64_t most = (ns + 63) / 64;               // at least 64 sources per range
     return (int)std::max<int64_t>(1, std::min<int64_t>(std::min(want, most), 64));
 }
 
+// Sources of one range.  Mixed ranges are multiples of 64 sources.
+__device__ __forceinline__ void direct_range(const ProdJob &J, int range, int quantum, int64_t &a, int64_t &b)
+{
+    int64_t per = (J.ns + J.dsplit - 1) / J.dsplit;
+    per = (per + quantum - 1) / quantum * quantum;
+    a = min(J.ns, (int64_t)range * per);
+    b = min(J.ns, a + per);
+}
+
+// 2^y for y = d2 c, c = -log2(e) / eta given as c_hi + c_lo, d2 >= 0.  n = rint(y) and the
+// remainder f = d2 c - n by two FMAs, which keeps the low part of c, so f is exact to one
+// rounding; 2^f on [-1/2, 1/2] is its Chebyshev interpolant of degree 11 (relative error
+// 4e-18, below the FP64 rounding).  dmax = 1100 / |c| bounds y: terms below 2^-1100 are zero.
+struct ExpScale {
+    double c_hi, c_lo, dmax;
+};
+
+__device__ __forceinline__ ExpScale exp_scale(double eta)
+{
+    constexpr double L_hi = 1.4426950408889634, L_lo = 2.0355273740931033e-17;  // log2(e)
+    ExpScale E;
+    E.c_hi = -L_hi / eta;
+    E.c_lo = -(fma(E.c_hi, eta, L_hi) + L_lo) / eta;
+    if (!(E.c_hi > -DBL_MAX)) E.c_hi = -DBL_MAX;  // eta at the end of the FP64 range
+    if (!(fabs(E.c_lo) < DBL_MAX)) E.c_lo = 0.0;
+    E.dmax = fmin(1100.0 / -E.c_hi, DBL_MAX);
+    return E;
+}
+
+__device__ __forceinline__ double exp2_scaled(double d2, const ExpScale &E)
+{
+    constexpr double kMagic = 6755399441055744.0;  // 1.5 2^52: adding it rounds to an integer
+    d2 = fmin(d2, E.dmax);
+    const double t = fma(d2, E.c_hi, kMagic);
+    const int n = (int)__builtin_bit_cast(uint64_t, t);
+    double f = fma(d2, E.c_hi, kMagic - t);
+    f = fma(d2, E.c_lo, f);
+    double p = 4.4558179475918685e-10;
+    p = fma(p, f, 7.074194370937212e-09);
+    p = fma(p, f, 1.017805708751313e-07);
+    p = fma(p, f, 1.3215432535498108e-06);
+    p = fma(p, f, 1.5252733841557202e-05);
+    p = fma(p, f, 0.0001540353046372516);
+    p = fma(p, f, 0.001333355814640647);
+    p = fma(p, f, 0.009618129107587256);
+    p = fma(p, f, 0.055504108664821625);
+    p = fma(p, f, 0.24022650695910158);
+    p = fma(p, f, 0.6931471805599453);
+    p = fma(p, f, 1.0);
+    return ldexp(p, n);
+}
+
+// FP64 variant: an item is 64 targets (one per lane) and one of the job's dsplit equal
+// source ranges; the block's four wavefronts take the four quarters of that range, each
+// summing its sources in ascending order, and the quarters are added in order.  Bound by
+// FP64 issue (half the FP32 rate): 24 FP64 instructions per pair in 3-D, where a division and
+// the library's exp took about 40.  Five marginals of up to 7000 points in 3-D: 122 -> 60 us
+// per launch.
 template <int D>
 __global__ __launch_bounds__(256) void direct_fp64_kernel(const ProdJob *__restrict__ jobs,
                                                           const int4 *__restrict__ items, int n_items)
 {
     __shared__ double red[3][kDirectT];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int4 itm = items[it];
         const ProdJob &J = jobs[itm.x];
@@ -54,21 +124,24 @@ __global__ __launch_bounds__(256) void direct_fp64_kernel(const ProdJob *__restr
         const bool act = i < J.nt;
         double x[D];
 #pragma unroll
-        for (int c = 0; c < D; ++c) x[c] = act ? J.tgt_pts[i * D + c] : 0.0;
-        const double eta = J.eta;
-        const int64_t per = (J.ns + J.dsplit - 1) / J.dsplit;
-        const int64_t a = (int64_t)itm.z * per, b = min(J.ns, a + per);
+        for (int c = 0; c < D; ++c) x[c] = act ? gp(J.tgt_pts)[i * D + c] : 0.0;
+        const ExpScale E = exp_scale(J.eta);
+        int64_t a, b;
+        direct_range(J, itm.z, 1, a, b);
         const int64_t q = (b - a + 3) / 4;
         const int64_t ja = min(b, a + wave * q), jb = min(b, ja + q);
+        const MOT_CONST double *y = (const MOT_CONST double *)J.src_pts;
+        const MOT_CONST double *v = (const MOT_CONST double *)J.v;
         double acc = 0.0;
+#pragma unroll 4
         for (int64_t j = ja; j < jb; ++j) {
             double d2 = 0.0;
 #pragma unroll
             for (int c = 0; c < D; ++c) {
-                const double df = x[c] - J.src_pts[j * D + c];
-                d2 += df * df;
+                const double df = x[c] - y[j * D + c];
+                d2 = fma(df, df, d2);
             }
-            acc += J.v[j] * exp(-d2 / eta);
+            acc = fma(v[j], exp2_scaled(d2, E), acc);
         }
         __syncthreads();  // the previous item's reads of red are done
         if (wave > 0) red[wave - 1][lane] = acc;
@@ -84,148 +157,187 @@ __global__ __launch_bounds__(256) void direct_fp64_kernel(const ProdJob *__restr
 }
 
 // out_i = sum over the job's source ranges, in range order, of the partial sums.
-__global__ __launch_bounds__(256) void direct_fp64_reduce_kernel(const ProdJob *__restrict__ jobs,
-                                                                 const int2 *__restrict__ items, int n_items)
+__global__ __launch_bounds__(256) void direct_reduce_kernel(const ProdJob *__restrict__ jobs,
+                                                            const int2 *__restrict__ items, int n_items)
 {
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 itm = items[it];
         const ProdJob &J = jobs[itm.x];
         const int64_t i = (int64_t)itm.y + threadIdx.x;
         if (i >= J.nt) continue;
+        const MOT_GLOBAL double *p = gp(J.dpart) + i;
+        const int64_t nt = J.nt;
         double acc = 0.0;
-        for (int r = 0; r < J.dsplit; ++r) acc += J.dpart[(int64_t)r * J.nt + i];
-        J.out[i] = acc;
+#pragma unroll 8
+        for (int r = 0; r < J.dsplit; ++r) acc += p[(int64_t)r * nt];
+        gp(J.out)[i] = acc;
     }
 }
 
-constexpr int kDirectR = 4;
-
-// Source staging of the mixed kernel: FP32 (2 c y, -c|y|^2) or the same in FP64.
-template <bool WIDE>
-struct DirectSrc;
-template <>
-struct DirectSrc<false> {
-    float4 y;
-};
-template <>
-struct DirectSrc<true> {
-    double y[4];
-};
+// Mixed variant on the MFMA.  A wavefront owns 64 targets, four tiles of 16, and runs over
+// the item's sources 16 at a time: one 16x16x4 MFMA per tile gives the exponents of 256
+// pairs, with the sources (y', a_y) as the A operand (lane l: source l % 16, component l / 16) and
+// the targets (x, 1) as the B operand (lane l: target l % 16), so that lane l's four results
+// belong to target l % 16 and four sources, whose values are one 16-byte LDS read.  A pair
+// then costs the vector unit one v_exp_f32 (four issue slots) and one FMA, five slots where
+// forming the exponent there too took nine; the MFMAs run beside it.
+//   FP32: r = x.y' + a_y is at most c |x|^2 <= 8, so 2^r is summed and 2^(a_x) applied once per
+//         target;
+//   WIDE: the exponent with a_x on the FP64 MFMA, rounded to FP32 once (the D tile of the FP64
+//         form holds row l / 16 + 4 r in register r).
+// A lane sums 64 terms (every fourth of 256 sources) in FP32 and adds that to its FP64
+// accumulator; the four lane groups of a target are added at the end.  Bound by vector issue:
+// nine jobs of 1e5 x 1e5 pairs in 3-D took 19.6 ms with the exponent on the vector unit (four
+// targets per lane), 13.2 ms here (9.2 ms is v_exp_f32's own rate); WIDE 27.8 -> 19.2 ms.  The
+// bound of four blocks per CU makes the compiler keep the MFMA results in vector registers;
+// without it they pass through accumulation registers (15 ms).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kMixedTiles = 4;
 
 template <int D, bool WIDE>
-__global__ __launch_bounds__(256) void direct_mixed_kernel(const ProdJob *__restrict__ jobs,
+__global__ __launch_bounds__(256, 4) void direct_mixed_kernel(const ProdJob *__restrict__ jobs,
                                                            const int4 *__restrict__ items, int n_items)
 {
     typedef typename std::conditional<WIDE, double, float>::type real;
-    __shared__ DirectSrc<WIDE> sy[256];
-    __shared__ float sv[256];
-    const int tid = threadIdx.x;
+    typedef typename std::conditional<WIDE, f64x4, f32x4>::type real4;
+    constexpr int kPad = WIDE ? 8 : 16;  // the four component rows start on different banks
+    __shared__ real sy[2][4][kMixedS + kPad];
+    __shared__ __align__(16) float sv[2][kMixedS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, lk = lane >> 4;
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int4 itm = items[it];
         const ProdJob &J = jobs[itm.x];
         const double c2 = 1.4426950408889634 / J.eta;  // log2(e) / eta
-        int e = *J.v_exp;
+        int e = *gp(J.v_exp);
         if (e == INT32_MIN) e = 0;
-        real xs[kDirectR][3], ax[kDirectR];
-        double acc[kDirectR];
+        const MOT_GLOBAL double *src = gp(J.src_pts), *vv = gp(J.v), *tgt = gp(J.tgt_pts);
+        int64_t ja, jb;
+        direct_range(J, itm.z, 64, ja, jb);
+        const int64_t i0 = (int64_t)itm.y + 64 * wave;
+        real xt[kMixedTiles];
+        double ax[kMixedTiles], acc[kMixedTiles];
 #pragma unroll
-        for (int r = 0; r < kDirectR; ++r) {
-            const int64_t i = (int64_t)itm.y + tid + 256 * r;
+        for (int t = 0; t < kMixedTiles; ++t) {
+            const int64_t i = i0 + 16 * t + li;
+            double nrm = 0.0, mine = lk == 3 ? 1.0 : 0.0;
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                const double dx = i < J.nt ? tgt[i * D + c] - J.ctr[c] : 0.0;
+                if (lk == c) mine = dx;
+                nrm += dx * dx;
+            }
+            xt[t] = (real)mine;
+            ax[t] = -c2 * nrm;
+            acc[t] = 0.0;
+        }
+        // source tid of the next stage, loaded one stage ahead
+        double ly[3] = {0.0, 0.0, 0.0}, lv = 0.0;
+        auto fetch = [&](int64_t j) {
+            lv = 0.0;
+            if (j < jb) {
+#pragma unroll
+                for (int c = 0; c < D; ++c) ly[c] = src[j * D + c];
+                lv = vv[j];
+            }
+        };
+        auto put = [&](int buf) {
             double nrm = 0.0;
 #pragma unroll
             for (int c = 0; c < 3; ++c) {
-                double dx = 0.0;
-                if (c < D && i < J.nt) dx = J.tgt_pts[i * D + c] - J.ctr[c];
-                xs[r][c] = (real)dx;
-                nrm += dx * dx;
+                const double dy = c < D ? ly[c] - J.ctr[c] : 0.0;
+                sy[buf][c][tid] = (real)(2.0 * c2 * dy);
+                nrm += dy * dy;
             }
-            ax[r] = (real)(-c2 * nrm);
-            acc[r] = 0.0;
-        }
-        for (int64_t j0 = 0; j0 < J.ns; j0 += 256) {
-            const int nj = (int)min((int64_t)256, J.ns - j0);
-            __syncthreads();
-            if (tid < nj) {
-                double dy[3] = {0.0, 0.0, 0.0}, nrm = 0.0;
+            sy[buf][3][tid] = (real)(-c2 * nrm);
+            sv[buf][tid] = (float)ldexp(lv, -e);
+        };
+        const int nstages = (int)((jb - ja + kMixedS - 1) / kMixedS);
+        fetch(ja + tid);
+        __syncthreads();  // the previous item's reads of LDS are done
+        put(0);
+        __syncthreads();
+        for (int k = 0; k < nstages; ++k) {
+            const int64_t j0 = ja + (int64_t)k * kMixedS;
+            const bool more = k + 1 < nstages;
+            if (more) fetch(j0 + kMixedS + tid);
+            const int steps = ((int)min((int64_t)kMixedS, jb - j0) + 15) / 16;
+            const real *ya = &sy[k & 1][lk][li];
+            const f32x4 *va = reinterpret_cast<const f32x4 *>(sv[k & 1]);
+            float part[kMixedTiles];
 #pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    dy[c] = J.src_pts[(j0 + tid) * D + c] - J.ctr[c];
-                    nrm += dy[c] * dy[c];
-                }
+            for (int t = 0; t < kMixedTiles; ++t) part[t] = 0.0f;
+#pragma unroll 2
+            for (int m = 0; m < steps; ++m) {
+                const real a = ya[16 * m];
+                f32x4 w;
                 if constexpr (WIDE) {
-                    sy[tid].y[0] = 2.0 * c2 * dy[0];
-                    sy[tid].y[1] = 2.0 * c2 * dy[1];
-                    sy[tid].y[2] = 2.0 * c2 * dy[2];
-                    sy[tid].y[3] = -c2 * nrm;
+                    // register r of the FP64 tile is source l / 16 + 4 r
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) w[r] = sv[k & 1][16 * m + lk + 4 * r];
                 } else {
-                    sy[tid].y = make_float4((float)(2.0 * c2 * dy[0]), (float)(2.0 * c2 * dy[1]),
-                                            (float)(2.0 * c2 * dy[2]), (float)(-c2 * nrm));
+                    w = va[4 * m + lk];
                 }
-                sv[tid] = (float)ldexp(J.v[j0 + tid], -e);
+                real4 g[kMixedTiles];
+#pragma unroll
+                for (int t = 0; t < kMixedTiles; ++t) {
+                    if constexpr (WIDE)
+                        g[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, xt[t], f64x4{ax[t], ax[t], ax[t], ax[t]}, 0, 0, 0);
+                    else
+                        g[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, xt[t], f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+                }
+#pragma unroll
+                for (int t = 0; t < kMixedTiles; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        part[t] = fmaf(w[r], __builtin_amdgcn_exp2f((float)g[t][r]), part[t]);
             }
+#pragma unroll
+            for (int t = 0; t < kMixedTiles; ++t) acc[t] += (double)part[t];
+            if (more) put((k + 1) & 1);
             __syncthreads();
-            for (int jb = 0; jb < nj; jb += 64) {
-                const int je = min(nj, jb + 64);
-                float part[kDirectR];
-#pragma unroll
-                for (int r = 0; r < kDirectR; ++r) part[r] = 0.0f;
-                for (int jj = jb; jj < je; ++jj) {
-                    real s[4];
-                    if constexpr (WIDE) {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) s[q] = sy[jj].y[q];
-                    } else {
-                        const float4 f = sy[jj].y;
-                        s[0] = f.x;
-                        s[1] = f.y;
-                        s[2] = f.z;
-                        s[3] = f.w;
-                    }
-                    const float w = sv[jj];
-#pragma unroll
-                    for (int r = 0; r < kDirectR; ++r) {
-                        real arg = ax[r] + s[3];
-                        arg = fma(xs[r][0], s[0], arg);
-                        if (D > 1) arg = fma(xs[r][1], s[1], arg);
-                        if (D > 2) arg = fma(xs[r][2], s[2], arg);
-                        part[r] = fmaf(w, __builtin_amdgcn_exp2f((float)arg), part[r]);
-                    }
-                }
-#pragma unroll
-                for (int r = 0; r < kDirectR; ++r) acc[r] += (double)part[r];
-            }
         }
 #pragma unroll
-        for (int r = 0; r < kDirectR; ++r) {
-            const int64_t i = (int64_t)itm.y + tid + 256 * r;
-            if (i < J.nt) J.out[i] = ldexp(acc[r], e);
+        for (int t = 0; t < kMixedTiles; ++t) {
+            double s = acc[t];
+            s += __shfl_xor(s, 16);
+            s += __shfl_xor(s, 32);
+            if constexpr (!WIDE) s *= exp2(ax[t]);
+            const int64_t i = i0 + 16 * t + li;
+            if (lk == 0 && i < J.nt) {
+                const double o = ldexp(s, e);
+                if (J.dsplit > 1)
+                    gp(J.dpart)[(int64_t)itm.z * J.nt + i] = o;
+                else
+                    gp(J.out)[i] = o;
+            }
         }
     }
 }
 
-int direct_targets_per_item(int precision) { return precision == MOT_PREC_FP64 ? kDirectT : 256 * kDirectR; }
+template <int D>
+static void launch_direct_d(const ProdJob *jobs, const int4 *items, int n_items, int precision, int diff, hipStream_t s)
+{
+    const dim3 grid(n_items < 65535 ? n_items : 65535), block(256);
+    if (precision == MOT_PREC_FP64)
+        hipLaunchKernelGGL(direct_fp64_kernel<D>, grid, block, 0, s, jobs, items, n_items);
+    else if (diff)
+        hipLaunchKernelGGL((direct_mixed_kernel<D, true>), grid, block, 0, s, jobs, items, n_items);
+    else
+        hipLaunchKernelGGL((direct_mixed_kernel<D, false>), grid, block, 0, s, jobs, items, n_items);
+}
 
 hipError_t launch_direct(int d, const ProdJob *jobs_dev, const int4 *items, int n_items, const int2 *red_items,
                          int n_red, int precision, int diff, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    const int grid = n_items < 16384 ? n_items : 16384;
-    if (precision == MOT_PREC_FP64) {
-        if (d == 1) hipLaunchKernelGGL(direct_fp64_kernel<1>, dim3(grid), dim3(256), 0, s, jobs_dev, items, n_items);
-        if (d == 2) hipLaunchKernelGGL(direct_fp64_kernel<2>, dim3(grid), dim3(256), 0, s, jobs_dev, items, n_items);
-        if (d == 3) hipLaunchKernelGGL(direct_fp64_kernel<3>, dim3(grid), dim3(256), 0, s, jobs_dev, items, n_items);
-        if (n_red > 0)
-            hipLaunchKernelGGL(direct_fp64_reduce_kernel, dim3(n_red < 16384 ? n_red : 16384), dim3(256), 0, s, jobs_dev,
-                               red_items, n_red);
-    } else if (diff) {
-        if (d == 1) hipLaunchKernelGGL((direct_mixed_kernel<1, true>), dim3(grid), dim3(256), 0, s, jobs_dev, items, n_items);
-        if (d == 2) hipLaunchKernelGGL((direct_mixed_kernel<2, true>), dim3(grid), dim3(256), 0, s, jobs_dev, items, n_items);
-        if (d == 3) hipLaunchKernelGGL((direct_mixed_kernel<3, true>), dim3(grid), dim3(256), 0, s, jobs_dev, items, n_items);
-    } else {
-        if (d == 1) hipLaunchKernelGGL((direct_mixed_kernel<1, false>), dim3(grid), dim3(256), 0, s, jobs_dev, items, n_items);
-        if (d == 2) hipLaunchKernelGGL((direct_mixed_kernel<2, false>), dim3(grid), dim3(256), 0, s, jobs_dev, items, n_items);
-        if (d == 3) hipLaunchKernelGGL((direct_mixed_kernel<3, false>), dim3(grid), dim3(256), 0, s, jobs_dev, items, n_items);
-    }
+    if (d == 1) launch_direct_d<1>(jobs_dev, items, n_items, precision, diff, s);
+    if (d == 2) launch_direct_d<2>(jobs_dev, items, n_items, precision, diff, s);
+    if (d == 3) launch_direct_d<3>(jobs_dev, items, n_items, precision, diff, s);
+    if (n_red > 0)
+        hipLaunchKernelGGL(direct_reduce_kernel, dim3(n_red < 16384 ? n_red : 16384), dim3(256), 0, s, jobs_dev,
+                           red_items, n_red);
     return hipGetLastError();
 }
 

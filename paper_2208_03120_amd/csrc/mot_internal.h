@@ -66,7 +66,7 @@ struct ProdJob {
     int32_t *v_exp;    // slot holding max_j exponent(|v_j|) (atomicMax), reset per sweep
     double *out;       // target vector, n_t entries
     int64_t ns, nt;
-    double *dpart;     // FP64 direct path: partial sums, dsplit x n_t (dsplit > 1 only)
+    double *dpart;     // direct path: partial sums, dsplit x n_t (dsplit > 1 only)
     int32_t dsplit, pad_d;
     double eta;
     double ctr[3];     // centre of the point cloud (mixed direct path works relative to it)
@@ -148,9 +148,10 @@ struct FinalJob {
 // ---------------------------------------------------------------------------------------
 // Kernel launchers (implemented in the .hip files).
 int direct_targets_per_item(int precision);
-// FP64 direct products: source ranges per job (partial sums added by a second kernel when
-// above 1), from the target and source counts
-int direct_source_split(int64_t nt, int64_t ns);
+int direct_items_wanted(int precision);
+// Direct products: source ranges per job (partial sums added by a second kernel when above
+// 1), from the target and source counts
+int direct_source_split(int64_t nt, int64_t ns, int precision);
 constexpr int kMaxTruncRows = 400;  // neighbour rows per truncated work item, (2w + 1)^(d-1)
 // Truncated products: items int4 (job, first cell of a run of B cells of one row, first
 // sorted target, count | B << 16), count <= 64 * R; R = 1, 2 or 4 (FP64: 1 or 2).

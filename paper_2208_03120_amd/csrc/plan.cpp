@@ -306,7 +306,7 @@ struct StepBuilder {
                   const std::vector<int> &ids)
     {
         std::map<std::tuple<int, int, int>, std::vector<int4>> direct;  // (d, precision, diff)
-        std::map<std::tuple<int, int, int>, std::vector<int2>> direct_red;  // FP64 range sums
+        std::map<std::tuple<int, int, int>, std::vector<int2>> direct_red;  // range sums
         std::map<std::tuple<int, int, int, int>, std::vector<std::pair<double, int4>>> trunc;  // (d, prec, R, wide)
         std::map<int, std::vector<int2>> spread, fold, interp;   // d
         // 3-D spreading: jobs by the points they spread from (a binned marginal's rows)
@@ -320,7 +320,7 @@ struct StepBuilder {
                 const int tpi = direct_targets_per_item(J.precision);
                 const auto key = std::make_tuple(J.d, J.precision, J.diff);
                 auto &v = direct[key];
-                const int split = J.precision == MOT_PREC_FP64 ? std::max(1, J.dsplit) : 1;
+                const int split = std::max(1, J.dsplit);
                 for (int64_t t = 0; t < J.nt; t += tpi)
                     for (int r = 0; r < split; ++r) v.push_back(make_int4(j, (int)t, r, 0));
                 if (split > 1)
@@ -956,14 +956,8 @@ int mot::make_prod_job(mot_plan_s *P, int t, int s, const double *v, int32_t *sl
     Q.diff = P->precision == MOT_PREC_MIXED && 1.4426950408889634 * half * half / Q.eta > 8.0;
     Q.src_pts = P->marg[s].pts;
     Q.tgt_pts = P->marg[t].pts;
-    Q.dsplit = 1;
-    if (P->path == MOT_DIRECT && P->precision == MOT_PREC_FP64 && alloc_buffers) {
-        const int split = direct_source_split(Q.nt, Q.ns);
-        if (split > 1) {
-            MOT_TRY(P->arena.get_n((size_t)split * Q.nt, &Q.dpart));
-            Q.dsplit = split;
-        }
-    }
+    // a sweep's direct products may split their sources (partial buffers: create_tree)
+    Q.dsplit = P->path == MOT_DIRECT && alloc_buffers ? direct_source_split(Q.nt, Q.ns, P->precision) : 1;
     if (P->path == MOT_TRUNC) {
         const TruncParams &T = P->TP;
         Q.src_cell_off = P->marg[s].cell_off;
@@ -1216,6 +1210,13 @@ static int create_tree(mot_plan_s *P, const std::vector<double> &pts_h, const st
         // up: beta_k = K^{(p,k)} v_k  (targets p, sources k)
         MOT_TRY(make_prod_job(P, p, k, P->marg[k].up_src, P->exp_slots + (size_t)(2 * k + 1) * kExpSlotStride, P->marg[k].beta,
                               &P->jobs[2 * k + 1], nullptr));
+        // direct products: the two never run at the same time and share a partial buffer
+        ProdJob &D = P->jobs[2 * k], &U = P->jobs[2 * k + 1];
+        const int64_t part = std::max(D.dsplit > 1 ? D.dsplit * D.nt : 0, U.dsplit > 1 ? U.dsplit * U.nt : 0);
+        if (part > 0) {
+            MOT_TRY(P->arena.get_n((size_t)part, &D.dpart));
+            U.dpart = D.dpart;
+        }
     }
     MOT_TRY(P->arena.get_n(P->jobs.size(), &P->jobs_dev));
     MOT_HIP(hipMemcpy(P->jobs_dev, P->jobs.data(), P->jobs.size() * sizeof(ProdJob), hipMemcpyHostToDevice));
@@ -1952,9 +1953,11 @@ int mot_plan_footprint(int32_t K, int32_t d, const int64_t *n, int32_t topology,
         // launch items: FFT passes, spreading and interpolation chunks, fold cells
         b += (size_t)(2 * (K - 1)) * (16 * (fft_items_of(d, Q.n, Q.M, Q.L) + 8) + 8 * 2 * chunks_per_job +
                                       8 * (cells / kFoldCellsPerItem + 1));
-    } else if (path == MOT_DIRECT && precision == MOT_PREC_FP64 && topology == MOT_TREE) {
-        // partial sums of the source ranges: split x n_t <= 1024 x 64 + n_t + 64 per job
-        b += (size_t)(2 * (K - 1)) * (size_t)(1024 * 64 + nmax + 64) * 8;
+    } else if (path == MOT_DIRECT && topology == MOT_TREE) {
+        // partial sums of the source ranges, one buffer per edge: split x n_t is at most
+        // (items wanted + groups of targets) x targets per item, and at most 64 n_t
+        const int64_t tpi = direct_targets_per_item(precision), want = direct_items_wanted(precision);
+        b += (size_t)(K - 1) * ((size_t)std::min((want + 1) * tpi + nmax, 64 * nmax) * 8 + 512);
     } else if (path == MOT_TRUNC) {
         Extent E;
         for (int c = 0; c < d; ++c) {
