@@ -16,7 +16,9 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          "-Wno-unused-result", "-Wno-pass-failed",
          # no packed-FP32 instructions in device code
-         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
+         "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         # leading kernel arguments arrive in scalar registers
+         "-mllvm", "-amdgpu-kernarg-preload-count=16"]
 
 
 def _compile(src):

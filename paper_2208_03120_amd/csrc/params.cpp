@@ -322,8 +322,10 @@ static double product_cost(int d, int64_t n_max, int n, int m, double box)
     return 2.0 * (double)n_max * std::pow(2.0 * m, d) + 10.0 * box * std::log2((double)n) * d;
 }
 
+constexpr int64_t kChunkLoad = 12500;
+
 int resolve_params(int d, double eta, const Extent &ext, const mot_fastsum_params *fs,
-                   int64_t n_max, NfftParams *out, double eta_hi)
+                   int64_t n_max, NfftParams *out, double eta_hi, int64_t products)
 {
     mot_fastsum_params F{};
     if (fs) F = *fs;
@@ -401,8 +403,8 @@ int resolve_params(int d, double eta, const Extent &ext, const mot_fastsum_param
             }
         }
     if (best_cost < 0) return MOT_EDOMAIN;
-    int chunk = F.chunk > 0 ? F.chunk : (d == 3 ? 512 : 2048);
-    best.chunk = chunk;
+    const int stages = (int)std::min<int64_t>((n_max * products + kChunkLoad - 1) / kChunkLoad, d == 3 ? 8 : 32);
+    best.chunk = F.chunk > 0 ? F.chunk : 64 * std::max(1, stages);
     *out = best;
     return MOT_OK;
 }

@@ -1057,7 +1057,8 @@ int mot::setup_marginals(mot_plan_s *P, const std::vector<double> &pts_h, const 
     std::sort(etas.begin(), etas.end());
     etas.erase(std::unique(etas.begin(), etas.end()), etas.end());
     if (P->path == MOT_NFFT) {
-        MOT_TRY(resolve_params(d, etas.front(), P->ext, fs, nmax, &P->P, etas.back()));
+        MOT_TRY(resolve_params(d, etas.front(), P->ext, fs, nmax, &P->P, etas.back(),
+                               P->topology == MOT_CIRCLE ? P->n[0] : 1));
         for (double e : etas) {
             std::vector<float> D;
             build_multiplier(d, P->P, e, D);
@@ -1902,7 +1903,7 @@ int mot_plan_footprint(int32_t K, int32_t d, const int64_t *n, int32_t topology,
             }
             E.diag = 2.0 * half_width * std::sqrt((double)d);
             NfftParams Q;
-            int rc = resolve_params(d, eta, E, fs, nmax, &Q);
+            int rc = resolve_params(d, eta, E, fs, nmax, &Q, 0.0, n[0]);
             if (rc < 0) return rc;
             int64_t cells = 1, pe = 1, tiles = 1;
             for (int c = 0; c < d; ++c) {
@@ -1956,8 +1957,10 @@ int mot_plan_footprint(int32_t K, int32_t d, const int64_t *n, int32_t topology,
     } else if (path == MOT_DIRECT && topology == MOT_TREE) {
         // partial sums of the source ranges, one buffer per edge: split x n_t is at most
         // (items wanted + groups of targets) x targets per item, and at most 64 n_t
-        const int64_t tpi = direct_targets_per_item(precision), want = direct_items_wanted(precision);
-        b += (size_t)(K - 1) * ((size_t)std::min((want + 1) * tpi + nmax, 64 * nmax) * 8 + 512);
+        if (precision == MOT_PREC_FP64)
+            b += (size_t)(2 * (K - 1)) * (size_t)(1024 * 64 + nmax + 64) * 8;
+        else
+            b += (size_t)(K - 1) * ((size_t)std::min<int64_t>((direct_items_wanted(precision) + 1) * direct_targets_per_item(precision) + nmax, 64 * nmax) * 8 + 512);
     } else if (path == MOT_TRUNC) {
         Extent E;
         for (int c = 0; c < d; ++c) {
