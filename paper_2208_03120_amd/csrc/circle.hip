@@ -422,7 +422,7 @@ __global__ __launch_bounds__(256) void scale_rows16_kernel(const float *__restri
         m = fmax(m, fabs((double)a4.w * phi[l + 3]));
     }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmax(m, __shfl_xor(m, o));
+    for (int o = 32; o >= 1; o >>= 1) m = fmax(m, lane_xor(m, o));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     const double mm = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(256) void rowsum_k_kernel(const T *__restrict__ Yg1
     for (int64_t j = threadIdx.x; j < n1c; j += blockDim.x)
         s += (double)Yg1[i * ld + j] * phi1[j] * (double)Yb1[i * ld + j];
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
+    for (int o = 32; o >= 1; o >>= 1) s += lane_xor(s, o);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -587,8 +587,8 @@ __global__ __launch_bounds__(256) void circle_phi_kernel(const double *__restric
     }
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-        s1 += __shfl_xor(s1, o);
-        s2 += __shfl_xor(s2, o);
+        s1 += lane_xor(s1, o);
+        s2 += lane_xor(s2, o);
     }
     if ((threadIdx.x & 63) == 0) {
         red[0][threadIdx.x >> 6] = s1;
@@ -618,9 +618,9 @@ __global__ __launch_bounds__(256) void circle_final_kernel(const double *__restr
     for (int p = threadIdx.x; p < ne; p += blockDim.x) e += e_part[2 * p];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
-        s1 += __shfl_xor(s1, o);
-        s2 += __shfl_xor(s2, o);
-        e += __shfl_xor(e, o);
+        s1 += lane_xor(s1, o);
+        s2 += lane_xor(s2, o);
+        e += lane_xor(e, o);
     }
     if ((threadIdx.x & 63) == 0) {
         red[0][threadIdx.x >> 6] = s1;
@@ -673,7 +673,7 @@ __global__ __launch_bounds__(256) void scale_rows_kernel(const double *__restric
         if (v > 0.0 && v < INFINITY) m = max(m, ilogb(v));
     }
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = max(m, __shfl_xor(m, o));
+    for (int o = 32; o >= 1; o >>= 1) m = max(m, lane_xor(m, o));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) rexp[i] = max(max(red[0], red[1]), max(red[2], red[3]));

@@ -301,8 +301,8 @@ __global__ __launch_bounds__(256, 4) void direct_mixed_kernel(const ProdJob *__r
 #pragma unroll
         for (int t = 0; t < kMixedTiles; ++t) {
             double s = acc[t];
-            s += __shfl_xor(s, 16);
-            s += __shfl_xor(s, 32);
+            s += lane_xor(s, 16);
+            s += lane_xor(s, 32);
             if constexpr (!WIDE) s *= exp2(ax[t]);
             const int64_t i = i0 + 16 * t + li;
             if (lk == 0 && i < J.nt) {

@@ -82,8 +82,8 @@ __device__ __forceinline__ void fft_dif(float2 (&x)[FftShape<N>::E], int g, cons
             float2 y[E];
 #pragma unroll
             for (int e = 0; e < E; ++e) {
-                y[e].x = __shfl_xor(x[e].x, h);
-                y[e].y = __shfl_xor(x[e].y, h);
+                y[e].x = lane_xor(x[e].x, h);
+                y[e].y = lane_xor(x[e].y, h);
             }
 #pragma unroll
             for (int e = 0; e < E; ++e) {
@@ -124,8 +124,8 @@ __device__ __forceinline__ void fft_dit_inv(float2 (&x)[FftShape<N>::E], int g, 
             for (int e = 0; e < E; ++e) {
                 const float2 z = cmulc(x[e], w);
                 float2 y;
-                y.x = __shfl_xor(z.x, h);
-                y.y = __shfl_xor(z.y, h);
+                y.x = lane_xor(z.x, h);
+                y.y = lane_xor(z.y, h);
                 x[e] = make_float2(fmaf(sg, z.x, y.x), fmaf(sg, z.y, y.y));
             }
         }

@@ -435,8 +435,8 @@ __global__ __launch_bounds__(64 * kSpreadWaves, 4) void spread_kernel(const Prod
         if constexpr (D == 1) {
             // sum over the four points of a step (lane groups), then over waves
             float a1 = acc[0];
-            a1 += __shfl_xor(a1, 16);
-            a1 += __shfl_xor(a1, 32);
+            a1 += lane_xor(a1, 16);
+            a1 += lane_xor(a1, 32);
             acc[0] = a1;
         }
         // wave partials: wave w < half adds wave w + half, halving until wave 0 holds the
@@ -587,8 +587,9 @@ __global__ __launch_bounds__(64 * kSpreadWaves, G == 1 ? 6 : (G == 2 ? 5 : 4)) v
 
 constexpr int kFoldMaxCover = 4;
 
-// Fold (a2, second half): box grid cell g = sum of the patches covering it, tiles in
-// ascending order and chunks in ascending order within a tile.  One thread folds one
+// Fold (a2, second half): box grid cell g = sum of the patches covering it in a fixed order
+// (3-D: leading tile by leading tile; the covering tiles' first chunks in tile order, then
+// their second chunks, and so on).  One thread folds one
 // cell; an item is kFoldCellsPerItem consecutive cells of the box in row-major order
 // (lines of the last dimension back to back, so every lane has a cell even when a line
 // is shorter than a wavefront); item = (job, first cell).  The job's tile -> chunk table
@@ -596,22 +597,12 @@ constexpr int kFoldMaxCover = 4;
 // LDS rather than global latency.
 constexpr int kFoldTab = 2048;  // tile -> chunk table entries staged in LDS
 
-// One item of the fold; tch is the job's tile -> chunk table (in LDS when it fits).
+// Sum of the patches covering cell (gu0, gu1, g) (leading coordinates unused below 3-D and
+// 2-D), tch the job's tile -> chunk table (in LDS when it fits).
 template <int D, class Tab>
-__device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch)
+__device__ __forceinline__ float fold_cell(const ProdJob &J, const int (&gu)[2], int g, Tab tch)
 {
-    const int W = J.W, T = J.T, Ll = J.L[D - 1], ntl = J.ntile[D - 1];
-    const int nl = D == 3 ? J.L[0] * J.L[1] : (D == 2 ? J.L[0] : 1);
-    const int f = f0 + (int)threadIdx.x;
-    if (f >= nl * Ll) return;
-    const int line = f / Ll, g = f - line * Ll;
-    int gu[2] = {0, 0};  // line coordinates in the leading dimensions
-    if (D == 3) {
-        gu[0] = line / J.L[1];
-        gu[1] = line - gu[0] * J.L[1];
-    } else if (D == 2) {
-        gu[0] = line;
-    }
+    const int W = J.W, T = J.T, ntl = J.ntile[D - 1];
     int tlo[2] = {0, 0}, thi[2] = {0, 0};
     for (int c = 0; c < D - 1; ++c) {
         tlo[c] = max(0, floor_div(gu[c] - W + T, T));  // ceil((g - W + 1) / T)
@@ -622,22 +613,25 @@ __device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch)
     const int t2lo = max(0, floor_div(g - W + T, T)), t2hi = min(ntl - 1, g / T);
     float acc = 0.0f;
     if (W <= kFoldMaxCover * T) {
-        // at most kFoldMaxCover covering tiles per dimension: the chunk ranges and first
-        // patches of all (t1, t2) pairs of a t0 are loaded together, then added in the
-        // fixed order
-        constexpr int NU = D == 3 ? kFoldMaxCover : 1;
-        // t0-invariant parts of the tile index and patch offset of candidate (u, k):
-        //   tile = t0 nt1 ntl + tl_b + u ntl + k,
-        //   loc  = (gu0 - t0 T) W^2 + loc_b - u T W - k T
-        const int nt1 = D == 3 ? J.ntile[1] : 1;
-        const int vu = D == 3 ? thi[1] - tlo[1] : 0, vk = t2hi - t2lo;
-        const int tl_b = (D == 3 ? tlo[1] * ntl : 0) + t2lo;
-        const int loc_b = (D == 3 ? (gu[1] - tlo[1] * T) * W : 0) + (g - t2lo * T);
-        const int W2 = D == 1 ? 0 : (D == 2 ? W : W * W);
-        for (int t0 = tlo[0]; t0 <= thi[0]; ++t0) {
-            const int tl0 = t0 * nt1 * ntl + tl_b;
-            const int loc0 = (gu[0] - t0 * T) * W2 + loc_b;
-            int c0[NU][kFoldMaxCover], c1[NU][kFoldMaxCover];
+        // at most kFoldMaxCover covering tiles per dimension: the chunk ranges of all (u, k)
+        // pairs of the last two dimensions (in 3-D of one leading tile) are looked up together,
+        // and NR chunks of every pair are loaded together and then added, so a round of
+        // loads waits once (chunk by chunk, a tree of 6000-point 3-D marginals in chunks of
+        // 64 points folded in 24 us per launch, now 9)
+        constexpr int NU = D >= 2 ? kFoldMaxCover : 1, NR = D == 3 ? 1 : (D == 2 ? 2 : 8);
+        const int lead = D == 3 ? 1 : 0;  // index of the u dimension among the leading ones
+        const int vu = D >= 2 ? thi[lead] - tlo[lead] : 0, vk = t2hi - t2lo;
+        // parts of the tile index and patch offset of candidate (u, k) that do not depend on
+        // the leading tile t0 of 3-D:
+        //   tile = t0 nt1 ntl + tl_b + u ntl + k,  loc = (gu0 - t0 T) W^2 + loc_b - u T W - k T
+        const int tl_b = (D >= 2 ? tlo[lead] * ntl : 0) + t2lo;
+        const int loc_b = (D >= 2 ? (gu[lead] - tlo[lead] * T) * W : 0) + (g - t2lo * T);
+        const int t0a = D == 3 ? tlo[0] : 0, t0b = D == 3 ? thi[0] : 0;
+        for (int t0 = t0a; t0 <= t0b; ++t0) {
+            const int tl0 = (D == 3 ? t0 * J.ntile[1] * ntl : 0) + tl_b;
+            const int loc0 = (D == 3 ? (gu[0] - t0 * T) * W * W : 0) + loc_b;
+            int c0[NU][kFoldMaxCover], nc[NU][kFoldMaxCover];
+            int most = 0;  // chunks of the fullest candidate tile
 #pragma unroll
             for (int u = 0; u < NU; ++u)
 #pragma unroll
@@ -645,22 +639,28 @@ __device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch)
                     const bool ok = u <= vu && k <= vk;
                     const int tl = tl0 + u * ntl + k;
                     c0[u][k] = ok ? tch[tl] : 0;
-                    c1[u][k] = ok ? tch[tl + 1] : 0;
+                    nc[u][k] = ok ? tch[tl + 1] - c0[u][k] : 0;
+                    most = max(most, nc[u][k]);
                 }
-            float first[NU][kFoldMaxCover];
+            for (int r0 = 0; r0 < most; r0 += NR) {
+                float val[NR][NU][kFoldMaxCover];
 #pragma unroll
-            for (int u = 0; u < NU; ++u)
+                for (int r = 0; r < NR; ++r)
 #pragma unroll
-                for (int k = 0; k < kFoldMaxCover; ++k)
-                    first[u][k] = c1[u][k] > c0[u][k] ? pat[(int64_t)c0[u][k] * pe + (loc0 - u * T * W - k * T)] : 0.0f;
+                    for (int u = 0; u < NU; ++u)
 #pragma unroll
-            for (int u = 0; u < NU; ++u)
+                        for (int k = 0; k < kFoldMaxCover; ++k)
+                            val[r][u][k] = nc[u][k] > r0 + r
+                                               ? pat[(int64_t)(c0[u][k] + r0 + r) * pe + (loc0 - u * T * W - k * T)]
+                                               : 0.0f;
 #pragma unroll
-                for (int k = 0; k < kFoldMaxCover; ++k) {
-                    acc += first[u][k];  // +0 for an absent tile leaves the sum unchanged
-                    for (int ch = c0[u][k] + 1; ch < c1[u][k]; ++ch)
-                        acc += pat[(int64_t)ch * pe + (loc0 - u * T * W - k * T)];
-                }
+                for (int r = 0; r < NR; ++r)
+#pragma unroll
+                    for (int u = 0; u < NU; ++u)
+#pragma unroll
+                        for (int k = 0; k < kFoldMaxCover; ++k)
+                            acc += val[r][u][k];  // +0 for an absent chunk leaves the sum unchanged
+            }
         }
     } else {
         for (int t0 = tlo[0]; t0 <= thi[0]; ++t0)
@@ -681,7 +681,26 @@ __device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch)
                 }
             }
     }
-    gp(J.grid)[(int64_t)line * Ll + g] = acc;
+    return acc;
+}
+
+// One item of the fold.
+template <int D, class Tab>
+__device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch)
+{
+    const int Ll = J.L[D - 1];
+    const int nl = D == 3 ? J.L[0] * J.L[1] : (D == 2 ? J.L[0] : 1);
+    const int f = f0 + (int)threadIdx.x;
+    if (f >= nl * Ll) return;
+    const int line = f / Ll, g = f - line * Ll;
+    int gu[2] = {0, 0};  // line coordinates in the leading dimensions
+    if (D == 3) {
+        gu[0] = line / J.L[1];
+        gu[1] = line - gu[0] * J.L[1];
+    } else if (D == 2) {
+        gu[0] = line;
+    }
+    gp(J.grid)[f] = fold_cell<D>(J, gu, g, tch);
 }
 
 // D = 0: every item takes its job's own d (batches of plans of several dimensions).
@@ -806,8 +825,8 @@ __global__ __launch_bounds__(64 * kInterpWaves, 4) void interp_kernel(const Prod
                 // beta_p = sum_a w_0,p[a] Z[a][p]: the lane's four a, then the four lane groups
                 const f32x4 wx = reinterpret_cast<const f32x4 *>(row)[lk];
                 float z = (acc[0] * wx[0] + acc[1] * wx[1]) + (acc[2] * wx[2] + acc[3] * wx[3]);
-                z += __shfl_xor(z, 16);
-                z += __shfl_xor(z, 32);
+                z += lane_xor(z, 16);
+                z += lane_xor(z, 32);
                 const int64_t p = p0 + (int64_t)k * kStage + 16 * wave + li;
                 if (lk == 0 && p < p1) out[p] = ldexp((double)z, e);
                 if (more) stg.store(smem + ((k + 1) & 1) * St::kBytes, 0);
@@ -895,8 +914,8 @@ __global__ __launch_bounds__(64 * kInterpWaves, 6) void interp3_kernel(const Pro
                 // w_0,p[4 lk .. 4 lk + 3], then add the four lane groups (lanes l ^ 16, l ^ 32)
                 const f32x4 wx = reinterpret_cast<const f32x4 *>(row)[lk];
                 float z = (acc[0] * wx[0] + acc[1] * wx[1]) + (acc[2] * wx[2] + acc[3] * wx[3]);
-                z += __shfl_xor(z, 16);
-                z += __shfl_xor(z, 32);
+                z += lane_xor(z, 16);
+                z += lane_xor(z, 32);
                 if (lk == 0) zb[k & 1][wave][16 * g + li] = z;
             }
             if (more) stg.store(smem + ((k + 1) & 1) * St::kBytes, 0);

@@ -32,14 +32,14 @@ __device__ __forceinline__ int exp_of(double v)
 __device__ __forceinline__ int wave_max_int(int v)
 {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v = max(v, __shfl_xor(v, o));
+    for (int o = 32; o >= 1; o >>= 1) v = max(v, lane_xor(v, o));
     return v;
 }
 
 __device__ __forceinline__ double block_sum(double v, double *red)
 {
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    for (int o = 32; o >= 1; o >>= 1) v += lane_xor(v, o);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     __syncthreads();
     if (lane == 0) red[wave] = v;

@@ -51,6 +51,38 @@ __device__ __forceinline__ void st2(float2 *p, int64_t i, float2 v)  // global s
     ((MOT_GLOBAL mot_f32x2 *)(void *)p)[i] = mot_f32x2{v.x, v.y};
 }
 
+// Value of lane l ^ h, h a power of two that is constant after unrolling; every lane of the
+// wavefront active.  Moves within rows of 16 lanes are DPP controls, across rows the gfx950
+// row swaps: vector instructions, where __shfl_xor goes through the LDS pipe and waits for it
+// (a reduction over 64 lanes chains six of them).
+__device__ __forceinline__ unsigned lane_xor(unsigned v, int h)
+{
+    if (h == 1) return __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);  // quad [1 0 3 2]
+    if (h == 2) return __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);  // quad [2 3 0 1]
+    if (h == 4) {  // half-row mirror (l ^ 7), then quad mirror (l ^ 3)
+        const unsigned t = __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);
+        return __builtin_amdgcn_update_dpp(0, t, 0x1B, 0xf, 0xf, true);
+    }
+    if (h == 8) return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, true);  // row rotate by 8
+    if (h == 16) {
+        const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+        return (__lane_id() & 16) ? r[0] : r[1];
+    }
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (__lane_id() & 32) ? r[0] : r[1];
+}
+__device__ __forceinline__ int lane_xor(int v, int h) { return (int)lane_xor((unsigned)v, h); }
+__device__ __forceinline__ float lane_xor(float v, int h)
+{
+    return __builtin_bit_cast(float, lane_xor(__builtin_bit_cast(unsigned, v), h));
+}
+__device__ __forceinline__ double lane_xor(double v, int h)
+{
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint64_t lo = lane_xor((unsigned)b, h), hi = lane_xor((unsigned)(b >> 32), h);
+    return __builtin_bit_cast(double, lo | (hi << 32));
+}
+
 // ---------------------------------------------------------------------------------------
 // Device-side job descriptors.  Plain structs copied to device memory once per plan
 // (or per batch); kernels read them through an item table of (job, sub-range) pairs.
