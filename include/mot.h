@@ -255,7 +255,7 @@ const char *mot_strerror(int status);
 /* Per-step device timing of the plan's sweep (tree plans): runs `sweeps` sweeps with a
  * HIP event pair around every launch of the sweep schedule on the plan's stream and
  * reports, per schedule position, the kernel kind and the mean duration.  kind:
- * 0 node update, 1 direct product, 2 spread, 3 fold, 4 FFT pass (fft_kind 0..7),
+ * 0 node update, 1 direct product, 2 spread, 3 fold, 4 FFT pass (fft_kind 0..8),
  * 5 interpolation, 6 sweep finalisation, 7 fill, 8 truncated product.  group: jobs per
  * item of a 3-D spreading launch (jobs spreading from the same points share items), else 0.
  * Returns the number of entries written (<= max_out) or an error.  The sweeps advance the

@@ -147,6 +147,7 @@ struct Step {
     int lane = 0;                 // i >= 1: runs on side stream i - 1 between ST_FORK and ST_JOIN
     int d = 0, n = 0, fft_kind = 0, precision = 0, max_patch = 0, trunc_r = 0, diff = 0;
     int group = 0;                // 3-D spreading: jobs per item (items int4)
+    int lds = 0;                  // one-launch transforms: LDS bytes of the largest job
     int max_children = 0;         // node update: most children of a node in the launch
     const void *jobs = nullptr;   // device ProdJob / NodeJob / FinalJob array
     const void *items = nullptr;  // device int2 / int4 array
@@ -187,7 +188,7 @@ struct MargDev {
     // NFFT layout
     float *win = nullptr;    // window rows, n x d x 16
     int32_t *chunk_start = nullptr, *chunk_tile = nullptr, *tile_chunks = nullptr;
-    int nchunks = 0;
+    int nchunks = 0, tile_most = 0;  // chunks; most chunks of one tile
     std::vector<int32_t> h_chunk_tile;
     std::vector<int32_t> h_chunk_start;  // chunk bounds, nchunks + 1 entries
     // truncated path: sorted point range of each cell

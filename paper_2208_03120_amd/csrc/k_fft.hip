@@ -558,8 +558,7 @@ __global__ __launch_bounds__(kSlabThreads) void fft_slab_mixed_kernel(const Prod
 template <int N>
 static hipError_t launch_n(int kind, const ProdJob *jobs, const int4 *items, int n_items,
                            const float2 *tw, hipStream_t s)
-{
-    const int grid = n_items < 8192 ? n_items : 8192;
+{    const int grid = n_items < 8192 ? n_items : 8192;
     switch (kind) {
     case 0: hipLaunchKernelGGL((fft_pass_kernel<N, 0>), dim3(grid), dim3(256), 0, s, jobs, items, n_items, tw); break;
     case 1: hipLaunchKernelGGL((fft_pass_kernel<N, 1>), dim3(grid), dim3(256), 0, s, jobs, items, n_items, tw); break;

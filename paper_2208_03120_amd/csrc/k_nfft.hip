@@ -17,7 +17,7 @@
 // read rates), and the grid does not depend on which other jobs share a launch.
 // Interpolation keeps a tile's patch of the result grid in registers and contracts it
 // with the points' windows, again on the MFMA units.
-#include "mot_internal.h"
+#include "nfft_device.h"
 
 namespace mot {
 
@@ -284,11 +284,6 @@ hipError_t launch_window_rows(int d, int64_t npts, const double *pts, double s, 
     hipLaunchKernelGGL(window_rows_kernel, dim3(blocks), dim3(256), 0, st, d, npts, pts, s, o[0],
                        d > 1 ? o[1] : 0.0, d > 2 ? o[2] : 0.0, T, m, b, 1.0 / sinh(b * m), rows);
     return hipGetLastError();
-}
-
-__device__ __forceinline__ int floor_div(int a, int b)  // floor(a / b) for b > 0
-{
-    return a >= 0 ? a / b : -((-a + b - 1) / b);
 }
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -585,8 +580,6 @@ __global__ __launch_bounds__(64 * kSpreadWaves, G == 1 ? 6 : (G == 2 ? 5 : 4)) v
     }
 }
 
-constexpr int kFoldMaxCover = 4;
-
 // Fold (a2, second half): box grid cell g = sum of the patches covering it in a fixed order
 // (3-D: leading tile by leading tile; the covering tiles' first chunks in tile order, then
 // their second chunks, and so on).  One thread folds one
@@ -595,95 +588,6 @@ constexpr int kFoldMaxCover = 4;
 // is shorter than a wavefront); item = (job, first cell).  The job's tile -> chunk table
 // is staged in LDS when it fits, so the chunk lookups of a thread's covering tiles cost
 // LDS rather than global latency.
-constexpr int kFoldTab = 2048;  // tile -> chunk table entries staged in LDS
-
-// Sum of the patches covering cell (gu0, gu1, g) (leading coordinates unused below 3-D and
-// 2-D), tch the job's tile -> chunk table (in LDS when it fits).
-template <int D, class Tab>
-__device__ __forceinline__ float fold_cell(const ProdJob &J, const int (&gu)[2], int g, Tab tch)
-{
-    const int W = J.W, T = J.T, ntl = J.ntile[D - 1];
-    int tlo[2] = {0, 0}, thi[2] = {0, 0};
-    for (int c = 0; c < D - 1; ++c) {
-        tlo[c] = max(0, floor_div(gu[c] - W + T, T));  // ceil((g - W + 1) / T)
-        thi[c] = min(J.ntile[c] - 1, gu[c] / T);
-    }
-    const int pe = D == 3 ? W * W * W : (D == 2 ? W * W : W);
-    const MOT_GLOBAL float *pat = gp(J.patches);
-    const int t2lo = max(0, floor_div(g - W + T, T)), t2hi = min(ntl - 1, g / T);
-    float acc = 0.0f;
-    if (W <= kFoldMaxCover * T) {
-        // at most kFoldMaxCover covering tiles per dimension: the chunk ranges of all (u, k)
-        // pairs of the last two dimensions (in 3-D of one leading tile) are looked up together,
-        // and NR chunks of every pair are loaded together and then added, so a round of
-        // loads waits once (chunk by chunk, a tree of 6000-point 3-D marginals in chunks of
-        // 64 points folded in 24 us per launch, now 9)
-        constexpr int NU = D >= 2 ? kFoldMaxCover : 1, NR = D == 3 ? 1 : (D == 2 ? 2 : 8);
-        const int lead = D == 3 ? 1 : 0;  // index of the u dimension among the leading ones
-        const int vu = D >= 2 ? thi[lead] - tlo[lead] : 0, vk = t2hi - t2lo;
-        // parts of the tile index and patch offset of candidate (u, k) that do not depend on
-        // the leading tile t0 of 3-D:
-        //   tile = t0 nt1 ntl + tl_b + u ntl + k,  loc = (gu0 - t0 T) W^2 + loc_b - u T W - k T
-        const int tl_b = (D >= 2 ? tlo[lead] * ntl : 0) + t2lo;
-        const int loc_b = (D >= 2 ? (gu[lead] - tlo[lead] * T) * W : 0) + (g - t2lo * T);
-        const int t0a = D == 3 ? tlo[0] : 0, t0b = D == 3 ? thi[0] : 0;
-        for (int t0 = t0a; t0 <= t0b; ++t0) {
-            const int tl0 = (D == 3 ? t0 * J.ntile[1] * ntl : 0) + tl_b;
-            const int loc0 = (D == 3 ? (gu[0] - t0 * T) * W * W : 0) + loc_b;
-            int c0[NU][kFoldMaxCover], nc[NU][kFoldMaxCover];
-            int most = 0;  // chunks of the fullest candidate tile
-#pragma unroll
-            for (int u = 0; u < NU; ++u)
-#pragma unroll
-                for (int k = 0; k < kFoldMaxCover; ++k) {
-                    const bool ok = u <= vu && k <= vk;
-                    const int tl = tl0 + u * ntl + k;
-                    c0[u][k] = ok ? tch[tl] : 0;
-                    nc[u][k] = ok ? tch[tl + 1] - c0[u][k] : 0;
-                    most = max(most, nc[u][k]);
-                }
-            for (int r0 = 0; r0 < most; r0 += NR) {
-                float val[NR][NU][kFoldMaxCover];
-#pragma unroll
-                for (int r = 0; r < NR; ++r)
-#pragma unroll
-                    for (int u = 0; u < NU; ++u)
-#pragma unroll
-                        for (int k = 0; k < kFoldMaxCover; ++k)
-                            val[r][u][k] = nc[u][k] > r0 + r
-                                               ? pat[(int64_t)(c0[u][k] + r0 + r) * pe + (loc0 - u * T * W - k * T)]
-                                               : 0.0f;
-#pragma unroll
-                for (int r = 0; r < NR; ++r)
-#pragma unroll
-                    for (int u = 0; u < NU; ++u)
-#pragma unroll
-                        for (int k = 0; k < kFoldMaxCover; ++k)
-                            acc += val[r][u][k];  // +0 for an absent chunk leaves the sum unchanged
-            }
-        }
-    } else {
-        for (int t0 = tlo[0]; t0 <= thi[0]; ++t0)
-            for (int t1 = tlo[1]; t1 <= thi[1]; ++t1) {
-                int lead_tile = 0, lead_loc = 0;
-                if constexpr (D == 3) {
-                    lead_tile = t0 * J.ntile[1] + t1;
-                    lead_loc = (gu[0] - t0 * T) * W + (gu[1] - t1 * T);
-                } else if constexpr (D == 2) {
-                    lead_tile = t0;
-                    lead_loc = gu[0] - t0 * T;
-                }
-                for (int t2 = t2lo; t2 <= t2hi; ++t2) {
-                    const int tl = lead_tile * ntl + t2;
-                    const int lc = lead_loc * W + (g - t2 * T);
-                    const int ca = tch[tl], cb = tch[tl + 1];
-                    for (int ch = ca; ch < cb; ++ch) acc += pat[(int64_t)ch * pe + lc];
-                }
-            }
-    }
-    return acc;
-}
-
 // One item of the fold.
 template <int D, class Tab>
 __device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch)

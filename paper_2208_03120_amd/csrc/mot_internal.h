@@ -110,6 +110,8 @@ struct ProdJob {
     const int32_t *src_chunk_tile, *tgt_chunk_tile;    // box-relative tile of each chunk
     const int32_t *src_tile_chunks;       // [ntiles+1] chunk range of each box tile
     int32_t src_nchunks, tgt_nchunks;
+    int32_t src_tile_most;  // most chunks of one source tile
+    int32_t plane;          // the transform runs in one workgroup (launch_plane)
     // host copies of the chunk bounds, used when launch items are built (never read on
     // the device)
     const int32_t *h_src_chunk_start, *h_tgt_chunk_start;
@@ -253,6 +255,38 @@ hipError_t launch_interp(int d, const ProdJob *jobs, const int2 *items, int n_it
 // lines (23 complex) is two rounds and its 33 half-spectrum lines (M = 32) three.
 constexpr int kSlabThreads = 768;
 constexpr int kSlabLds = 48 * 1024;  // bytes of LDS for a slab's half spectrum L1 x (M+1)
+// Whole transform of 1-D and 2-D jobs in one launch (items int2 (job, fold); fold != 0: the
+// patches are folded too, else the grid is): 1-D always, 2-D when the box and its spectra fit
+// in kPlaneLds bytes of LDS.
+constexpr int kPlaneLds = 128 * 1024;
+struct PlaneGeom {  // padded extents and LDS pitches of a 2-D job, in floats (k_plane.hip)
+    int L0p, p1, H4, Hp, px, pz, py, ry, xz;
+    static __host__ __device__ constexpr int up(int v, int q) { return (v + q - 1) / q * q; }
+    static __host__ __device__ constexpr int odd(int v, int q)  // least odd multiple of q >= v
+    {
+        return up(v, q) / q % 2 ? up(v, q) : up(v, q) + q;
+    }
+    __host__ __device__ constexpr PlaneGeom(int L0, int L1, int M)
+        : L0p(up(L0, 16)), p1(odd(L1, 4)), H4(up(M + 1, 4)), Hp(up(M + 1, 16)), px(odd(2 * Hp, 16)),
+          pz(odd(2 * H4, 4)), py(odd(Hp, 16)), ry(L0p * p1 > 4 * H4 * py ? L0p * p1 : 4 * H4 * py),
+          xz(L0p * (px > pz ? px : pz))
+    {
+    }
+};
+constexpr int64_t plane_lds(int d, int n, const int32_t *L, int M)
+{
+    if (d == 1) return (int64_t)8 * n + 4 * ((L[0] + 1) / 2 * 2) + 8 * (M + 1);
+    const PlaneGeom P(L[0], L[1], M);
+    return (int64_t)8 * n + 4 * ((int64_t)P.ry + P.xz);
+}
+// MFMAs of a 2-D job on that path.
+constexpr int64_t plane_mfmas(const int32_t *L, int M)
+{
+    const PlaneGeom P(L[0], L[1], M);
+    const int64_t mt = P.L0p / 16, kt = P.Hp / 16, nt = (L[1] + 15) / 16;
+    return mt * kt * ((L[1] + 3) / 4) * 2 + kt * kt * ((L[0] + 3) / 4) * 4 + mt * kt * P.H4 + mt * nt * P.H4 / 2;
+}
+hipError_t launch_plane(const ProdJob *jobs, const int2 *items, int n_items, int lds_bytes, hipStream_t s);
 // n = 0: the items' jobs have grids n <= 128 of several sizes (twiddle: the 128-point
 // table); results equal those of the launch per size.
 hipError_t launch_fft_pass(int kind, int n, const ProdJob *jobs, const int4 *items, int n_items,

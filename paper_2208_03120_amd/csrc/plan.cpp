@@ -195,6 +195,10 @@ int run_steps(const std::vector<Step> &steps, hipStream_t s0, const Lanes *lanes
             MOT_HIP(launch_fold(st.d, (const ProdJob *)st.jobs, (const int2 *)st.items, st.n_items, s));
             break;
         case ST_FFT:
+            if (st.fft_kind == 8) {
+                MOT_HIP(launch_plane((const ProdJob *)st.jobs, (const int2 *)st.items, st.n_items, st.lds, s));
+                break;
+            }
             MOT_HIP(launch_fft_pass(st.fft_kind, st.n, (const ProdJob *)st.jobs, (const int4 *)st.items,
                                     st.n_items, st.twiddle, s));
             break;
@@ -227,6 +231,15 @@ int run_steps(const std::vector<Step> &steps, hipStream_t s0, const Lanes *lanes
 // ..., r + (group - 1) kXcds receive group consecutive items.  Results do not depend on the
 // order of items.
 constexpr int kXcds = 8;
+
+// One-launch transforms of 1-D and 2-D jobs.  A workgroup has one CU's matrix cores for its
+// job: from kPlaneMfmas MFMAs on the fold and three passes, which spread a job over the chip,
+// are faster for a tree's few jobs (70 x 70 box, M = 32, 2200 MFMAs: 20 us against 15 us for
+// the three passes; 30 x 30, M = 16, 300: 7 us against 14 us); a circle's rows fill the chip
+// whatever their size (4000 rows of 43 x 43: fold and passes 200 us, 105 us in one launch).
+constexpr int64_t kPlaneMfmas = 1300;
+constexpr int kPlaneRows = 64;
+constexpr int kPlaneRounds = 4;
 
 template <class T>
 static void xcd_group(std::vector<T> &v, int group)
@@ -313,6 +326,8 @@ struct StepBuilder {
         std::map<const float *, std::vector<int>> spread3_src;
         std::map<int, std::vector<int32_t>> spread_pts, interp_pts;  // points of each item
         std::map<int, std::vector<int4>> fft[8];  // items per grid size n, per pass kind
+        std::vector<int2> planes;                 // one-launch transforms
+        int plane_bytes = 0;                      // LDS of the largest
         std::map<int, int> max_patch;
         for (int j : ids) {
             const ProdJob &J = host_jobs[j];
@@ -371,9 +386,16 @@ struct StepBuilder {
                 for (int c = 0; c < J.src_nchunks; ++c)
                     spread_pts[J.d].push_back(J.h_src_chunk_start[c + 1] - J.h_src_chunk_start[c]);
             }
+            const bool plane = J.plane != 0;
             const int lines = J.d == 3 ? J.L[0] * J.L[1] : (J.d == 2 ? J.L[0] : 1);
             const int cells = lines * J.L[J.d - 1];
-            for (int f = 0; f < cells; f += kFoldCellsPerItem) fold[J.d].push_back(make_int2(j, f));
+            // a workgroup that folds its own job waits once per cell of a thread and round of
+            // chunks; beyond kPlaneRounds such waits the fold's own launch is faster, unless
+            // the jobs fill the chip
+            const int waits = (cells + 1023) / 1024 * (J.d == 1 ? (J.src_tile_most + 3) / 4 : J.src_tile_most);
+            const bool plane_fold = plane && (waits <= kPlaneRounds || ids.size() >= 512);
+            if (!plane_fold)
+                for (int f = 0; f < cells; f += kFoldCellsPerItem) fold[J.d].push_back(make_int2(j, f));
             for (int c = 0; c < J.tgt_nchunks; ++c) {
                 interp[J.d].push_back(make_int2(j, c));
                 interp_pts[J.d].push_back(J.h_tgt_chunk_start[c + 1] - J.h_tgt_chunk_start[c]);
@@ -386,7 +408,10 @@ struct StepBuilder {
             const int kinds3[5] = {0, 1, 2, 3, 4}, kinds2[3] = {0, 2, 4}, kinds1[2] = {0, 4};
             const int *kinds = J.d == 3 ? kinds3 : (J.d == 2 ? kinds2 : kinds1);
             const int nk = J.d == 3 ? 5 : (J.d == 2 ? 3 : 2);
-            if (slab) {
+            if (plane) {
+                planes.push_back(make_int2(j, plane_fold ? 1 : 0));
+                plane_bytes = std::max(plane_bytes, (int)plane_lds(J.d, J.n, J.L, J.M));
+            } else if (slab) {
                 for (int g0 = 0; g0 < J.L[0]; ++g0) {
                     fft[6][J.n].push_back(make_int4(j, g0, 0, 0));
                     fft[7][J.n].push_back(make_int4(j, g0, 0, 0));
@@ -514,6 +539,15 @@ struct StepBuilder {
         }
         // per job the chain order holds: 0 < 1 < 2 < 3 < 4 and 6 < 5 < 7.  A pass kernel
         // serves every d; grids n <= 128 of several sizes share one launch (n = 0).
+        if (!planes.empty()) {
+            Step st{ST_FFT};
+            st.fft_kind = 8;
+            st.lds = plane_bytes;
+            st.jobs = jobs_dev;
+            st.items = upload(planes);
+            st.n_items = (int)planes.size();
+            out->push_back(st);
+        }
         for (int kind : {0, 6, 1, 2, 5, 3, 4, 7}) {
             std::vector<std::pair<int, std::vector<int4>>> launches;
             std::vector<int4> mixed;
@@ -908,6 +942,7 @@ static int bin_marginal(mot_plan_s *P, int k, const double *pts_orig_dev, void *
         }
         covered += b - a;
         tch2.push_back((int32_t)starts.size());
+        G.tile_most = std::max(G.tile_most, tch2[bt + 1] - tch2[bt]);
     }
     if (covered != G.n) return MOT_EDOMAIN;  // a point outside the box tiles
     std::vector<int32_t> bounds = starts;
@@ -989,6 +1024,7 @@ int mot::make_prod_job(mot_plan_s *P, int t, int s, const double *v, int32_t *sl
     Q.src_tile_chunks = S.tile_chunks;
     Q.src_nchunks = S.nchunks;
     Q.tgt_nchunks = Tm.nchunks;
+    Q.src_tile_most = S.tile_most;
     Q.h_src_chunk_start = S.h_chunk_start.data();
     Q.h_tgt_chunk_start = Tm.h_chunk_start.data();
     Q.n = N.n;
@@ -1011,6 +1047,9 @@ int mot::make_prod_job(mot_plan_s *P, int t, int s, const double *v, int32_t *sl
         pe *= N.W;
         cells *= N.L[c];
     }
+    Q.plane = P->d < 3 && plane_lds(P->d, N.n, N.L, N.M) <= kPlaneLds &&
+              (P->d == 1 || plane_mfmas(N.L, N.M) <= kPlaneMfmas ||
+               (P->topology == MOT_CIRCLE && P->n[0] >= kPlaneRows));
     const int H = N.M + 1, B = 2 * N.M + 1;
     int64_t spec = H;
     if (P->d == 2) spec = (int64_t)H * N.L[0];
