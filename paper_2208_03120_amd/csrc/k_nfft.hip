@@ -833,6 +833,269 @@ __global__ __launch_bounds__(64 * kInterpWaves, 6) void interp3_kernel(const Pro
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// 1-D and 2-D jobs in groups that share their points (the rows of a circle's matrix, the
+// products of a node of many children): spreading and interpolation as matrix products with
+// the window matrix, whose entries are formed once for 16 jobs.
+//   spreading      G[cell][job] = sum_p W[cell][p] v_p[job]      (K = points)
+//   interpolation  beta[p][job] = sum_cell W[cell][p] G[cell][job]  (K = cells)
+// with W[(a, c')][p] = w_0,p[a] w_1,p[c'] in 2-D and w_0,p[c'] in 1-D.  As many MFMAs as job by
+// job (one per job and four points, a sixteenth in 1-D), but a chunk's rows are staged once for
+// 16 jobs (64 in 1-D) and there is one operand product for 16 jobs' MFMA, where the kernels
+// above read 128 bytes of rows per point and job from L2: 4000 jobs of 4000 points in 2-D, 184 us
+// to spread and 194 us to interpolate, take 93 and 120 us (the values read and the patches
+// written are 78 us of the spreading at the card's copy rate, the MFMAs 52 us of each).
+//
+// gids: job indices, kGroupJobs1 (1-D) or kGroupJobs2 per group, -1 for absent ones.  An item
+// (first group, groups, chunk) takes several groups one after another: the next group's
+// values (grid cells) are loaded while the current one is multiplied, which a block of one
+// group spends as long waiting for as multiplying (interpolation 195 us with one group per
+// block).  The rows of a chunk of one stage are staged once for all of them.
+template <int D>
+struct GroupShape {
+    static constexpr int J = D == 1 ? kGroupJobs1 : kGroupJobs2;  // jobs of a group
+    static constexpr int PV = kStage * J / 256;                    // values per thread and stage
+    static constexpr int kPitch = J + 4;                           // a row's values (LDS banks)
+};
+
+template <int D>
+__global__ __launch_bounds__(256, 4) void spread_group_kernel(const ProdJob *__restrict__ jobs,
+                                                              const int32_t *__restrict__ gids,
+                                                              const int4 *__restrict__ items, int n_items)
+{
+    using S = GroupShape<D>;
+    using St = Stage<D, false>;
+    constexpr int NA = D == 2 ? 4 : 1;  // accumulators: 2-D patch rows a = 4 wave + u
+    __shared__ __align__(16) unsigned char rows[2][St::kBytes];
+    __shared__ float vals[2][kStage * S::kPitch];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+        const int4 itm = items[it];
+        const int32_t *gid = gids + (int64_t)itm.x * S::J;
+        const int ng = itm.y, c = itm.z;
+        const ProdJob &J0 = jobs[gid[0]];  // the points, shared by the groups
+        const int64_t p0 = gp(J0.src_chunk_start)[c], p1 = gp(J0.src_chunk_start)[c + 1];
+        const int nst = (int)((p1 - p0 + kStage - 1) / kStage);
+        // thread tid stages PV consecutive points of job tid % J of a group; the values of the
+        // group being loaded, and the pointer and exponent of the one after it
+        const int vp = tid / S::J * S::PV;
+        const double *vsrc = nullptr, *vnext = nullptr;
+        int e = 0, enext = 0;
+        auto job_of = [&](int g) {  // the group's job of this thread, into vnext and enext
+            const int j = g < ng ? gid[g * S::J + tid % S::J] : -1;
+            vnext = j >= 0 ? jobs[j].v : nullptr;
+            enext = j >= 0 ? source_exponent(jobs[j]) : 0;
+        };
+        double v[S::PV];
+        auto load_v = [&](int64_t pb) {
+#pragma unroll
+            for (int q = 0; q < S::PV; ++q) {
+                const int64_t p = pb + vp + q;
+                v[q] = vsrc && p < p1 ? gp(vsrc)[p] : 0.0;
+            }
+        };
+        auto store_v = [&](float *buf, int ex) {
+#pragma unroll
+            for (int q = 0; q < S::PV; ++q) buf[(vp + q) * S::kPitch + tid % S::J] = (float)ldexp(v[q], -ex);
+        };
+        f32x4 acc[NA];
+#pragma unroll
+        for (int u = 0; u < NA; ++u) acc[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        St stg;
+        job_of(0);
+        vsrc = vnext;
+        e = enext;
+        stg.load(J0.src_win, nullptr, p0, p1);
+        load_v(p0);
+        job_of(1);
+        __syncthreads();  // the previous item's reads of LDS are done
+        stg.store(rows[0], 0);
+        store_v(vals[0], e);
+        __syncthreads();
+        int buf = 0;
+        for (int g = 0; g < ng; ++g)
+            for (int k = 0; k < nst; ++k, buf ^= 1) {
+                // next: the following stage of this group, or the next group's first
+                const bool last = k + 1 == nst, more = !last || g + 1 < ng;
+                if (more) {
+                    if (last) {
+                        vsrc = vnext;
+                        e = enext;
+                        job_of(g + 2);
+                    }
+                    const int64_t pn = last ? p0 : p0 + (int64_t)(k + 1) * kStage;
+                    load_v(pn);
+                    if (nst > 1) stg.load(J0.src_win, nullptr, pn, p1);
+                }
+                const float *rl = reinterpret_cast<const float *>(rows[nst > 1 ? buf : 0]);
+                const float *vl = vals[buf];
+                // points past the chunk's end have zero rows and values
+                const int cnt = (int)min((int64_t)kStage, p1 - p0 - (int64_t)k * kStage);
+                for (int j = 0; j < cnt; j += 16) {
+                    float x[4][NA], b[4];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int pi = j + 4 * q + lk;
+                        const float *row = rl + pi * (D * kPatch);
+                        if constexpr (D == 2) {
+                            const float w1 = row[kPatch + li];
+                            const f32x4 w0 = reinterpret_cast<const f32x4 *>(row)[wave];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) x[q][u] = w0[u] * w1;
+                            b[q] = vl[pi * S::kPitch + li];
+                        } else {
+                            x[q][0] = row[li];
+                            b[q] = vl[pi * S::kPitch + 16 * wave + li];
+                        }
+                    }
+#pragma unroll
+                    for (int q = 0; q < 4; ++q)
+#pragma unroll
+                        for (int u = 0; u < NA; ++u)
+                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q][u], b[q], acc[u], 0, 0, 0);
+                }
+                if (more) {
+                    store_v(vals[buf ^ 1], e);
+                    if (nst > 1) stg.store(rows[buf ^ 1], 0);
+                }
+                if (last) {
+                    // acc[u][r] = G[c' = 4 lk + r] (2-D: patch row a = 4 wave + u) of job li (1-D: 16 wave
+                    // + li)
+                    const int jo = gid[g * S::J + (D == 2 ? li : 16 * wave + li)];
+                    if (jo >= 0) {
+                        MOT_GLOBAL f32x4 *out = reinterpret_cast<MOT_GLOBAL f32x4 *>(gp(jobs[jo].patches)) +
+                                                (int64_t)c * (D == 2 ? 64 : 4);
+#pragma unroll
+                        for (int u = 0; u < NA; ++u) out[(D == 2 ? (4 * wave + u) * 4 : 0) + lk] = acc[u];
+                    }
+#pragma unroll
+                    for (int u = 0; u < NA; ++u) acc[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                }
+                __syncthreads();
+            }
+    }
+}
+
+template <int D>
+__global__ __launch_bounds__(256, 4) void interp_group_kernel(const ProdJob *__restrict__ jobs,
+                                                              const int32_t *__restrict__ gids,
+                                                              const int4 *__restrict__ items, int n_items)
+{
+    using S = GroupShape<D>;
+    using St = Stage<D, false>;
+    constexpr int kGPitch = 17;             // staged grid cells x 16 jobs (2-D)
+    constexpr int NG = D == 2 ? 16 : 4;     // grid values loaded per thread and group
+    __shared__ __align__(16) unsigned char rows[St::kBytes];
+    __shared__ float cells[D == 2 ? 256 * kGPitch : 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int li = lane & 15, lk = lane >> 4;
+    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+        const int4 itm = items[it];
+        const int32_t *gid = gids + (int64_t)itm.x * S::J;
+        const int ng = itm.y, c = itm.z;
+        const ProdJob &J0 = jobs[gid[0]];
+        const int64_t p0 = gp(J0.tgt_chunk_start)[c], p1 = gp(J0.tgt_chunk_start)[c + 1];
+        const int tile = gp(J0.tgt_chunk_tile)[c], T = J0.T;
+        const int nst = (int)((p1 - p0 + kStage - 1) / kStage);
+        // 2-D: thread tid loads grid row a = tid / 16 of the tile for job tid % 16; 1-D: the B
+        // operand of the wave's 16 jobs
+        int64_t base;
+        if constexpr (D == 2) {
+            const int t0 = tile / J0.ntile[1], t1 = tile - t0 * J0.ntile[1];
+            base = (int64_t)(t0 * T + (tid >> 4)) * J0.L[1] + t1 * T;
+        } else {
+            base = tile * T + lk;
+        }
+        const int lj = D == 2 ? tid & 15 : 16 * wave + li;  // job the thread loads the grid of
+        const int oj = D == 2 ? li : 16 * wave + li;          // job the lane's results belong to
+        const float *gnext = nullptr;
+        double *onext = nullptr;
+        int enext = 0;
+        auto job_of = [&](int g) {
+            const int jl = g < ng ? gid[g * S::J + lj] : -1, jo = g < ng ? gid[g * S::J + oj] : -1;
+            gnext = jl >= 0 ? jobs[jl].grid : nullptr;
+            onext = jo >= 0 ? jobs[jo].out : nullptr;
+            enext = jo >= 0 ? source_exponent(jobs[jo]) : 0;
+        };
+        float gv[NG];
+        auto load_g = [&]() {
+#pragma unroll
+            for (int q = 0; q < NG; ++q) gv[q] = gnext ? gp(gnext)[base + (D == 2 ? q : 4 * q)] : 0.0f;
+        };
+        St stg;
+        job_of(0);
+        stg.load(J0.tgt_win, nullptr, p0, p1);
+        load_g();
+        __syncthreads();  // the previous item's reads of LDS are done
+        stg.store(rows, 0);
+        for (int g = 0; g < ng; ++g) {
+            double *out = onext;
+            const int e = enext;
+            float gb[4];
+            if constexpr (D == 2) {
+                if (g > 0) __syncthreads();  // the previous group's reads of the cells are done
+#pragma unroll
+                for (int q = 0; q < 16; ++q) cells[((tid >> 4) * 16 + q) * kGPitch + (tid & 15)] = gv[q];
+            } else {
+#pragma unroll
+                for (int s = 0; s < 4; ++s) gb[s] = gv[s];
+            }
+            __syncthreads();
+            job_of(g + 1);
+            load_g();
+            for (int k = 0; k < nst; ++k) {
+                const int64_t pb = p0 + (int64_t)k * kStage;
+                if (nst > 1 && g + k > 0) {
+                    stg.load(J0.tgt_win, nullptr, pb, p1);
+                    __syncthreads();
+                    stg.store(rows, 0);
+                    __syncthreads();
+                }
+                const float *rl = reinterpret_cast<const float *>(rows);
+                // 16-point groups: in 2-D group `wave` of the stage for the 16 jobs, in 1-D every one for
+                // the wave's 16 jobs
+#pragma unroll 1
+                for (int q = D == 2 ? wave : 0; q < (D == 2 ? wave + 1 : 4); ++q) {
+                    if (pb + 16 * q >= p1) break;
+                    const float *row = rl + (16 * q + li) * (D * kPatch);
+                    f32x4 acc[4];
+#pragma unroll
+                    for (int s = 0; s < 4; ++s) acc[s] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    if constexpr (D == 2) {
+                        float w1[4];
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) w1[s] = row[kPatch + 4 * s + lk];
+                        const float *gc = cells + lk * kGPitch + li;
+#pragma unroll
+                        for (int a4 = 0; a4 < 4; ++a4) {
+                            const f32x4 w0 = reinterpret_cast<const f32x4 *>(row)[a4];
+#pragma unroll
+                            for (int u = 0; u < 4; ++u)
+#pragma unroll
+                                for (int s = 0; s < 4; ++s)
+                                    acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                                        w0[u] * w1[s], gc[((4 * a4 + u) * 16 + 4 * s) * kGPitch], acc[s], 0, 0, 0);
+                        }
+                    } else {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s)
+                            acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(row[4 * s + lk], gb[s], acc[s], 0, 0, 0);
+                    }
+                    const f32x4 z = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+                    // z[r]: point 16 q + 4 lk + r of the stage, the lane's job
+                    if (out)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const int64_t p = pb + 16 * q + 4 * lk + r;
+                            if (p < p1) gp(out)[p] = ldexp((double)z[r], e);
+                        }
+                }
+            }
+        }
+    }
+}
+
 static int nfft_grid(int n_items)
 {
     return n_items < 65535 ? n_items : 65535;
@@ -864,6 +1127,30 @@ hipError_t launch_spread(int d, const ProdJob *jobs, const int2 *items, int n_it
         hipLaunchKernelGGL(spread_kernel<2>, grid, block, 0, s, jobs, items, n_items);
     else
         hipLaunchKernelGGL(spread_kernel<1>, grid, block, 0, s, jobs, items, n_items);
+    return hipGetLastError();
+}
+
+hipError_t launch_spread_group(int d, const ProdJob *jobs, const int32_t *gids, const int4 *items, int n_items,
+                               hipStream_t s)
+{
+    if (n_items == 0) return hipSuccess;
+    const dim3 grid(nfft_grid(n_items)), block(256);
+    if (d == 2)
+        hipLaunchKernelGGL(spread_group_kernel<2>, grid, block, 0, s, jobs, gids, items, n_items);
+    else
+        hipLaunchKernelGGL(spread_group_kernel<1>, grid, block, 0, s, jobs, gids, items, n_items);
+    return hipGetLastError();
+}
+
+hipError_t launch_interp_group(int d, const ProdJob *jobs, const int32_t *gids, const int4 *items, int n_items,
+                               hipStream_t s)
+{
+    if (n_items == 0) return hipSuccess;
+    const dim3 grid(nfft_grid(n_items)), block(256);
+    if (d == 2)
+        hipLaunchKernelGGL(interp_group_kernel<2>, grid, block, 0, s, jobs, gids, items, n_items);
+    else
+        hipLaunchKernelGGL(interp_group_kernel<1>, grid, block, 0, s, jobs, gids, items, n_items);
     return hipGetLastError();
 }
 

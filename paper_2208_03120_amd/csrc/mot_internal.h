@@ -244,6 +244,15 @@ hipError_t launch_spread(int d, const ProdJob *jobs, const int2 *items, int n_it
 // 3-D spreading; items int4 (job_0, .., job_{group-1}, chunk): group jobs (1..3) that spread
 // from the same points.
 hipError_t launch_spread3(int group, const ProdJob *jobs, const int4 *items, int n_items, hipStream_t s);
+// 1-D and 2-D jobs that share their source (spreading) or target (interpolation) points, in
+// groups of kGroupJobs1 / kGroupJobs2: gids the groups' job indices (-1: absent, never the
+// first), items int4 (first group, groups, chunk, 0).
+constexpr int kGroupJobs1 = 64, kGroupJobs2 = 16;
+constexpr int kGroupMin = 16;  // jobs sharing their points from which they are grouped
+hipError_t launch_spread_group(int d, const ProdJob *jobs, const int32_t *gids, const int4 *items, int n_items,
+                               hipStream_t s);
+hipError_t launch_interp_group(int d, const ProdJob *jobs, const int32_t *gids, const int4 *items, int n_items,
+                               hipStream_t s);
 hipError_t launch_fold(int d, const ProdJob *jobs, const int2 *items, int n_items, hipStream_t s);
 hipError_t launch_interp(int d, const ProdJob *jobs, const int2 *items, int n_items,
                          int max_patch_elems, hipStream_t s);

@@ -185,7 +185,10 @@ int run_steps(const std::vector<Step> &steps, hipStream_t s0, const Lanes *lanes
                                   (const int2 *)st.items2, st.n_items2, st.precision, st.diff, s));
             break;
         case ST_SPREAD:
-            if (st.group > 0)
+            if (st.items2)
+                MOT_HIP(launch_spread_group(st.d, (const ProdJob *)st.jobs, (const int32_t *)st.items2,
+                                            (const int4 *)st.items, st.n_items, s));
+            else if (st.group > 0)
                 MOT_HIP(launch_spread3(st.group, (const ProdJob *)st.jobs, (const int4 *)st.items, st.n_items, s));
             else
                 MOT_HIP(launch_spread(st.d, (const ProdJob *)st.jobs, (const int2 *)st.items, st.n_items,
@@ -203,6 +206,11 @@ int run_steps(const std::vector<Step> &steps, hipStream_t s0, const Lanes *lanes
                                     st.n_items, st.twiddle, s));
             break;
         case ST_INTERP:
+            if (st.items2) {
+                MOT_HIP(launch_interp_group(st.d, (const ProdJob *)st.jobs, (const int32_t *)st.items2,
+                                            (const int4 *)st.items, st.n_items, s));
+                break;
+            }
             MOT_HIP(launch_interp(st.d, (const ProdJob *)st.jobs, (const int2 *)st.items, st.n_items,
                                   st.max_patch, s));
             break;
@@ -240,6 +248,10 @@ constexpr int kXcds = 8;
 constexpr int64_t kPlaneMfmas = 1300;
 constexpr int kPlaneRows = 64;
 constexpr int kPlaneRounds = 4;
+
+// Grouped spreading and interpolation: groups of an item at most, and items below which an
+// item takes fewer (eight 256-thread blocks per CU).
+constexpr int kGroupsPerItem = 8, kGroupItems = 2048;
 
 template <class T>
 static void xcd_group(std::vector<T> &v, int group)
@@ -324,6 +336,15 @@ struct StepBuilder {
         std::map<int, std::vector<int2>> spread, fold, interp;   // d
         // 3-D spreading: jobs by the points they spread from (a binned marginal's rows)
         std::map<const float *, std::vector<int>> spread3_src;
+        // 1-D and 2-D: jobs by their source and by their target points, in order of appearance
+        std::vector<std::vector<int>> src_sets, tgt_sets;
+        std::map<const float *, size_t> src_set, tgt_set;
+        auto into_set = [](std::vector<std::vector<int>> &sets, std::map<const float *, size_t> &at, const float *pts,
+                           int j) {
+            auto r = at.insert({pts, sets.size()});
+            if (r.second) sets.emplace_back();
+            sets[r.first->second].push_back(j);
+        };
         std::map<int, std::vector<int32_t>> spread_pts, interp_pts;  // points of each item
         std::map<int, std::vector<int4>> fft[8];  // items per grid size n, per pass kind
         std::vector<int2> planes;                 // one-launch transforms
@@ -379,13 +400,10 @@ struct StepBuilder {
                     }
                 continue;
             }
-            if (J.d == 3) {
+            if (J.d == 3)
                 spread3_src[J.src_win].push_back(j);
-            } else {
-                for (int c = 0; c < J.src_nchunks; ++c) spread[J.d].push_back(make_int2(j, c));
-                for (int c = 0; c < J.src_nchunks; ++c)
-                    spread_pts[J.d].push_back(J.h_src_chunk_start[c + 1] - J.h_src_chunk_start[c]);
-            }
+            else
+                into_set(src_sets, src_set, J.src_win, j);
             const bool plane = J.plane != 0;
             const int lines = J.d == 3 ? J.L[0] * J.L[1] : (J.d == 2 ? J.L[0] : 1);
             const int cells = lines * J.L[J.d - 1];
@@ -396,9 +414,13 @@ struct StepBuilder {
             const bool plane_fold = plane && (waits <= kPlaneRounds || ids.size() >= 512);
             if (!plane_fold)
                 for (int f = 0; f < cells; f += kFoldCellsPerItem) fold[J.d].push_back(make_int2(j, f));
-            for (int c = 0; c < J.tgt_nchunks; ++c) {
-                interp[J.d].push_back(make_int2(j, c));
-                interp_pts[J.d].push_back(J.h_tgt_chunk_start[c + 1] - J.h_tgt_chunk_start[c]);
+            if (J.d < 3) {
+                into_set(tgt_sets, tgt_set, J.tgt_win, j);
+            } else {
+                for (int c = 0; c < J.tgt_nchunks; ++c) {
+                    interp[J.d].push_back(make_int2(j, c));
+                    interp_pts[J.d].push_back(J.h_tgt_chunk_start[c + 1] - J.h_tgt_chunk_start[c]);
+                }
             }
             int pe = 1;
             for (int c = 0; c < J.d; ++c) pe *= J.W;
@@ -476,6 +498,58 @@ struct StepBuilder {
             for (size_t i = 0; i < ord.size(); ++i) out[i] = v[ord[i]];
             v.swap(out);
         };
+        // 1-D and 2-D: sets of at least kGroupMin jobs go in groups that share a chunk's window
+        // rows and operand products; a partly filled group costs as much as a full one
+        std::vector<int32_t> sgids[3], igids[3];
+        std::vector<std::pair<int64_t, int4>> sgroup[3], igroup[3];  // with the item's work
+        auto place = [&](const std::vector<std::vector<int>> &sets, bool source, std::map<int, std::vector<int2>> &solo,
+                         std::map<int, std::vector<int32_t>> &solo_pts, std::vector<int32_t> *gids,
+                         std::vector<std::pair<int64_t, int4>> *group) {
+            for (const std::vector<int> &js : sets) {
+                const ProdJob &J = host_jobs[js[0]];
+                const int nch = source ? J.src_nchunks : J.tgt_nchunks;
+                const int32_t *start = source ? J.h_src_chunk_start : J.h_tgt_chunk_start;
+                if ((int)js.size() < kGroupMin) {
+                    for (int j : js)
+                        for (int c = 0; c < nch; ++c) {
+                            solo[J.d].push_back(make_int2(j, c));
+                            solo_pts[J.d].push_back(start[c + 1] - start[c]);
+                        }
+                    continue;
+                }
+                const int G = J.d == 1 ? kGroupJobs1 : kGroupJobs2;
+                const int ng = (int)((js.size() + G - 1) / G), g0 = (int)(gids[J.d].size() / G);
+                gids[J.d].insert(gids[J.d].end(), js.begin(), js.end());
+                gids[J.d].resize((size_t)(g0 + ng) * G, -1);
+                const int per = (int)std::max<int64_t>(1, std::min<int64_t>(kGroupsPerItem, (int64_t)ng * nch / kGroupItems));
+                for (int g = 0; g < ng; g += per)
+                    for (int c = 0; c < nch; ++c) {
+                        const int n = std::min(per, ng - g);
+                        group[J.d].push_back({(int64_t)n * (start[c + 1] - start[c]), make_int4(g0 + g, n, c, 0)});
+                    }
+            }
+        };
+        place(src_sets, true, spread, spread_pts, sgids, sgroup);
+        place(tgt_sets, false, interp, interp_pts, igids, igroup);
+        auto group_step = [&](StepKind kind, int d, std::vector<std::pair<int64_t, int4>> &work,
+                              const std::vector<int32_t> &gids) {
+            std::stable_sort(work.begin(), work.end(), [](const std::pair<int64_t, int4> &x,
+                                                          const std::pair<int64_t, int4> &y) { return x.first > y.first; });
+            std::vector<int4> its(work.size());
+            for (size_t i = 0; i < its.size(); ++i) its[i] = work[i].second;
+            Step st{kind};
+            st.d = d;
+            st.jobs = jobs_dev;
+            st.items = upload(its);
+            st.n_items = (int)its.size();
+            st.items2 = upload(gids);
+            st.n_items2 = (int)gids.size();
+            out->push_back(st);
+        };
+        for (int d = 1; d <= 2; ++d) {
+            if (sgroup[d].empty()) continue;
+            group_step(ST_SPREAD, d, sgroup[d], sgids[d]);
+        }
         for (auto &kv : spread) by_size(kv.second, spread_pts[kv.first]);
         // 3-D: jobs spreading from the same points go three (or the remaining two) to an
         // item, which stages the chunk's rows once for all of them
@@ -573,6 +647,10 @@ struct StepBuilder {
                 st.n_items = (int)l.second.size();
                 out->push_back(st);
             }
+        }
+        for (int d = 1; d <= 2; ++d) {
+            if (igroup[d].empty()) continue;
+            group_step(ST_INTERP, d, igroup[d], igids[d]);
         }
         for (auto &kv : interp) {
             Step st{ST_INTERP};
