@@ -117,17 +117,18 @@ int resolve_params(int d, double eta, const Extent &ext, const mot_fastsum_param
                    int64_t n_max, NfftParams *out, double eta_hi = 0.0, int64_t products = 1);
 int build_box(int d, const Extent &ext, NfftParams *P);
 int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params *fs,
-                  double n_mean, TruncParams *out);
+                  double n_mean, int precision, TruncParams *out);
 int64_t trunc_cells(int d, const TruncParams &T);  // nc^d
 // host mirror of the kernel's neighbour rows of a run of B cells starting at cc
 int trunc_row_range(int d, const TruncParams &T, const int cc[3], int B, int ri, int64_t *row_base,
                     int *xa, int *xb);
-double trunc_cost(int d, const TruncParams &T, double lam_t, double lam_s, int B, int R, bool wide);
-// cells per run B, targets per lane R and exponent form (wide: FP64) of the cheapest launch
-// shape; lam_t / lam_s: targets / sources per grid cell; sch = sqrt(log2(e) / eta) h;
-// fp64: the FP64 kernel (form fixed)
+// Launch shape of a product; lam_t / lam_s: targets / sources per grid cell; sch =
+// sqrt(log2(e) / eta) h.  FP64: cells per run B and targets per lane R of the cheapest (wide:
+// unused).  Mixed: cells per run, and whether the run is too long for one exponent shift;
+// returns the cost.
 void trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, int max_r, double sch, bool fp64,
                       int *B, int *R, int *wide);
+double trunc_choose_mixed(int d, const TruncParams &T, double lam_t, double lam_s, double sch, int *B, int *wide);
 void kappa_B_shifted(double eta, double tau, double eps_B, int p, std::vector<double> &q);
 double kappa_R(double r, double eta, double tau, double eps_B, const std::vector<double> &q);
 void kappa_hat_even(int d, int M, double eta, double tau, double eps_B, int p,

@@ -8,28 +8,31 @@
 // cells of one row of the neighbourhood (fixed leading coordinates, a range along the last
 // one) are one contiguous range of sorted sources.
 //
-// One wavefront takes one item: up to 64 R targets, R per lane, from a run of B
+// One wavefront takes one item: up to 64 targets (FP64: 64 R, R per lane) from a run of B
 // consecutive cells of one row (consecutive in the sorted order; B > 1 fills the lanes
 // when cells hold few points).  The neighbourhood rows of a run are those of its first
 // cell, widened by B - 1 cells along the row.  The wave first lists the item's non-empty
 // rows in LDS with the prefix sum of their lengths, so its sources form one list; it then
 // stages that list 64 entries at a time through its own LDS slice (every stage full but
-// the last), and every lane sums a stage against its R targets while the next stage's
-// sources are loaded.  The waves of a block take different items and synchronise only
-// within themselves.
+// the last) and multiplies a stage while the next one's sources are loaded.  The waves of a
+// block take different items and synchronise only within themselves.
 //
-// Mixed precision, two forms of the exponent (c = log2(e) / eta):
-//  * short runs: coordinates relative to the centre of the item's run of cells (in FP64),
-//    scaled by sqrt(c) and rounded to FP32; a term is exp2(-|x'' - y''|^2).  The host takes
-//    this form only when sqrt(c) times the run's half-diagonal is at most 3, so the targets
-//    and every source that contributes more than a rounding error have |x''|, |y''| of a
-//    few units and their FP32 rounding moves the exponent by ~1e-7;
-//  * long runs (sparse cells): -c|x|^2 - c|y|^2 + 2c x.y formed in FP64 (coordinates
-//    relative to the cloud's centre), rounded to FP32 for v_exp_f32.  On gfx950 the FP64
-//    adds and FMAs issue at half the FP32 rate, so this form costs ~1.6x per pair.
-// (The expanded form in FP32 would cancel terms of size c r^2.)  Values are scaled by
-// 2^-e (e = exponent of max v); sums over 64 sources are FP32 and are added into FP64
-// accumulators.
+// Mixed precision: the exponents of 16 sources x 16 targets are one 16x16x4 FP64 MFMA.  With
+// c = log2(e) / eta and coordinates relative to the centre of the item's run of cells,
+//   -c |x - y|^2 = -c |x|^2 + r,  r = x.(2 c y) - c |y|^2
+// and r is the contraction of (x, 1) with (2 c y, -c |y|^2); it is rounded to FP32 once, for
+// v_exp_f32.  r lies between c |x|^2 - log2(1 / eps) and c |x|^2, so with the item's shift s (half the
+// largest c |x|^2 of its cells, the MFMA's addend) 2^(r - s) stays in FP32 range up to
+// c |x|^2 = 196 and the factor 2^(s - c |x|^2) is applied once per target; longer runs (WIDE) put
+// every target's -c |x|^2 into the addend.  Values are scaled by 2^-e (e = exponent of max v);
+// a lane sums 16 of a stage's 64 sources in FP32 and adds that to its FP64 accumulator.  A
+// pair costs the vector unit a conversion, v_exp_f32 and an FMA, and targets come in tiles of
+// 16 where one per lane left half of the lanes idle in sparse cells.  Star trees in 3-D, time
+// per launch against FP32 coordinate differences with a target per lane: nine jobs of 1e5
+// points, eta = 1e-3 5.1 -> 5.0 ms, eta = 3e-4 2.0 -> 1.8 ms; three jobs of 20000 points 0.45 -> 0.27
+// ms, of 5000 points at eta = 3e-4 0.12 -> 0.06 ms.  Bound by vector issue (about 160 cycles per
+// 16 x 16 pairs with the staging, 131 without); a bound of three or five blocks per CU measured
+// 2 % slower.
 // FP64: plain exp(-|x - y|^2 / eta) with FP64 sums in source order.
 #include <type_traits>
 
@@ -111,20 +114,22 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane)
     return v;
 }
 
-template <int D, int R, bool WIDE>
-__global__ __launch_bounds__(64 * kTruncWaves) void trunc_mixed_kernel(const ProdJob *__restrict__ jobs,
-                                                                       const int4 *__restrict__ items,
-                                                                       int n_items)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kSrcPitch = 64 + 8;  // staged component rows, in doubles (LDS banks)
+
+template <int D, bool WIDE>
+__global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const ProdJob *__restrict__ jobs,
+                                                                          const int4 *__restrict__ items,
+                                                                          int n_items)
 {
-    // FP32 form: float4 sqrt(c) (y - run centre), 2^-e v;  FP64 form: 2c (y - cloud
-    // centre), -c |y - cloud centre|^2 and the value in its own array
-    __shared__ double sbuf_all[kTruncWaves][64][4];
-    __shared__ float sv_all[kTruncWaves][64];
+    __shared__ double sw_all[kTruncWaves][4 * kSrcPitch];         // 2c y, -c |y|^2
+    __shared__ __align__(16) float sv_all[kTruncWaves][64];
     __shared__ int32_t ra_all[kTruncWaves][kMaxTruncRows];      // first sorted source of each row
     __shared__ int32_t rp_all[kTruncWaves][kMaxTruncRows + 1];  // sources before each row
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    float4 *sy = reinterpret_cast<float4 *>(sbuf_all[wave]);
-    double(*sw)[4] = sbuf_all[wave];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    double *sw = sw_all[wave];
     float *sv = sv_all[wave];
     int32_t *ra = ra_all[wave], *rp = rp_all[wave];
     for (int it = blockIdx.x * kTruncWaves + wave; it < n_items; it += gridDim.x * kTruncWaves) {
@@ -134,11 +139,14 @@ __global__ __launch_bounds__(64 * kTruncWaves) void trunc_mixed_kernel(const Pro
         int cc[3];
         trunc_cell<D>(J, itm.y, cc);
         const double c2 = 1.4426950408889634 / J.eta;  // log2(e) / eta
-        const double sc = sqrt(c2);
-        double ctr[3] = {0.0, 0.0, 0.0};  // centre of the run (FP32 form), of the cloud (FP64)
+        double ctr[3] = {0.0, 0.0, 0.0}, half2 = 0.0;    // centre and squared half-diagonal of the run
 #pragma unroll
-        for (int c = 0; c < D; ++c)
-            ctr[c] = WIDE ? J.ctr[c] : J.glo[c] + (cc[c] + (c == D - 1 ? 0.5 * B : 0.5)) * J.h;
+        for (int c = 0; c < D; ++c) {
+            const double half = (c == D - 1 ? 0.5 * B : 0.5) * J.h;
+            ctr[c] = J.glo[c] + cc[c] * J.h + half;
+            half2 += half * half;
+        }
+        const double shift = WIDE ? 0.0 : 0.5 * c2 * half2;
         int e = *gp(J.v_exp);
         if (e == INT32_MIN) e = 0;
         const MOT_GLOBAL double *tgt = gp(J.tgt_pts);
@@ -159,33 +167,37 @@ __global__ __launch_bounds__(64 * kTruncWaves) void trunc_mixed_kernel(const Pro
                 ra[nr + fpos - 1] = (int32_t)a;
                 rp[nr + fpos - 1] = total + lpos - len;
             }
-            nr += __shfl(fpos, 63);
-            total += __shfl(lpos, 63);
+            nr += __builtin_amdgcn_readlane(fpos, 63);
+            total += __builtin_amdgcn_readlane(lpos, 63);
         }
         if (lane == 0) rp[nr] = total;
         wave_sync();
-        typedef typename std::conditional<WIDE, double, float>::type real;
-        real xs[R][3];
-        double ax[R], acc[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const bool act = lane + 64 * r < cnt;
-            const int64_t i = (int64_t)itm.z + lane + 64 * r;
+        // targets: 16-wide tile t, lane l has component l / 16 of target l % 16
+        auto target = [&](int t, double &mine) {  // component of target 16 t + li; returns -c |x|^2
+            const bool act = 16 * t + li < cnt;
+            const int64_t i = (int64_t)itm.z + 16 * t + li;
             double nrm = 0.0;
+            mine = lk == 3 ? 1.0 : 0.0;
 #pragma unroll
-            for (int c = 0; c < 3; ++c) {
-                const double dx = (c < D && act) ? tgt[i * D + c] - ctr[c] : 0.0;
-                xs[r][c] = WIDE ? (real)dx : (real)(dx * sc);
+            for (int c = 0; c < D; ++c) {
+                const double dx = act ? tgt[i * D + c] - ctr[c] : 0.0;
+                if (lk == c) mine = dx;
                 nrm += dx * dx;
             }
-            ax[r] = -c2 * nrm;
-            acc[r] = 0.0;
+            return -c2 * nrm;
+        };
+        double xt[4], ax[4], acc[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            ax[t] = target(t, xt[t]);
+            acc[t] = 0.0;
         }
         // stages of 64 consecutive list entries; each lane follows its entry's row with a
         // pointer that only moves forward, and loads its source one stage ahead
         int row = 0;
         double ly[3] = {0.0, 0.0, 0.0}, lv = 0.0;
         auto fetch = [&](int q) {
+            lv = 0.0;
             if (q < total) {
                 while (rp[row + 1] <= q) ++row;
                 const int64_t j = (int64_t)ra[row] + (q - rp[row]);
@@ -194,76 +206,65 @@ __global__ __launch_bounds__(64 * kTruncWaves) void trunc_mixed_kernel(const Pro
                 lv = vv[j];
             }
         };
-        fetch(lane);
-        for (int s0 = 0; s0 < total; s0 += 64) {
-            const int nj = min(64, total - s0);
-            wave_sync();
-            if (lane < nj) {
-                if constexpr (WIDE) {
-                    double nrm = 0.0;
-                    sw[lane][0] = sw[lane][1] = sw[lane][2] = 0.0;
+        // position of a source's value: the FP64 tile's register r of lane group g is source g + 4 r
+        const int vpos = (lane & 48) | ((lane & 3) << 2) | ((lane >> 2) & 3);
+        auto scan = [&](auto NT) {
+            for (int s0 = 0; s0 < total; s0 += 64) {
+                const int steps = (min(64, total - s0) + 15) >> 4;
+                wave_sync();
+                {
+                    double nrm = 0.0;  // entries past the list's end have the value 0
 #pragma unroll
-                    for (int c = 0; c < D; ++c) {
-                        const double dy = ly[c] - ctr[c];
-                        sw[lane][c] = 2.0 * c2 * dy;
+                    for (int c = 0; c < 3; ++c) {
+                        const double dy = c < D ? ly[c] - ctr[c] : 0.0;
+                        sw[c * kSrcPitch + lane] = 2.0 * c2 * dy;
                         nrm += dy * dy;
                     }
-                    sw[lane][3] = -c2 * nrm;
-                    sv[lane] = (float)ldexp(lv, -e);
-                } else {
-                    float y[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-                    for (int c = 0; c < D; ++c) y[c] = (float)((ly[c] - ctr[c]) * sc);
-                    sy[lane] = make_float4(y[0], y[1], y[2], (float)ldexp(lv, -e));
+                    sw[3 * kSrcPitch + lane] = -c2 * nrm;
+                    sv[vpos] = (float)ldexp(lv, -e);
                 }
-            }
-            wave_sync();
-            fetch(s0 + 64 + lane);
-            float part[R];
+                wave_sync();
+                fetch(s0 + 64 + lane);
+                float part[NT];
 #pragma unroll
-            for (int r = 0; r < R; ++r) part[r] = 0.0f;
-            if constexpr (WIDE) {
-#pragma unroll 2
-                for (int jj = 0; jj < nj; ++jj) {
-                    const double s0v = sw[jj][0], s1 = sw[jj][1], s2 = sw[jj][2], s3 = sw[jj][3];
-                    const float w = sv[jj];
+                for (int t = 0; t < NT; ++t) part[t] = 0.0f;
+                for (int m = 0; m < steps; ++m) {
+                    const double a = sw[lk * kSrcPitch + 16 * m + li];
+                    const f32x4 w = reinterpret_cast<const f32x4 *>(sv)[4 * m + lk];
+                    f64x4 g[NT];
 #pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        double arg = ax[r] + s3;
-                        arg = fma(xs[r][0], s0v, arg);
-                        if (D > 1) arg = fma(xs[r][1], s1, arg);
-                        if (D > 2) arg = fma(xs[r][2], s2, arg);
-                        part[r] = fmaf(w, __builtin_amdgcn_exp2f((float)arg), part[r]);
+                    for (int t = 0; t < NT; ++t) {
+                        const double c0 = WIDE ? ax[t] : -shift;
+                        g[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, xt[t], f64x4{c0, c0, c0, c0}, 0, 0, 0);
                     }
-                }
-            } else {
-#pragma unroll 2
-                for (int jj = 0; jj < nj; ++jj) {
-                    const float4 y = sy[jj];
 #pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        const float dx = xs[r][0] - y.x;
-                        float q = dx * dx;
-                        if (D > 1) {
-                            const float dy = xs[r][1] - y.y;
-                            q = fmaf(dy, dy, q);
-                        }
-                        if (D > 2) {
-                            const float dz = xs[r][2] - y.z;
-                            q = fmaf(dz, dz, q);
-                        }
-                        part[r] = fmaf(y.w, __builtin_amdgcn_exp2f(-q), part[r]);
-                    }
+                    for (int t = 0; t < NT; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            part[t] = fmaf(w[r], __builtin_amdgcn_exp2f((float)g[t][r]), part[t]);
                 }
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[t] += (double)part[t];
             }
-#pragma unroll
-            for (int r = 0; r < R; ++r) acc[r] += (double)part[r];
+        };
+        fetch(lane);
+        switch ((cnt + 15) >> 4) {
+        case 1: scan(std::integral_constant<int, 1>()); break;
+        case 2: scan(std::integral_constant<int, 2>()); break;
+        case 3: scan(std::integral_constant<int, 3>()); break;
+        default: scan(std::integral_constant<int, 4>()); break;
         }
         MOT_GLOBAL double *out = gp(J.out);
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int64_t i = (int64_t)itm.z + lane + 64 * r;
-            if (lane + 64 * r < cnt) out[i] = ldexp(acc[r], e);
+        for (int t = 0; t < 4; ++t) {
+            double s = acc[t];
+            s += lane_xor(s, 16);
+            s += lane_xor(s, 32);
+            if constexpr (!WIDE) {
+                double x;
+                s *= exp2(target(t, x) + shift);
+            }
+            if (lk == 0 && 16 * t + li < cnt) out[(int64_t)itm.z + 16 * t + li] = ldexp(s, e);
         }
     }
 }
@@ -341,15 +342,10 @@ static void launch_trunc_d(int precision, int R, int wide, const ProdJob *jobs, 
     } else {
         const int blocks = (n_items + kTruncWaves - 1) / kTruncWaves;
         const dim3 grid(blocks < (1 << 20) ? blocks : (1 << 20)), block(64 * kTruncWaves);
-        if (wide) {
-            if (R == 1) hipLaunchKernelGGL((trunc_mixed_kernel<D, 1, true>), grid, block, 0, s, jobs, items, n_items);
-            if (R == 2) hipLaunchKernelGGL((trunc_mixed_kernel<D, 2, true>), grid, block, 0, s, jobs, items, n_items);
-            if (R == 4) hipLaunchKernelGGL((trunc_mixed_kernel<D, 4, true>), grid, block, 0, s, jobs, items, n_items);
-        } else {
-            if (R == 1) hipLaunchKernelGGL((trunc_mixed_kernel<D, 1, false>), grid, block, 0, s, jobs, items, n_items);
-            if (R == 2) hipLaunchKernelGGL((trunc_mixed_kernel<D, 2, false>), grid, block, 0, s, jobs, items, n_items);
-            if (R == 4) hipLaunchKernelGGL((trunc_mixed_kernel<D, 4, false>), grid, block, 0, s, jobs, items, n_items);
-        }
+        if (wide)
+            hipLaunchKernelGGL((trunc_mixed_kernel<D, true>), grid, block, 0, s, jobs, items, n_items);
+        else
+            hipLaunchKernelGGL((trunc_mixed_kernel<D, false>), grid, block, 0, s, jobs, items, n_items);
     }
 }
 
@@ -357,8 +353,7 @@ hipError_t launch_trunc(int d, int precision, int R, int wide, const ProdJob *jo
                         int n_items, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    if (R != 1 && R != 2 && R != 4) return hipErrorInvalidValue;
-    if (precision == MOT_PREC_FP64 && R == 4) return hipErrorInvalidValue;
+    if (R != 1 && (R != 2 || precision != MOT_PREC_FP64)) return hipErrorInvalidValue;
     if (d == 1) launch_trunc_d<1>(precision, R, wide, jobs_dev, items, n_items, s);
     if (d == 2) launch_trunc_d<2>(precision, R, wide, jobs_dev, items, n_items, s);
     if (d == 3) launch_trunc_d<3>(precision, R, wide, jobs_dev, items, n_items, s);

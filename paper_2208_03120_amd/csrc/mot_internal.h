@@ -188,8 +188,8 @@ int direct_items_wanted(int precision);
 int direct_source_split(int64_t nt, int64_t ns, int precision);
 constexpr int kMaxTruncRows = 400;  // neighbour rows per truncated work item, (2w + 1)^(d-1)
 // Truncated products: items int4 (job, first cell of a run of B cells of one row, first
-// sorted target, count | B << 16), count <= 64 * R; R = 1, 2 or 4 (FP64: 1 or 2).
-// wide != 0 (mixed precision): exponent formed in FP64 instead of FP32 coordinate differences
+// sorted target, count | B << 16), count <= 64 * R; R = 1 or 2 (mixed precision: 1).
+// wide != 0 (mixed precision): runs so long that every target needs its own exponent offset
 hipError_t launch_trunc(int d, int precision, int R, int wide, const ProdJob *jobs_dev, const int4 *items,
                         int n_items, hipStream_t s);
 // diff != 0: mixed-precision pairs with the exponent formed in FP64 (small eta)

@@ -467,12 +467,9 @@ static double expected_chunks(double lam, int cap)
     return s;
 }
 
-// Modelled wave cycles of one product: per row ~100, per 64-source stage ~200, per source
-// and target slot ~40 (FP32 coordinate differences) or ~66 (FP64 exponent).  Points are
-// taken as Poisson counts per cell: lam_t / lam_s targets / sources per full cell (the
-// cloud's density times h^d).  A run of B cells holding k targets takes ceil(k / 64R)
-// items; the runs are those of the cells covering the cloud's box.
-double trunc_cost(int d, const TruncParams &T, double lam_t, double lam_s, int B, int R, bool wide)
+// Rows and sources of an interior run of B cells, and the runs covering the cloud's box.
+static void trunc_run_sources(int d, const TruncParams &T, double lam_s, int B, double *rows_out, double *src_out,
+                              double *runs_out)
 {
     const int span = 2 * T.w + 1;
     const int rows_total = d == 1 ? 1 : (d == 2 ? span : span * span);
@@ -490,8 +487,21 @@ double trunc_cost(int d, const TruncParams &T, double lam_t, double lam_s, int B
     double runs = 1.0;
     for (int c = 0; c < d - 1; ++c) runs *= T.box_cells[c];
     runs *= std::ceil(T.box_cells[d - 1] / B);
+    *rows_out = rows;
+    *src_out = cells * lam_s;
+    *runs_out = runs;
+}
+
+// Modelled wave cycles of one FP64 product (and the model its cell side is chosen with): per row ~100, per 64-source stage ~200, per source
+// and target slot ~40 (FP32 coordinate differences) or ~66 (FP64 exponent).  Points are
+// taken as Poisson counts per cell: lam_t / lam_s targets / sources per full cell (the
+// cloud's density times h^d).  A run of B cells holding k targets takes ceil(k / 64R)
+// items; the runs are those of the cells covering the cloud's box.
+static double trunc_cost(int d, const TruncParams &T, double lam_t, double lam_s, int B, int R, bool wide)
+{
+    double rows, src, runs;
+    trunc_run_sources(d, T, lam_s, B, &rows, &src, &runs);
     const double items = runs * expected_chunks(lam_t * B, 64 * R);
-    const double src = cells * lam_s;
     return items * (rows * 100.0 + (src / 64.0 + rows) * 200.0 + src * R * (wide ? 66.0 : 40.0));
 }
 
@@ -500,6 +510,35 @@ double trunc_cost(int d, const TruncParams &T, double lam_t, double lam_s, int B
 static double run_extent(int d, const TruncParams &T, double sch, int B)
 {
     return sch * std::sqrt(0.25 * B * B + 0.25 * (d - 1));
+}
+
+// The same for a mixed product: per row ~100 and per 64-source stage ~300 of an item of up to
+// 64 targets, and per source ~8.2 for each tile of 16 targets (131 per 16 x 16 pairs).
+static double trunc_cost_mixed(int d, const TruncParams &T, double lam_t, double lam_s, int B)
+{
+    double rows, src, runs;
+    trunc_run_sources(d, T, lam_s, B, &rows, &src, &runs);
+    return runs * (expected_chunks(lam_t * B, 64) * (rows * 100.0 + (src / 64.0 + 1.0) * 300.0) +
+                   expected_chunks(lam_t * B, 16) * src * 8.2);
+}
+
+// Scaled half-diagonal up to which a mixed run's exponents share one shift (k_trunc.hip).
+constexpr double kTruncShiftExtent = 14.0;
+
+double trunc_choose_mixed(int d, const TruncParams &T, double lam_t, double lam_s, double sch, int *B, int *wide)
+{
+    double best = -1.0;
+    *B = 1;
+    for (int b : {1, 2, 3, 4, 6, 8, 12, 16}) {
+        if (b > T.nc) break;
+        const double c = trunc_cost_mixed(d, T, lam_t, lam_s, b);
+        if (best < 0 || c < best) {
+            best = c;
+            *B = b;
+        }
+    }
+    *wide = run_extent(d, T, sch, *B) > kTruncShiftExtent;
+    return best;
 }
 
 void trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, int max_r, double sch, bool fp64,
@@ -528,7 +567,7 @@ void trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, i
 }
 
 int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params *fs, double n_mean,
-                  TruncParams *out)
+                  int precision, TruncParams *out)
 {
     const double target = fs && fs->target_rel_err > 0 ? fs->target_rel_err : 1e-7;
     if (!(target < 1.0)) return MOT_EINVAL;
@@ -564,8 +603,14 @@ int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params
         const double lam = std::max(n_mean, 1.0) * std::pow(C.h, d) / Vb;  // points per full cell
         const double sch = std::sqrt(1.4426950408889634 / eta) * C.h;
         int wide = 0;
-        trunc_choose_run(d, C, lam, lam, 4, sch, false, &C.B, &C.R, &wide);
-        const double cost = trunc_cost(d, C, lam, lam, C.B, C.R, wide != 0);
+        double cost;
+        if (precision == MOT_PREC_FP64) {
+            trunc_choose_run(d, C, lam, lam, 4, sch, false, &C.B, &C.R, &wide);
+            cost = trunc_cost(d, C, lam, lam, C.B, C.R, wide != 0);
+        } else {
+            C.R = 1;
+            cost = trunc_choose_mixed(d, C, lam, lam, sch, &C.B, &wide);
+        }
         if (best < 0 || cost < best) {
             best = cost;
             *out = C;

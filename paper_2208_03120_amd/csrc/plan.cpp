@@ -1085,9 +1085,14 @@ int mot::make_prod_job(mot_plan_s *P, int t, int s, const double *v, int32_t *sl
         // densities (points per grid cell)
         double cells = 1.0;  // full cells covering the cloud's box
         for (int c = 0; c < P->d; ++c) cells *= T.box_cells[c];
-        const bool fp64 = P->precision == MOT_PREC_FP64;
-        trunc_choose_run(P->d, T, (double)Q.nt / cells, (double)Q.ns / cells, fp64 ? 2 : 4,
-                         std::sqrt(1.4426950408889634 / Q.eta) * T.h, fp64, &Q.trunc_b, &Q.trunc_r, &Q.diff);
+        const double lam_t = (double)Q.nt / cells, lam_s = (double)Q.ns / cells;
+        const double sch = std::sqrt(1.4426950408889634 / Q.eta) * T.h;
+        if (P->precision == MOT_PREC_FP64) {
+            trunc_choose_run(P->d, T, lam_t, lam_s, 2, sch, true, &Q.trunc_b, &Q.trunc_r, &Q.diff);
+        } else {
+            Q.trunc_r = 1;
+            (void)trunc_choose_mixed(P->d, T, lam_t, lam_s, sch, &Q.trunc_b, &Q.diff);
+        }
         return MOT_OK;
     }
     if (P->path != MOT_NFFT) return MOT_OK;
@@ -1193,7 +1198,7 @@ int mot::setup_marginals(mot_plan_s *P, const std::vector<double> &pts_h, const 
     if (P->path == MOT_TRUNC) {
         double nsum = 0.0;
         for (int k = 0; k < K; ++k) nsum += (double)P->n[k];
-        MOT_TRY(resolve_trunc(d, etas.back(), P->ext, fs, nsum / K, &P->TP));
+        MOT_TRY(resolve_trunc(d, etas.back(), P->ext, fs, nsum / K, P->precision, &P->TP));
         log_msg("truncation: eps=%.3g r_c=%.6g h=%.6g cells=%d^%d w=%d", P->TP.eps, P->TP.rc, P->TP.h,
                 P->TP.nc, d, P->TP.w);
     }
@@ -2087,7 +2092,7 @@ int mot_plan_footprint(int32_t K, int32_t d, const int64_t *n, int32_t topology,
         E.width_max = 2.0 * half_width;
         E.diag = 2.0 * half_width * std::sqrt((double)d);
         TruncParams T;
-        int rc = resolve_trunc(d, eta, E, fs, (double)total / K, &T);
+        int rc = resolve_trunc(d, eta, E, fs, (double)total / K, precision, &T);
         if (rc < 0) return rc;
         const int64_t ncell = trunc_cells(d, T);
         b += (size_t)(K + 1) * (ncell + 1) * 4 + stable_tile_sort_scratch(nmax, ncell);
