@@ -148,6 +148,7 @@ struct Step {
     int lane = 0;                 // i >= 1: runs on side stream i - 1 between ST_FORK and ST_JOIN
     int d = 0, n = 0, fft_kind = 0, precision = 0, max_patch = 0, trunc_r = 0, diff = 0;
     int group = 0;                // 3-D spreading: jobs per item (items int4)
+    bool small = false;           // direct products and finalisation: the one-launch form
     int lds = 0;                  // one-launch transforms: LDS bytes of the largest job
     int max_children = 0;         // node update: most children of a node in the launch
     const void *jobs = nullptr;   // device ProdJob / NodeJob / FinalJob array
@@ -226,7 +227,7 @@ struct mot_plan_s {
     std::vector<int64_t> n, off;
     std::vector<int> parent, depth;
     std::vector<std::vector<int>> children;
-    int depth_max = 0;
+    int depth_max = 0, level_width = 1;  // most edges into one depth
     mot::Extent ext;
     mot::NfftParams P;
     mot::TruncParams TP;

@@ -1,9 +1,10 @@
 // Direct Gaussian-kernel products (a7), the plain O(n_t n_s) path:
 //   out_i = sum_j v_j exp(-|x_i - y_j|^2 / eta)      (Sec. 5, eq. fastsum-sum)
 //
-// Both precisions split a job's sources into dsplit equal ranges, so that products with few
-// targets still spread over the chip: an item is a group of targets and one range; with
-// dsplit > 1 it writes its partial sums to the job's partial buffer, and
+// Small products (direct_small_targets) run in one launch whose blocks split the sources among their
+// sixteen wavefronts.  Above, both precisions split a job's sources into dsplit equal ranges, so
+// that products with few targets still spread over the chip: an item is a group of targets and
+// one range; with dsplit > 1 it writes its partial sums to the job's partial buffer, and
 // direct_reduce_kernel adds the ranges in order.
 //
 // FP64 variant: one target per lane, a block's four wavefronts summing quarters of a
@@ -35,7 +36,23 @@ constexpr int kDirectT = 64;    // targets per FP64 item
 constexpr int kMixedT = 256;    // targets per mixed item, 64 per wavefront
 constexpr int kMixedS = 256;    // sources staged in LDS at a time
 
+constexpr int kSmallWaves = 16, kSmallT = 16;  // small products: wavefronts, targets of a block at most
+
 int direct_targets_per_item(int precision) { return precision == MOT_PREC_FP64 ? kDirectT : kMixedT; }
+
+// Targets of a block of the small form, for about 256 blocks of the `width` products that run
+// together (FP64: 2 to 16, mixed: a tile of 16), or 0 for products that take source ranges: a
+// second launch costs 3 us, but the small form reads a source once per block.  Paths of three
+// marginals in 2-D, 20 sweeps, FP64: 250 points 0.89 ms small, 1.11 with ranges; 1000 points
+// 1.06 and 1.21; 1500 points 1.28 and 1.36; 2500 points 2.09 and 1.78; mixed: 1000 points 1.04
+// and 1.30; 4000 points 1.32 and 1.64.
+int direct_small_targets(int precision, int64_t nt, int64_t ns, int width)
+{
+    if ((double)nt * ns * width > (precision == MOT_PREC_FP64 ? 2.6e6 : 3.2e7)) return 0;
+    int t = precision == MOT_PREC_FP64 ? 2 : kSmallT;
+    while (t < kSmallT && width * nt > 256 * t) t *= 2;
+    return width * nt > 256 * t && precision == MOT_PREC_FP64 ? 0 : t;
+}
 
 // Items a job is split into at least, while its sources last: two 256-thread blocks per CU in
 // mixed precision, four in FP64.  Without the split a star of four 3-D marginals of 3000
@@ -152,6 +169,78 @@ __global__ __launch_bounds__(256) void direct_fp64_kernel(const ProdJob *__restr
                 J.dpart[(int64_t)itm.z * J.nt + i] = sum;
             else
                 J.out[i] = sum;
+        }
+    }
+}
+
+// Small FP64 products: a block takes T = 2 to 16 targets (item: job, first target, T), lane l of
+// wavefront w the target l % T and every (1024 / T)-th source from (64 w + l) / T on; the lanes of
+// a target are added by lane exchanges, the wavefronts in order through LDS.  Bound by the
+// latency of the launch and its loads: a path of three marginals of 500 points spent 5.9 us in a
+// product's first launch and 3.7 us in adding its ranges.
+template <int D>
+__global__ __launch_bounds__(64 * kSmallWaves) void direct_fp64_small_kernel(const ProdJob *__restrict__ jobs,
+                                                                             const int4 *__restrict__ items,
+                                                                             int n_items)
+{
+    __shared__ double red[kSmallWaves][kSmallT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+        const int4 itm = items[it];
+        const ProdJob &J = jobs[itm.x];
+        const int T = itm.z, stride = 64 * kSmallWaves / T;
+        const int64_t i = (int64_t)itm.y + (lane & (T - 1));
+        const bool act = i < J.nt;
+        const MOT_GLOBAL double *y = gp(J.src_pts), *v = gp(J.v);
+        const int ns = (int)J.ns;
+        constexpr int U = 4;  // sources in flight per lane
+        double x[D], yv[U][D + 1], acc = 0.0;
+        auto fetch = [&](int j0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int j = j0 + stride * u, jc = j < ns ? j : 0;
+#pragma unroll
+                for (int c = 0; c < D; ++c) yv[u][c] = y[jc * D + c];
+                yv[u][D] = j < ns ? v[jc] : 0.0;
+            }
+        };
+        const int first = tid / T;
+        fetch(first);
+#pragma unroll
+        for (int c = 0; c < D; ++c) x[c] = act ? gp(J.tgt_pts)[i * D + c] : 0.0;
+        const ExpScale E = exp_scale(J.eta);
+        for (int j = first; j < ns; j += stride * U) {
+            double w[U][D + 1];
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int c = 0; c <= D; ++c) w[u][c] = yv[u][c];
+            if (j + stride * U < ns) fetch(j + stride * U);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (j + stride * u >= ns) break;
+                double d2 = 0.0;
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    const double df = x[c] - w[u][c];
+                    d2 = fma(df, df, d2);
+                }
+                acc = fma(w[u][D], exp2_scaled(d2, E), acc);
+            }
+        }
+        if (T <= 2) acc += lane_xor(acc, 2);
+        if (T <= 4) acc += lane_xor(acc, 4);
+        if (T <= 8) acc += lane_xor(acc, 8);
+        acc += lane_xor(acc, 16);
+        acc += lane_xor(acc, 32);
+        __syncthreads();  // the previous item's reads of red are done
+        if (lane < T) red[wave][lane] = acc;
+        __syncthreads();
+        if (tid < T && act) {
+            double sum = 0.0;
+#pragma unroll
+            for (int w = 0; w < kSmallWaves; ++w) sum += red[w][tid];
+            gp(J.out)[i] = sum;
         }
     }
 }
@@ -316,25 +405,143 @@ __global__ __launch_bounds__(256, 4) void direct_mixed_kernel(const ProdJob *__r
     }
 }
 
-template <int D>
-static void launch_direct_d(const ProdJob *jobs, const int4 *items, int n_items, int precision, int diff, hipStream_t s)
+// Small mixed products: a block takes one tile of 16 targets, wavefront w the w-th sixteenth of
+// the sources (a multiple of 16), staged 64 at a time in its own LDS slice; the exponents as
+// above, the wavefronts' sums added in order through LDS.  (64 targets to a block left most of
+// the chip idle: 20 sweeps of a star of four 1000-point marginals 0.95 ms, here 0.78.)
+template <int D, bool WIDE>
+__global__ __launch_bounds__(64 * kSmallWaves) void direct_mixed_small_kernel(const ProdJob *__restrict__ jobs,
+                                                                              const int4 *__restrict__ items,
+                                                                              int n_items)
 {
-    const dim3 grid(n_items < 65535 ? n_items : 65535), block(256);
-    if (precision == MOT_PREC_FP64)
-        hipLaunchKernelGGL(direct_fp64_kernel<D>, grid, block, 0, s, jobs, items, n_items);
-    else if (diff)
-        hipLaunchKernelGGL((direct_mixed_kernel<D, true>), grid, block, 0, s, jobs, items, n_items);
-    else
-        hipLaunchKernelGGL((direct_mixed_kernel<D, false>), grid, block, 0, s, jobs, items, n_items);
+    typedef typename std::conditional<WIDE, double, float>::type real;
+    typedef typename std::conditional<WIDE, f64x4, f32x4>::type real4;
+    constexpr int kPitch = 64 + (WIDE ? 8 : 16);
+    __shared__ real sy_all[kSmallWaves][4 * kPitch];
+    __shared__ __align__(16) float sv_all[kSmallWaves][64];
+    __shared__ double red[kSmallWaves][kSmallT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lk = lane >> 4;
+    real *sy = sy_all[wave];
+    float *sv = sv_all[wave];
+    for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
+        const int4 itm = items[it];
+        const ProdJob &J = jobs[itm.x];
+        const MOT_GLOBAL double *src = gp(J.src_pts), *vv = gp(J.v), *tgt = gp(J.tgt_pts);
+        const int ns = (int)J.ns;
+        const int per = (ns + 16 * kSmallWaves - 1) / (16 * kSmallWaves) * 16;
+        const int ja = min(ns, wave * per), jb = min(ns, ja + per);
+        double ly[3] = {0.0, 0.0, 0.0}, lv = 0.0;
+        auto fetch = [&](int j) {
+            lv = 0.0;
+            if (j < jb) {
+#pragma unroll
+                for (int c = 0; c < D; ++c) ly[c] = src[(int64_t)j * D + c];
+                lv = vv[j];
+            }
+        };
+        fetch(ja + lane);
+        const double c2 = 1.4426950408889634 / J.eta;  // log2(e) / eta
+        int e = *gp(J.v_exp);
+        if (e == INT32_MIN) e = 0;
+        const int64_t i = (int64_t)itm.y + li;
+        double nrmx = 0.0, mine = lk == 3 ? 1.0 : 0.0, acc = 0.0;
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            const double dx = i < J.nt ? tgt[i * D + c] - J.ctr[c] : 0.0;
+            if (lk == c) mine = dx;
+            nrmx += dx * dx;
+        }
+        const real xt = (real)mine;
+        const double ax = -c2 * nrmx;
+        // position of a source's value: register r of the FP64 tile's lane group g is source g + 4 r
+        const int vpos = WIDE ? (lane & 48) | ((lane & 3) << 2) | ((lane >> 2) & 3) : lane;
+        for (int j0 = ja; j0 < jb; j0 += 64) {
+            const int steps = (min(64, jb - j0) + 15) >> 4;
+            wave_sync();
+            double nrm = 0.0;
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                const double dy = c < D ? ly[c] - J.ctr[c] : 0.0;
+                sy[c * kPitch + lane] = (real)(2.0 * c2 * dy);
+                nrm += dy * dy;
+            }
+            sy[3 * kPitch + lane] = (real)(-c2 * nrm);
+            sv[vpos] = (float)ldexp(lv, -e);
+            wave_sync();
+            fetch(j0 + 64 + lane);
+            float part = 0.0f;
+            auto add = [&](auto U) {  // U tiles of 16 sources
+                real4 g[U];
+                f32x4 w[U];
+#pragma unroll
+                for (int m = 0; m < U; ++m) {
+                    const real a = sy[lk * kPitch + 16 * m + li];
+                    w[m] = reinterpret_cast<const f32x4 *>(sv)[4 * m + lk];
+                    if constexpr (WIDE)
+                        g[m] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, xt, f64x4{ax, ax, ax, ax}, 0, 0, 0);
+                    else
+                        g[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, xt, f32x4{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+                }
+#pragma unroll
+                for (int m = 0; m < U; ++m)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        part = fmaf(w[m][r], __builtin_amdgcn_exp2f((float)g[m][r]), part);
+            };
+            switch (steps) {
+            case 1: add(std::integral_constant<int, 1>()); break;
+            case 2: add(std::integral_constant<int, 2>()); break;
+            case 3: add(std::integral_constant<int, 3>()); break;
+            default: add(std::integral_constant<int, 4>()); break;
+            }
+            acc += (double)part;
+        }
+        __syncthreads();  // the previous item's reads of red are done
+        acc += lane_xor(acc, 16);
+        acc += lane_xor(acc, 32);
+        if constexpr (!WIDE) acc *= exp2(ax);
+        if (lk == 0) red[wave][li] = acc;
+        __syncthreads();
+        if (tid < kSmallT && itm.y + tid < J.nt) {
+            double sum = 0.0;
+#pragma unroll
+            for (int w = 0; w < kSmallWaves; ++w) sum += red[w][tid];
+            gp(J.out)[(int64_t)itm.y + tid] = ldexp(sum, e);
+        }
+    }
+}
+
+template <int D>
+static void launch_direct_d(const ProdJob *jobs, const int4 *items, int n_items, int precision, int diff, bool small,
+                            hipStream_t s)
+{
+    const dim3 grid(n_items < 65535 ? n_items : 65535), block(small ? 64 * kSmallWaves : 256);
+    if (precision == MOT_PREC_FP64) {
+        if (small)
+            hipLaunchKernelGGL(direct_fp64_small_kernel<D>, grid, block, 0, s, jobs, items, n_items);
+        else
+            hipLaunchKernelGGL(direct_fp64_kernel<D>, grid, block, 0, s, jobs, items, n_items);
+    } else if (diff) {
+        if (small)
+            hipLaunchKernelGGL((direct_mixed_small_kernel<D, true>), grid, block, 0, s, jobs, items, n_items);
+        else
+            hipLaunchKernelGGL((direct_mixed_kernel<D, true>), grid, block, 0, s, jobs, items, n_items);
+    } else {
+        if (small)
+            hipLaunchKernelGGL((direct_mixed_small_kernel<D, false>), grid, block, 0, s, jobs, items, n_items);
+        else
+            hipLaunchKernelGGL((direct_mixed_kernel<D, false>), grid, block, 0, s, jobs, items, n_items);
+    }
 }
 
 hipError_t launch_direct(int d, const ProdJob *jobs_dev, const int4 *items, int n_items, const int2 *red_items,
-                         int n_red, int precision, int diff, hipStream_t s)
+                         int n_red, int precision, int diff, bool small, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
-    if (d == 1) launch_direct_d<1>(jobs_dev, items, n_items, precision, diff, s);
-    if (d == 2) launch_direct_d<2>(jobs_dev, items, n_items, precision, diff, s);
-    if (d == 3) launch_direct_d<3>(jobs_dev, items, n_items, precision, diff, s);
+    if (d == 1) launch_direct_d<1>(jobs_dev, items, n_items, precision, diff, small, s);
+    if (d == 2) launch_direct_d<2>(jobs_dev, items, n_items, precision, diff, small, s);
+    if (d == 3) launch_direct_d<3>(jobs_dev, items, n_items, precision, diff, small, s);
     if (n_red > 0)
         hipLaunchKernelGGL(direct_reduce_kernel, dim3(n_red < 16384 ? n_red : 16384), dim3(256), 0, s, jobs_dev,
                            red_items, n_red);

@@ -36,30 +36,44 @@ __device__ __forceinline__ int wave_max_int(int v)
     return v;
 }
 
-__device__ __forceinline__ double block_sum(double v, double *red)
+__device__ __forceinline__ double wave_sum(double v)
 {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) v += lane_xor(v, o);
+    return v;
+}
+
+// Sum over the four wavefronts of a 256-thread group whose wavefronts wrote their sums to red.
+__device__ __forceinline__ double group_sum(const double *red)
+{
+    return ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+__device__ __forceinline__ double block_sum(double v, double *red)
+{
+    v = wave_sum(v);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     __syncthreads();
     if (lane == 0) red[wave] = v;
     __syncthreads();
-    double s = 0.0;
-    for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
-    return s;
+    return group_sum(red);
 }
 
 // One node item: up to kNodeItemElems elements of one node.  The messages of up to RC
 // children are held in registers (loaded before any output is written); a node with more
 // children reads them from memory for every product and records the exponent maxima of its
-// down sources with one atomic per element.
+// down sources with one atomic per element.  Launches of small trees are bound by the chain
+// of dependent loads, the FP64 logarithm and division and the block's reductions: the child
+// pointers of up to kInlineChildren children are in the job itself, the logarithm is taken
+// while the messages load, and all reductions meet at one barrier (500 points: 4.9 -> 4.5 us).
 template <int RC>
 __global__ __launch_bounds__(256) void node_kernel(const NodeJob *__restrict__ jobs,
                                                    const int2 *__restrict__ items, int n_items)
 {
-    __shared__ double red[4];
+    __shared__ double red[2][4];
     __shared__ int emx[4][RC + 1];
-    const int tid = threadIdx.x;
+    constexpr bool INL = RC <= kInlineChildren;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 itm = items[it];
         const NodeJob &J = jobs[itm.x];
@@ -68,6 +82,8 @@ __global__ __launch_bounds__(256) void node_kernel(const NodeJob *__restrict__ j
         const bool freen = op & 32;
         const int nch = J.nchild;
         const bool regs = nch <= RC;
+        auto beta_of = [&](int t) { return INL ? J.beta_in[t] : (const double *)gp(J.beta)[t]; };
+        auto down_of = [&](int t) { return INL ? J.down_in[t] : (double *)gp(J.down_src)[t]; };
         double s1 = 0.0, s2 = 0.0;
         int em_up = INT32_MIN;
         int em[RC];
@@ -92,9 +108,13 @@ __global__ __launch_bounds__(256) void node_kernel(const NodeJob *__restrict__ j
                 if (regs)
 #pragma unroll
                     for (int t = 0; t < RC; ++t)
-                        if (t < nch) b[t][k] = gp(gp(J.beta)[t])[i];
+                        if (t < nch) b[t][k] = gp(beta_of(t))[i];
             }
         }
+        if (upd && !freen)
+#pragma unroll
+            for (int k = 0; k < kNodeEPT; ++k)
+                if ((int64_t)itm.y + tid + 256 * k < J.n && mu_k[k] > 0.0) s1 += mu_k[k] * log(ph_k[k]);
 #pragma unroll
         for (int k = 0; k < kNodeEPT; ++k) {
             const int64_t i = (int64_t)itm.y + tid + 256 * k;
@@ -115,10 +135,7 @@ __global__ __launch_bounds__(256) void node_kernel(const NodeJob *__restrict__ j
                 ph = 1.0;
             } else if (upd) {
                 const double nv = mu / (g * cp);
-                if (mu > 0.0) {
-                    s1 += mu * log(ph);
-                    if (root) s2 += (mu / nv) * ph;
-                }
+                if (root && mu > 0.0) s2 += (mu / nv) * ph;
                 if (!isfinite(nv)) bad = true;
                 gp(J.phi)[i] = nv;
                 ph = nv;
@@ -144,7 +161,7 @@ __global__ __launch_bounds__(256) void node_kernel(const NodeJob *__restrict__ j
                         for (int t = 0; t < RC; ++t)
                             if (t < nch && t != c) w *= b[t][k];
                         const double u = pg * w;
-                        gp(gp(J.down_src)[c])[i] = u;
+                        gp(down_of(c))[i] = u;
                         em[c] = max(em[c], exp_of(u));
                     }
                 } else {
@@ -160,41 +177,41 @@ __global__ __launch_bounds__(256) void node_kernel(const NodeJob *__restrict__ j
             }
         }
         if (bad) atomicOr(J.flag, 1);
-        // exponent maxima: wave max, then block max, then one atomic per block and vector
-        if (usrc || dsrc) {
-            const int wave = tid >> 6, lane = tid & 63;
-            __syncthreads();
-            if (usrc) {
-                const int m = wave_max_int(em_up);
-                if (lane == 0) emx[wave][RC] = m;
+        // wavefront sums and exponent maxima, then over the block: one partial sum pair per
+        // item and one atomic per vector
+        if (it != (int)blockIdx.x) __syncthreads();  // the previous item's reads of LDS are done
+        if (upd || marg) {
+            const double t1 = wave_sum(s1);
+            const double t2 = root ? wave_sum(s2) : 0.0;
+            if (lane == 0) {
+                red[0][wave] = t1;
+                red[1][wave] = t2;
             }
-            if (dsrc && regs) {
+        }
+        if (usrc) {
+            const int m = wave_max_int(em_up);
+            if (lane == 0) emx[wave][RC] = m;
+        }
+        if (dsrc && regs) {
 #pragma unroll
-                for (int c = 0; c < RC; ++c) {
-                    if (c < nch) {  // nch is uniform over the block
-                        const int m = wave_max_int(em[c]);
-                        if (lane == 0) emx[wave][c] = m;
-                    }
-                }
-            }
-            __syncthreads();
-            if (tid <= RC) {
-                const bool is_up = tid == RC;
-                if ((is_up && usrc) || (!is_up && dsrc && regs && tid < nch)) {
-                    int m = emx[0][tid];
-                    for (int w = 1; w < (int)(blockDim.x >> 6); ++w) m = max(m, emx[w][tid]);
-                    if (m != INT32_MIN) atomicMax(is_up ? J.up_exp : J.down_exp[tid], m);
+            for (int c = 0; c < RC; ++c) {
+                if (c < nch) {  // nch is uniform over the block
+                    const int m = wave_max_int(em[c]);
+                    if (lane == 0) emx[wave][c] = m;
                 }
             }
         }
-        if (upd || marg) {
-            const double t1 = block_sum(s1, red);
-            const double t2 = block_sum(s2, red);
-            if (tid == 0) {
-                const int slot = J.block0 + (int)(itm.y / kNodeElems);
-                gp(J.partial)[2 * slot] = t1;
-                gp(J.partial)[2 * slot + 1] = t2;
+        __syncthreads();
+        if (tid <= RC) {
+            const bool is_up = tid == RC;
+            if ((is_up && usrc) || (!is_up && dsrc && regs && tid < nch)) {
+                const int m = max(max(emx[0][tid], emx[1][tid]), max(emx[2][tid], emx[3][tid]));
+                if (m != INT32_MIN) atomicMax(is_up ? J.up_exp : (INL ? J.dexp_in[tid] : J.down_exp[tid]), m);
             }
+        }
+        if ((upd || marg) && tid >= 64 && tid < 66) {  // the second wavefront, beside the atomics
+            const int slot = J.block0 + (int)(itm.y / kNodeElems);
+            gp(J.partial)[2 * slot + tid - 64] = group_sum(red[tid - 64]);
         }
     }
 }
@@ -226,55 +243,90 @@ hipError_t launch_node(const NodeJob *jobs_dev, const int2 *items, int n_items, 
 //     the next sweep.
 // The kernel boundary orders the partials before their reduction, so no block waits on
 // another and no device-scope fence is needed.
+// L1 error of the elements first + tid, first + tid + 256, .. of an item.
+__device__ __forceinline__ double finalize_l1(const FinalJob &J, int64_t first, int tid)
+{
+    // child products of all of this thread's elements, children in ascending order
+    double cp[kNodeEPT], l1 = 0.0;
+    bool ok[kNodeEPT];
+#pragma unroll
+    for (int k = 0; k < kNodeEPT; ++k) {
+        cp[k] = 1.0;
+        ok[k] = first + tid + 256 * k < J.n0;
+    }
+    if (J.nchild <= kRegChildren) {
+        // all children's messages loaded before the products, so the loads are in
+        // flight together; multiplied in ascending child order
+        double b[kRegChildren][kNodeEPT];
+#pragma unroll
+        for (int t = 0; t < kRegChildren; ++t)
+#pragma unroll
+            for (int k = 0; k < kNodeEPT; ++k)
+                b[t][k] = (t < J.nchild && ok[k]) ? gp(gp(J.root_beta)[t])[first + tid + 256 * k] : 1.0;
+#pragma unroll
+        for (int t = 0; t < kRegChildren; ++t)
+#pragma unroll
+            for (int k = 0; k < kNodeEPT; ++k)
+                if (t < J.nchild) cp[k] *= b[t][k];
+    } else {
+        for (int t = 0; t < J.nchild; ++t) {
+            const MOT_GLOBAL double *bt = gp(gp(J.root_beta)[t]);
+#pragma unroll
+            for (int k = 0; k < kNodeEPT; ++k)
+                if (ok[k]) cp[k] *= bt[first + tid + 256 * k];
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < kNodeEPT; ++k) {
+        const int64_t i = first + tid + 256 * k;
+        if (ok[k]) l1 += fabs(gp(J.phi0)[i] * cp[k] - gp(J.mu0)[i]);
+    }
+    return l1;
+}
+
+// Thread tid's share (of 256) of the node updates' partial sums: a fixed strided subset.  Eight
+// strided partials are loaded before they are added (in the same order), so the loads of a
+// thread are in flight together.
+__device__ __forceinline__ void finalize_partials(const FinalJob &J, int tid, double &s1, double &s2)
+{
+    constexpr int U = 8;
+    s1 = s2 = 0.0;
+    for (int p0 = tid; p0 < J.n_partials; p0 += U * 256) {
+        double a[U], b[U];
+#pragma unroll
+        for (int q = 0; q < U; ++q) {
+            const int p = p0 + q * 256;
+            a[q] = p < J.n_partials ? J.s_partial[2 * p] : 0.0;
+            b[q] = p < J.n_partials ? J.s_partial[2 * p + 1] : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+            if (p0 + q * 256 < J.n_partials) {
+                s1 += a[q];
+                s2 += b[q];
+            }
+    }
+}
+
+__device__ __forceinline__ void finalize_record(const FinalJob &J, double s1, double s2, double e1)
+{
+    const int r = *J.sweep_ctr;
+    const int slot = r % J.hist_cap;
+    J.S_hist[slot] = J.eta * (s1 - s2);
+    J.err_hist[slot] = e1;
+    J.flag_hist[slot] = *J.flag;
+    *J.sweep_ctr = r + 1;
+}
+
 __global__ __launch_bounds__(256) void finalize_l1_kernel(const FinalJob *__restrict__ jobs,
                                                           const int2 *__restrict__ items, int n_items)
 {
     __shared__ double red[4];
-    const int tid = threadIdx.x;
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 itm = items[it];
         const FinalJob &J = jobs[itm.x];
-        double l1 = 0.0;
-        {
-            // child products of all of this thread's elements, children in ascending order
-            double cp[kNodeEPT];
-            bool ok[kNodeEPT];
-#pragma unroll
-            for (int k = 0; k < kNodeEPT; ++k) {
-                cp[k] = 1.0;
-                ok[k] = (int64_t)itm.y + tid + 256 * k < J.n0;
-            }
-            if (J.nchild <= kRegChildren) {
-                // all children's messages loaded before the products, so the loads are in
-                // flight together; multiplied in ascending child order
-                double b[kRegChildren][kNodeEPT];
-#pragma unroll
-                for (int t = 0; t < kRegChildren; ++t)
-#pragma unroll
-                    for (int k = 0; k < kNodeEPT; ++k)
-                        b[t][k] = (t < J.nchild && ok[k]) ? gp(gp(J.root_beta)[t])[(int64_t)itm.y + tid + 256 * k]
-                                                          : 1.0;
-#pragma unroll
-                for (int t = 0; t < kRegChildren; ++t)
-#pragma unroll
-                    for (int k = 0; k < kNodeEPT; ++k)
-                        if (t < J.nchild) cp[k] *= b[t][k];
-            } else {
-                for (int t = 0; t < J.nchild; ++t) {
-                    const MOT_GLOBAL double *bt = gp(gp(J.root_beta)[t]);
-#pragma unroll
-                    for (int k = 0; k < kNodeEPT; ++k)
-                        if (ok[k]) cp[k] *= bt[(int64_t)itm.y + tid + 256 * k];
-                }
-            }
-#pragma unroll
-            for (int k = 0; k < kNodeEPT; ++k) {
-                const int64_t i = (int64_t)itm.y + tid + 256 * k;
-                if (ok[k]) l1 += fabs(gp(J.phi0)[i] * cp[k] - gp(J.mu0)[i]);
-            }
-        }
-        const double tot = block_sum(l1, red);
-        if (tid == 0) J.l1_partial[itm.y / kNodeElems] = tot;
+        const double tot = block_sum(finalize_l1(J, itm.y, threadIdx.x), red);
+        if (threadIdx.x == 0) J.l1_partial[itm.y / kNodeElems] = tot;
     }
 }
 
@@ -284,51 +336,74 @@ __global__ __launch_bounds__(256) void finalize_reduce_kernel(const FinalJob *__
     const int tid = threadIdx.x;
     for (int j = blockIdx.x; j < n_jobs; j += gridDim.x) {
         const FinalJob &J = jobs[j];
-        // every thread sums a fixed strided subset; block_sum combines them in a fixed
-        // order.  Eight strided partials are loaded before they are added (in the same
-        // order), so the loads of a thread are in flight together.
-        constexpr int U = 8;
-        double s1 = 0.0, s2 = 0.0, e1 = 0.0;
-        for (int p0 = tid; p0 < J.n_partials; p0 += U * (int)blockDim.x) {
-            double a[U], b[U];
-#pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const int p = p0 + q * (int)blockDim.x;
-                a[q] = p < J.n_partials ? J.s_partial[2 * p] : 0.0;
-                b[q] = p < J.n_partials ? J.s_partial[2 * p + 1] : 0.0;
-            }
-#pragma unroll
-            for (int q = 0; q < U; ++q)
-                if (p0 + q * (int)blockDim.x < J.n_partials) {
-                    s1 += a[q];
-                    s2 += b[q];
-                }
-        }
+        double s1, s2, e1 = 0.0;
+        finalize_partials(J, tid, s1, s2);
         for (int p = tid; p < J.n_items; p += blockDim.x) e1 += J.l1_partial[p];
         s1 = block_sum(s1, red);
         s2 = block_sum(s2, red);
         e1 = block_sum(e1, red);
-        if (tid == 0) {
-            const int r = *J.sweep_ctr;
-            const int slot = r % J.hist_cap;
-            J.S_hist[slot] = J.eta * (s1 - s2);
-            J.err_hist[slot] = e1;
-            J.flag_hist[slot] = *J.flag;
-            *J.sweep_ctr = r + 1;
-        }
+        if (tid == 0) finalize_record(J, s1, s2, e1);
         for (int s = tid; s < J.n_exp_slots; s += blockDim.x) J.exp_slots[s] = INT32_MIN;
         __syncthreads();  // red is reused by the next job
     }
 }
 
-hipError_t launch_finalize(const FinalJob *jobs, const int2 *items, int n_items, int n_jobs, hipStream_t s)
+// Both steps in one block per job, for roots of at most kFinalSmall elements (a second launch
+// costs more than the block's rounds: 500 points, 2.9 and 3.6 us in two launches, 3.8 us in one): four groups of 256 threads take an item each, then the
+// first group reduces.  Sums are formed exactly as by the two kernels.
+constexpr int kFinalGroups = 4, kFinalSmall = 4096;
+static_assert(kFinalSmall % kNodeElems == 0, "whole items");
+__global__ __launch_bounds__(256 * kFinalGroups) void finalize_small_kernel(const FinalJob *__restrict__ jobs, int n_jobs)
+{
+    __shared__ double red[kFinalGroups][4], l1p[kFinalSmall / kNodeElems], red3[3][4];
+    const int grp = threadIdx.x >> 8, tid = threadIdx.x & 255, wave = tid >> 6, lane = tid & 63;
+    for (int j = blockIdx.x; j < n_jobs; j += gridDim.x) {
+        const FinalJob &J = jobs[j];
+        for (int q0 = 0; q0 < J.n_items; q0 += kFinalGroups) {
+            const int q = q0 + grp;
+            double l1 = 0.0;
+            if (q < J.n_items) l1 = finalize_l1(J, (int64_t)q * kNodeElems, tid);
+            l1 = wave_sum(l1);
+            if (lane == 0) red[grp][wave] = l1;
+            __syncthreads();
+            if (tid == 0 && q < J.n_items) l1p[q] = group_sum(red[grp]);
+            __syncthreads();
+        }
+        if (grp == 0) {
+            double s1, s2, e1 = 0.0;
+            finalize_partials(J, tid, s1, s2);
+            for (int p = tid; p < J.n_items; p += 256) e1 += l1p[p];
+            s1 = wave_sum(s1);
+            s2 = wave_sum(s2);
+            e1 = wave_sum(e1);
+            if (lane == 0) {
+                red3[0][wave] = s1;
+                red3[1][wave] = s2;
+                red3[2][wave] = e1;
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) finalize_record(J, group_sum(red3[0]), group_sum(red3[1]), group_sum(red3[2]));
+        for (int s = threadIdx.x; s < J.n_exp_slots; s += blockDim.x) J.exp_slots[s] = INT32_MIN;
+        __syncthreads();
+    }
+}
+
+hipError_t launch_finalize(const FinalJob *jobs, const int2 *items, int n_items, int n_jobs, bool small, hipStream_t s)
 {
     if (n_items == 0 || n_jobs == 0) return hipSuccess;
+    if (small) {
+        hipLaunchKernelGGL(finalize_small_kernel, dim3(n_jobs < 8192 ? n_jobs : 8192), dim3(256 * kFinalGroups), 0, s,
+                           jobs, n_jobs);
+        return hipGetLastError();
+    }
     hipLaunchKernelGGL(finalize_l1_kernel, dim3(n_items < 8192 ? n_items : 8192), dim3(256), 0, s, jobs, items,
                        n_items);
     hipLaunchKernelGGL(finalize_reduce_kernel, dim3(n_jobs < 8192 ? n_jobs : 8192), dim3(256), 0, s, jobs, n_jobs);
     return hipGetLastError();
 }
+
+bool finalize_small(int64_t n0) { return n0 <= kFinalSmall; }
 
 // ---------------------------------------------------------------------------------------
 // Utilities

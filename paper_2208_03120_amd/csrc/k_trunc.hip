@@ -92,16 +92,6 @@ __device__ __forceinline__ int trunc_rows(int D, int w)
     return D == 1 ? 1 : (D == 2 ? span : span * span);
 }
 
-// Wavefront-local ordering of LDS accesses: the waves of a block work on different items
-// and never wait for each other; a wave's own LDS operations execute in issue order, so
-// only the compiler has to be kept from moving accesses across this point.
-__device__ __forceinline__ void wave_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 constexpr int kTruncWaves = 4;  // independent wavefronts per block, one item each
 
 __device__ __forceinline__ int wave_incl_scan(int v, int lane)

@@ -19,6 +19,7 @@ constexpr int kMaxTaps = 16;      // 2m taps per dimension, m <= 8
 constexpr int kMaxN = 512;        // FFT grid per dimension
 constexpr int kMinN = 16;
 constexpr int kMaxChildren = 64;  // children per tree node handled by the node kernels
+constexpr int kInlineChildren = 4;  // children whose pointers a node job holds itself
 // Exponent slots (one int each, raised by atomicMax from every block of a node launch) sit
 // one 128-byte line apart, so the atomics on different slots go to different L2 lines
 // instead of queueing on one.
@@ -83,6 +84,16 @@ __device__ __forceinline__ double lane_xor(double v, int h)
     return __builtin_bit_cast(double, lo | (hi << 32));
 }
 
+// Wavefront-local ordering of LDS accesses: waves that stage through LDS slices of
+// their own never wait for each other; a wave's own LDS operations execute in issue order, so
+// only the compiler has to be kept from moving accesses across this point.
+__device__ __forceinline__ void wave_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------------------
 // Device-side job descriptors.  Plain structs copied to device memory once per plan
 // (or per batch); kernels read them through an item table of (job, sub-range) pairs.
@@ -99,7 +110,8 @@ struct ProdJob {
     double *out;       // target vector, n_t entries
     int64_t ns, nt;
     double *dpart;     // direct path: partial sums, dsplit x n_t (dsplit > 1 only)
-    int32_t dsplit, pad_d;
+    int32_t dsplit;
+    int32_t dsmall;    // direct path: targets of a block of the one-launch form (0: ranges)
     double eta;
     double ctr[3];     // centre of the point cloud (mixed direct path works relative to it)
     // direct path: sorted FP64 coordinates (n x d) of sources and targets
@@ -161,6 +173,10 @@ struct NodeJob {
     int32_t *flag;              // set to 1 if an updated phi is not finite
     int32_t block0;             // first partial slot of this job
     int32_t pad;
+    // beta, down_src and down_exp entries of nodes with at most kInlineChildren children
+    const double *beta_in[kInlineChildren];
+    double *down_in[kInlineChildren];
+    int32_t *dexp_in[kInlineChildren];
 };
 
 // Sweep finalisation of one tree plan.
@@ -183,6 +199,8 @@ struct FinalJob {
 // Kernel launchers (implemented in the .hip files).
 int direct_targets_per_item(int precision);
 int direct_items_wanted(int precision);
+// targets of a block of the one-launch form (width: products that run together), 0: not taken
+int direct_small_targets(int precision, int64_t nt, int64_t ns, int width);
 // Direct products: source ranges per job (partial sums added by a second kernel when above
 // 1), from the target and source counts
 int direct_source_split(int64_t nt, int64_t ns, int precision);
@@ -194,10 +212,12 @@ hipError_t launch_trunc(int d, int precision, int R, int wide, const ProdJob *jo
                         int n_items, hipStream_t s);
 // diff != 0: mixed-precision pairs with the exponent formed in FP64 (small eta)
 hipError_t launch_direct(int d, const ProdJob *jobs_dev, const int4 *items, int n_items, const int2 *red_items,
-                         int n_red, int precision, int diff, hipStream_t s);
+                         int n_red, int precision, int diff, bool small, hipStream_t s);
 hipError_t launch_node(const NodeJob *jobs_dev, const int2 *items, int n_items, int max_children,
                        hipStream_t s);
-hipError_t launch_finalize(const FinalJob *jobs, const int2 *items, int n_items, int n_jobs, hipStream_t s);
+// small: every job's root passes finalize_small (one launch instead of two, the same sums)
+hipError_t launch_finalize(const FinalJob *jobs, const int2 *items, int n_items, int n_jobs, bool small, hipStream_t s);
+bool finalize_small(int64_t n0);
 hipError_t launch_fill_int(int32_t *p, int32_t value, int64_t count, hipStream_t s);
 hipError_t launch_fill_double(double *p, double value, int64_t count, hipStream_t s);
 hipError_t launch_vec_exp(const double *v, int64_t n, int32_t *slot, hipStream_t s);

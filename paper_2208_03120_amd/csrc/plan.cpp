@@ -182,7 +182,7 @@ int run_steps(const std::vector<Step> &steps, hipStream_t s0, const Lanes *lanes
             break;
         case ST_DIRECT:
             MOT_HIP(launch_direct(st.d, (const ProdJob *)st.jobs, (const int4 *)st.items, st.n_items,
-                                  (const int2 *)st.items2, st.n_items2, st.precision, st.diff, s));
+                                  (const int2 *)st.items2, st.n_items2, st.precision, st.diff, st.small, s));
             break;
         case ST_SPREAD:
             if (st.items2)
@@ -215,7 +215,7 @@ int run_steps(const std::vector<Step> &steps, hipStream_t s0, const Lanes *lanes
                                   st.max_patch, s));
             break;
         case ST_FINAL:
-            MOT_HIP(launch_finalize((const FinalJob *)st.jobs, (const int2 *)st.items, st.n_items, st.n_jobs, s));
+            MOT_HIP(launch_finalize((const FinalJob *)st.jobs, (const int2 *)st.items, st.n_items, st.n_jobs, st.small, s));
             break;
         case ST_FILL_INT:
             MOT_HIP(launch_fill_int(st.fill_ptr, st.fill_value, st.fill_count, s));
@@ -306,6 +306,8 @@ struct StepBuilder {
         st.items = upload(items);
         st.n_items = (int)items.size();
         st.n_jobs = (int)host_jobs.size();
+        st.small = true;
+        for (const FinalJob &F : host_jobs) st.small = st.small && finalize_small(F.n0);
         out->push_back(st);
     }
 
@@ -330,8 +332,8 @@ struct StepBuilder {
     void products(const ProdJob *jobs_dev, const std::vector<ProdJob> &host_jobs,
                   const std::vector<int> &ids)
     {
-        std::map<std::tuple<int, int, int>, std::vector<int4>> direct;  // (d, precision, diff)
-        std::map<std::tuple<int, int, int>, std::vector<int2>> direct_red;  // range sums
+        std::map<std::tuple<int, int, int, bool>, std::vector<int4>> direct;  // (d, precision, diff, small)
+        std::map<std::tuple<int, int, int, bool>, std::vector<int2>> direct_red;  // range sums
         std::map<std::tuple<int, int, int, int>, std::vector<std::pair<double, int4>>> trunc;  // (d, prec, R, wide)
         std::map<int, std::vector<int2>> spread, fold, interp;   // d
         // 3-D spreading: jobs by the points they spread from (a binned marginal's rows)
@@ -353,12 +355,13 @@ struct StepBuilder {
         for (int j : ids) {
             const ProdJob &J = host_jobs[j];
             if (J.path == MOT_DIRECT) {
-                const int tpi = direct_targets_per_item(J.precision);
-                const auto key = std::make_tuple(J.d, J.precision, J.diff);
+                const bool small = J.dsmall > 0;
+                const int tpi = small ? J.dsmall : direct_targets_per_item(J.precision);
+                const auto key = std::make_tuple(J.d, J.precision, J.diff, small);
                 auto &v = direct[key];
                 const int split = std::max(1, J.dsplit);
                 for (int64_t t = 0; t < J.nt; t += tpi)
-                    for (int r = 0; r < split; ++r) v.push_back(make_int4(j, (int)t, r, 0));
+                    for (int r = 0; r < split; ++r) v.push_back(make_int4(j, (int)t, small ? tpi : r, 0));
                 if (split > 1)
                     for (int64_t t = 0; t < J.nt; t += 256) direct_red[key].push_back(make_int2(j, (int)t));
                 continue;
@@ -478,6 +481,7 @@ struct StepBuilder {
             st.d = std::get<0>(kv.first);
             st.precision = std::get<1>(kv.first);
             st.diff = std::get<2>(kv.first);
+            st.small = std::get<3>(kv.first);
             st.jobs = jobs_dev;
             st.items = upload(kv.second);
             st.n_items = (int)kv.second.size();
@@ -734,6 +738,11 @@ int tree_build_schedule(mot_plan_s *P)
         }
         NodeJob base{};
         base.nchild = (int)ch.size();
+        for (size_t c = 0; c < ch.size() && ch.size() <= (size_t)kInlineChildren; ++c) {
+            base.beta_in[c] = bptr[c];
+            base.down_in[c] = dptr[c];
+            base.dexp_in[c] = eptr[c];
+        }
         base.n = P->marg[k].n;
         base.mu = P->marg[k].mu;
         base.phi = P->marg[k].phi;
@@ -1070,7 +1079,11 @@ int mot::make_prod_job(mot_plan_s *P, int t, int s, const double *v, int32_t *sl
     Q.src_pts = P->marg[s].pts;
     Q.tgt_pts = P->marg[t].pts;
     // a sweep's direct products may split their sources (partial buffers: create_tree)
-    Q.dsplit = P->path == MOT_DIRECT && alloc_buffers ? direct_source_split(Q.nt, Q.ns, P->precision) : 1;
+    Q.dsplit = 1;
+    if (P->path == MOT_DIRECT) {
+        Q.dsmall = direct_small_targets(P->precision, Q.nt, Q.ns, P->level_width);
+        if (Q.dsmall == 0 && alloc_buffers) Q.dsplit = direct_source_split(Q.nt, Q.ns, P->precision);
+    }
     if (P->path == MOT_TRUNC) {
         const TruncParams &T = P->TP;
         Q.src_cell_off = P->marg[s].cell_off;
@@ -1322,6 +1335,8 @@ static int create_tree(mot_plan_s *P, const std::vector<double> &pts_h, const st
     }
     for (int k = 0; k < K; ++k)
         if ((int)P->children[k].size() > kMaxChildren) return MOT_EUNSUPPORTED;
+    for (int l = 1; l <= P->depth_max; ++l)
+        P->level_width = std::max(P->level_width, (int)std::count(P->depth.begin(), P->depth.end(), l));
     MOT_TRY(setup_marginals(P, pts_h, w_h, fs, 0));
     // product jobs
     P->jobs.assign(2 * K + 1, ProdJob{});

@@ -38,6 +38,35 @@ def test_mixed_direct_tiles_and_ranges(mot, d, eta):
     plan.close()
 
 
+@pytest.mark.parametrize("eta", [0.2, 0.004])
+def test_mixed_direct_ranges(mot, eta):
+    """Products large enough for source ranges (partial sums added by a second launch) beside
+    small ones, with the bounds of the test above."""
+    sizes = [9001, 4097, 1100, 65]
+    rng = np.random.Generator(np.random.PCG64(50))
+    inst = W.make_instance(rng, 4, sizes, 2, W.TREE, eta, parent=W.star_parent(4))
+    plan = mot.Plan(inst.points, inst.weights, W.TREE, inst.parent, eta, path=mot.DIRECT, precision=mot.PREC_MIXED)
+    plan.sinkhorn(2)
+    ophi = oracle.tree_sinkhorn(inst.points, inst.weights, inst.parent, eta, 2)[0]
+    for a, b in zip(plan.scalings(), ophi):
+        np.testing.assert_allclose(a, b, rtol=5e-5)
+    plan.close()
+
+
+@pytest.mark.parametrize("sizes", [[1, 2, 3], [129, 255, 257], [511, 1025, 640], [1700, 1650, 90], [3100, 2049, 4100]])
+def test_fp64_direct_small_and_ranges(mot, sizes):
+    """FP64 products in the one-launch form with 2 to 16 targets to a block and with source
+    ranges; every term is positive, so the sums agree to a few roundings per product."""
+    rng = np.random.Generator(np.random.PCG64(sum(sizes)))
+    inst = W.make_instance(rng, 3, sizes, 3, W.TREE, 0.05, parent=W.chain_parent(3))
+    plan = mot.Plan(inst.points, inst.weights, W.TREE, inst.parent, 0.05, path=mot.DIRECT, precision=mot.PREC_FP64)
+    plan.sinkhorn(3)
+    ophi = oracle.tree_sinkhorn(inst.points, inst.weights, inst.parent, 0.05, 3)[0]
+    for a, b in zip(plan.scalings(), ophi):
+        np.testing.assert_allclose(a, b, rtol=1e-12)
+    plan.close()
+
+
 @pytest.mark.parametrize("eta", [1e-300, 1e-9, 1.0, 1e300])
 def test_fp64_direct_extreme_exponents(mot, eta):
     """Exponents far below the FP64 range (squared distances up to overflow) and at zero:
