@@ -195,6 +195,94 @@ __global__ __launch_bounds__(256 * KS) void gemm_kernel(const unsigned short *__
             }
 }
 
+// Products of few tiles (a few hundred rows): 32 x 32 tiles of C, eight wavefronts that each take a
+// contiguous eighth of K for the whole tile and are added in order through LDS.  The
+// fragments of the 16x16x32 MFMA come straight from global memory (16 rows of 64 bytes to a
+// load), two k32 steps requested before the previous two are multiplied: such a product is
+// bound by one launch and the round trips of its loads, and staging through LDS adds a barrier to
+// each (448 rows, split BF16: 8.8 us with four staged groups on 64 x 64 tiles, here 6.3 us; the
+// 32x32x16 MFMA, whose loads touch 32 rows of 32 bytes, 7.3 us).  M and N are multiples of 32, K
+// of 32.
+constexpr int kTinyT = 32, kTinyU = 2, kTinyWaves = 8;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+template <int MODE>
+__global__ __launch_bounds__(64 * kTinyWaves) void gemm_tiny_kernel(const unsigned short *__restrict__ Ah,
+                                                                    const unsigned short *__restrict__ Al, int lda,
+                                                                    const unsigned short *__restrict__ Bh,
+                                                                    const unsigned short *__restrict__ Bl, int ldb,
+                                                                    float *__restrict__ C, int ldc, int K)
+{
+    __shared__ f32x4 part[kTinyWaves][4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, li = lane & 15, lk = lane >> 4;
+    const int m0 = blockIdx.y * kTinyT, n0 = blockIdx.x * kTinyT;
+    const int s_lo = wave * (K / 32) / kTinyWaves, steps = (wave + 1) * (K / 32) / kTinyWaves - s_lo;  // k32 steps
+    const int64_t ka = 32 * (int64_t)s_lo + 8 * lk;
+    const int64_t ra = (int64_t)(m0 + li) * lda + ka, rb = (int64_t)(n0 + li) * ldb + ka;
+    constexpr int NP = MODE == 2 ? 2 : 1;  // parts of an operand
+    uint4 a[2][kTinyU][2][NP], b[2][kTinyU][2][NP];
+    auto fetch = [&](int buf, int s0) {
+#pragma unroll
+        for (int u = 0; u < kTinyU; ++u) {
+            if (s0 + u >= steps) break;
+            const int64_t k = 32 * (int64_t)(s0 + u);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {  // rows 0 .. 15 and 16 .. 31 of the tile
+                a[buf][u][h][0] = *reinterpret_cast<const uint4 *>(Ah + ra + 16 * h * (int64_t)lda + k);
+                b[buf][u][h][0] = *reinterpret_cast<const uint4 *>(Bh + rb + 16 * h * (int64_t)ldb + k);
+                if constexpr (MODE == 2) {
+                    a[buf][u][h][1] = *reinterpret_cast<const uint4 *>(Al + ra + 16 * h * (int64_t)lda + k);
+                    b[buf][u][h][1] = *reinterpret_cast<const uint4 *>(Bl + rb + 16 * h * (int64_t)ldb + k);
+                }
+            }
+        }
+    };
+    f32x4 acc[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[q] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto mult = [&](int buf, int s0) {
+#pragma unroll
+        for (int u = 0; u < kTinyU; ++u) {
+            if (s0 + u >= steps) break;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint4 *pa = a[buf][u][q >> 1], *pb = b[buf][u][q & 1];
+                if constexpr (MODE == 1) {
+                    acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, pa[0]),
+                                                                    __builtin_bit_cast(f16x8, pb[0]), acc[q], 0, 0, 0);
+                } else {
+                    acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa[0]),
+                                                                     __builtin_bit_cast(bf16x8, pb[0]), acc[q], 0, 0, 0);
+                    if constexpr (MODE == 2) {
+                        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, pa[0]), __builtin_bit_cast(bf16x8, pb[NP - 1]), acc[q], 0, 0, 0);
+                        acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            __builtin_bit_cast(bf16x8, pa[NP - 1]), __builtin_bit_cast(bf16x8, pb[0]), acc[q], 0, 0, 0);
+                    }
+                }
+            }
+        }
+    };
+    fetch(0, 0);
+    for (int s = 0; s < steps; s += 2 * kTinyU) {
+        if (s + kTinyU < steps) fetch(1, s + kTinyU);
+        mult(0, s);
+        if (s + kTinyU >= steps) break;
+        if (s + 2 * kTinyU < steps) fetch(0, s + 2 * kTinyU);
+        mult(1, s + kTinyU);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) part[wave][q][lane] = acc[q];
+    __syncthreads();
+    if (wave >= 4) return;
+    // wavefront q adds and stores quarter q of the tile: D row 4 (l / 16) + r, column l % 16
+    f32x4 t = part[0][wave][lane];
+#pragma unroll
+    for (int w = 1; w < kTinyWaves; ++w) t += part[w][wave][lane];
+    float *out = C + (int64_t)(m0 + 16 * (wave >> 1) + 4 * lk) * ldc + n0 + 16 * (wave & 1) + li;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) out[(int64_t)r * ldc] = t[r];
+}
+
 // ---------------------------------------------------------------------------------------
 // Large products, C[M x N] = A'[M x K] B[N x K]^T with M and N multiples of 256 and K of
 // 128 (the dense matrices of at least 2048 points are padded to 256).  A workgroup of 16
@@ -601,21 +689,103 @@ __global__ __launch_bounds__(256) void circle_phi_kernel(const double *__restric
     }
 }
 
-// Sweep finalisation: S^(r) from the phi-update partials, L1 error of the first marginal
-// from P_0 = phi^0 den0 (partials written by circle_phi_kernel in marginal mode).
-__global__ __launch_bounds__(256) void circle_final_kernel(const double *__restrict__ s_part, int ns,
-                                                           const double *__restrict__ e_part, int ne,
-                                                           double eta, int32_t *ctr, int hist_cap,
-                                                           double *S_hist, double *err_hist, int32_t *flag,
-                                                           int32_t *flag_hist)
+// Column sums and phi update of small marginals in one launch (circle_phi_kernel on
+// colsum_kernel's sums, summed over 64 row groups instead of chunks): a block takes 16 columns,
+// thread t the column t % 16 and every 64th row from t / 16 on, with the rows' weights formed
+// once in LDS.  400 columns: 4.4 us, 3.5 and 3.8 us in two launches; up to kColPhiRows rows, as a
+// cycle of five of 1400 points takes 2.81 ms for ten sweeps here and 2.93 ms in two launches.
+constexpr int kColPhiCols = 16, kColPhiGroups = 64, kColPhiRows = 1536;  // most rows of this form
+template <class T>
+__global__ __launch_bounds__(1024) void colsum_phi_kernel(const T *__restrict__ Yb, const T *__restrict__ Yg, int ld,
+                                                          int n1, int nk, const double *__restrict__ phi0,
+                                                          const int32_t *__restrict__ sb,
+                                                          const int32_t *__restrict__ sg,
+                                                          const double *__restrict__ mu, double *__restrict__ phi,
+                                                          double *__restrict__ s_out, int32_t *flag,
+                                                          double *__restrict__ marg_out, int marg_only)
 {
-    __shared__ double red[3][4];
+    __shared__ double red[16][kColPhiCols + 1], w[kColPhiRows];
+    constexpr int U = 8;  // rows in flight
+    const int c = threadIdx.x % kColPhiCols, g = threadIdx.x / kColPhiCols;
+    const int j = blockIdx.x * kColPhiCols + c, jc = min(j, nk - 1);
+    T yb[U], yg[U];
+    auto fetch = [&](int i0) {
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t i = min(i0 + kColPhiGroups * u, n1 - 1);
+            yb[u] = Yb[i * ld + jc];
+            yg[u] = Yg[i * ld + jc];
+        }
+    };
+    fetch(g);
+    for (int i = threadIdx.x; i < n1; i += 1024) w[i] = sb ? ldexp(phi0[i], sb[i] + sg[i]) : phi0[i];
+    const double m = mu[jc], old = phi[jc];
+    __syncthreads();
+    double acc = 0.0;
+    for (int i0 = g; i0 < n1; i0 += kColPhiGroups * U) {
+        T b[U], a[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            a[u] = yb[u];
+            b[u] = yg[u];
+        }
+        if (i0 + kColPhiGroups * U < n1) fetch(i0 + kColPhiGroups * U);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + kColPhiGroups * u < n1) acc += (double)a[u] * w[i0 + kColPhiGroups * u] * (double)b[u];
+    }
+    // the four row groups of a wavefront, then the wavefronts in order
+    acc += lane_xor(acc, 16);
+    acc += lane_xor(acc, 32);
+    if ((threadIdx.x & 63) < kColPhiCols) red[threadIdx.x >> 6][c] = acc;
+    __syncthreads();
+    if (threadIdx.x >= 64) return;
+    double s1 = 0.0;
+    if (threadIdx.x < kColPhiCols && j < nk) {
+        double den = 0.0;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) den += red[q][c];
+        if (marg_only) {
+            const double P = old * den;
+            marg_out[j] = P;
+            s1 = fabs(P - m);
+        } else {
+            const double nv = m / den;
+            if (m > 0.0) s1 = m * log(old);
+            if (!isfinite(nv)) atomicOr(flag, 1);
+            phi[j] = nv;
+        }
+    }
+#pragma unroll
+    for (int o = 8; o >= 1; o >>= 1) s1 += lane_xor(s1, o);
+    if (threadIdx.x == 0) {
+        s_out[2 * blockIdx.x] = s1;
+        s_out[2 * blockIdx.x + 1] = 0.0;
+    }
+}
+
+// Sweep finalisation: the first marginal P_0 = phi^0 den0 and its L1 error, and S^(r) from the
+// phi-update partials.  One block; its sixteen wavefronts' sums are added in order.
+__global__ __launch_bounds__(1024) void circle_final_kernel(const double *__restrict__ s_part, int ns,
+                                                            const double *__restrict__ den0, int64_t n1,
+                                                            const double *__restrict__ mu0,
+                                                            const double *__restrict__ phi0,
+                                                            double *__restrict__ marg_out, double eta, int32_t *ctr,
+                                                            int hist_cap, double *S_hist, double *err_hist,
+                                                            int32_t *flag, int32_t *flag_hist)
+{
+    __shared__ double red[3][16];
     double s1 = 0.0, s2 = 0.0, e = 0.0;
-    for (int p = threadIdx.x; p < ns; p += blockDim.x) {
+#pragma unroll 4
+    for (int64_t i = threadIdx.x; i < n1; i += 1024) {
+        const double P = phi0[i] * den0[i];
+        marg_out[i] = P;
+        e += fabs(P - mu0[i]);
+    }
+    for (int p = threadIdx.x; p < ns; p += 1024) {
         s1 += s_part[2 * p];
         s2 += s_part[2 * p + 1];
     }
-    for (int p = threadIdx.x; p < ne; p += blockDim.x) e += e_part[2 * p];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {
         s1 += lane_xor(s1, o);
@@ -629,9 +799,12 @@ __global__ __launch_bounds__(256) void circle_final_kernel(const double *__restr
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        const double S1 = (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]);
-        const double S2 = (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]);
-        const double E = (red[2][0] + red[2][1]) + (red[2][2] + red[2][3]);
+        double S1 = 0.0, S2 = 0.0, E = 0.0;
+        for (int w = 0; w < 16; ++w) {
+            S1 += red[0][w];
+            S2 += red[1][w];
+            E += red[2][w];
+        }
         const int r = *ctr, slot = r % hist_cap;
         S_hist[slot] = eta * (S1 - S2);
         err_hist[slot] = E;
@@ -708,7 +881,6 @@ struct CircleState {
     double *s_part = nullptr;      // phi-update partials
     std::vector<int> s_slot;       // first partial slot of marginal k's phi update
     int ns = 0;
-    double *e_part = nullptr;      // first-marginal L1 partials
     double *m_part = nullptr;      // scratch partials of marginal-only evaluations
     // NFFT path: per-row product jobs for each product position
     double *src = nullptr;
@@ -744,8 +916,11 @@ static bool gemm_big(int Mp, int Np, int Kp)
            (Mp / kBigT) * (Np / kBigT) >= kBigMinTiles;
 }
 
-// K split of gemm_kernel by the product's count of 64 x 64 tiles: 1 from kSplitK1Tiles
-// tiles on, 2 from kSplitK2Tiles, else 4.
+// Kernel of the other products by their count of 64 x 64 tiles: gemm_kernel from kSplitK1Tiles
+// tiles on, its form that splits K over two groups from kSplitK2Tiles, gemm_tiny_kernel below.  The
+// lower line: products of 1024 rows (256 tiles) of a split BF16 cycle of five took 1.87 ms with
+// two groups for ten sweeps and 3.08 ms as gemm_tiny_kernel, of 704 (121 tiles) 1.63 ms here and
+// 1.64 ms with four staged groups.
 constexpr int kSplitK1Tiles = 512, kSplitK2Tiles = 128;
 
 template <int MODE>
@@ -753,9 +928,7 @@ static void launch_gemm_small(int ks, dim3 grid, const unsigned short *Ah, const
                               const unsigned short *Bh, const unsigned short *Bl, int ldb, float *Cm, int ldc, int Kp,
                               hipStream_t s)
 {
-    if (ks == 4)
-        hipLaunchKernelGGL((gemm_kernel<MODE, 4>), grid, dim3(1024), 0, s, Ah, Al, lda, Bh, Bl, ldb, Cm, ldc, Kp);
-    else if (ks == 2)
+    if (ks == 2)
         hipLaunchKernelGGL((gemm_kernel<MODE, 2>), grid, dim3(512), 0, s, Ah, Al, lda, Bh, Bl, ldb, Cm, ldc, Kp);
     else
         hipLaunchKernelGGL((gemm_kernel<MODE, 1>), grid, dim3(256), 0, s, Ah, Al, lda, Bh, Bl, ldb, Cm, ldc, Kp);
@@ -789,9 +962,19 @@ static hipError_t launch_gemm(const CircleState &C, const float *A, int lda, con
             hipLaunchKernelGGL(gemm_big_kernel<0>, grid, block, 0, s, Ah, lda, Bh, ldb, Cm, ldc, Kp, tm, tn);
         return hipGetLastError();
     }
-    const dim3 grid(Np / kSmallT, Mp / kSmallT);
     const int tiles = (Np / kSmallT) * (Mp / kSmallT);
-    const int ks = tiles >= kSplitK1Tiles ? 1 : (tiles >= kSplitK2Tiles ? 2 : 4);
+    if (tiles < kSplitK2Tiles) {
+        const dim3 grid(Np / kTinyT, Mp / kTinyT), block(64 * kTinyWaves);
+        if (C.mode == 1)
+            hipLaunchKernelGGL(gemm_tiny_kernel<1>, grid, block, 0, s, Ah, Al, lda, Bh, Bl, ldb, Cm, ldc, Kp);
+        else if (C.mode == 2)
+            hipLaunchKernelGGL(gemm_tiny_kernel<2>, grid, block, 0, s, Ah, Al, lda, Bh, Bl, ldb, Cm, ldc, Kp);
+        else
+            hipLaunchKernelGGL(gemm_tiny_kernel<0>, grid, block, 0, s, Ah, Al, lda, Bh, Bl, ldb, Cm, ldc, Kp);
+        return hipGetLastError();
+    }
+    const dim3 grid(Np / kSmallT, Mp / kSmallT);
+    const int ks = tiles >= kSplitK1Tiles ? 1 : 2;
     if (C.mode == 1)
         launch_gemm_small<1>(ks, grid, Ah, Al, lda, Bh, Bl, ldb, Cm, ldc, Kp, s);
     else if (C.mode == 2)
@@ -836,6 +1019,23 @@ static int colsum_phi(mot_plan_s *P, CircleState &C, int k, bool marg_only)
 {
     hipStream_t st = P->stream;
     const int64_t n1 = C.n1, nk = P->n[k];
+    double *sout = marg_only ? C.m_part : C.s_part + 2 * C.s_slot[k];
+    if (n1 <= kColPhiRows && nk <= kColPhiRows) {
+        const dim3 g((unsigned)((nk + kColPhiCols - 1) / kColPhiCols));
+        if (C.nfft)
+            hipLaunchKernelGGL(colsum_phi_kernel<double>, g, dim3(1024), 0, st, (const double *)C.Yb[k],
+                               (const double *)Ymat(C, 1, k), C.ld[k], (int)n1, (int)nk,
+                               (const double *)P->marg[0].phi, (const int32_t *)nullptr, (const int32_t *)nullptr,
+                               (const double *)P->marg[k].mu, P->marg[k].phi, sout, P->flag, P->marg[k].marg,
+                               marg_only ? 1 : 0);
+        else
+            hipLaunchKernelGGL(colsum_phi_kernel<float>, g, dim3(1024), 0, st, (const float *)C.Yb[k],
+                               (const float *)Ymat(C, 1, k), C.ld[k], (int)n1, (int)nk,
+                               (const double *)P->marg[0].phi, (const int32_t *)Yscale(C, 0, k),
+                               (const int32_t *)Yscale(C, 1, k), (const double *)P->marg[k].mu, P->marg[k].phi, sout,
+                               P->flag, P->marg[k].marg, marg_only ? 1 : 0);
+        return hipGetLastError() == hipSuccess ? MOT_OK : MOT_EDEVICE;
+    }
     const int rows = colsum_rows(n1, nk);
     const int chunks = (int)((n1 + rows - 1) / rows);
     const dim3 g((unsigned)((nk + 255) / 256), (unsigned)chunks);
@@ -850,7 +1050,6 @@ static int colsum_phi(mot_plan_s *P, CircleState &C, int k, bool marg_only)
                            (const int32_t *)Yscale(C, 1, k), rows, C.part);
     MOT_HIP(hipGetLastError());
     const unsigned blocks = (unsigned)((nk + 255) / 256);
-    double *sout = marg_only ? C.m_part : C.s_part + 2 * C.s_slot[k];
     hipLaunchKernelGGL(circle_phi_kernel, dim3(blocks), dim3(256), 0, st, (const double *)C.part, chunks, nk,
                        (const double *)P->marg[k].mu, P->marg[k].phi, 0, sout, P->flag, P->marg[k].marg,
                        marg_only ? 1 : 0);
@@ -1001,12 +1200,12 @@ int circle_create(mot_plan_s *P, const std::vector<double> &pts_h, const std::ve
     int slot = 0;
     for (int k = 0; k < K; ++k) {
         C.s_slot[k] = slot;
-        slot += (int)((P->n[k] + 255) / 256);
+        const bool one = k > 0 && C.n1 <= kColPhiRows && P->n[k] <= kColPhiRows;  // colsum_phi_kernel
+        slot += (int)(one ? (P->n[k] + kColPhiCols - 1) / kColPhiCols : (P->n[k] + 255) / 256);
     }
     C.ns = slot;
     MOT_TRY(P->arena.get_n(2 * (size_t)slot, &C.s_part));
-    MOT_TRY(P->arena.get_n(2 * (size_t)((C.n1 + 255) / 256), &C.e_part));
-    MOT_TRY(P->arena.get_n(2 * (size_t)((nmax + 255) / 256), &C.m_part));
+    MOT_TRY(P->arena.get_n(2 * (size_t)((nmax + kColPhiCols - 1) / kColPhiCols), &C.m_part));
     if (C.nfft) {
         MOT_TRY(P->arena.get_n((size_t)C.n1 * nmax, &C.src));
         MOT_TRY(P->arena.get_n((size_t)C.n1, &C.rowexp));
@@ -1053,11 +1252,9 @@ int circle_run_sweeps(mot_plan_s *P, int sweeps)
         }
         MOT_TRY(circle_up(P, C));
         // first marginal after the sweep, P_0 = phi^0 den0, and S^(r)
-        hipLaunchKernelGGL(circle_phi_kernel, dim3((unsigned)((C.n1 + 255) / 256)), dim3(256), 0, st,
-                           (const double *)C.den0, 0, C.n1, (const double *)P->marg[0].mu, P->marg[0].phi, 1,
-                           C.e_part, P->flag, P->marg[0].marg, 1);
-        hipLaunchKernelGGL(circle_final_kernel, dim3(1), dim3(256), 0, st, (const double *)C.s_part, C.ns,
-                           (const double *)C.e_part, (int)((C.n1 + 255) / 256), P->eta, P->sweep_ctr, P->hist_cap,
+        hipLaunchKernelGGL(circle_final_kernel, dim3(1), dim3(1024), 0, st, (const double *)C.s_part, C.ns,
+                           (const double *)C.den0, C.n1, (const double *)P->marg[0].mu,
+                           (const double *)P->marg[0].phi, P->marg[0].marg, P->eta, P->sweep_ctr, P->hist_cap,
                            P->S_hist, P->err_hist, P->flag, P->flag_hist);
         MOT_HIP(hipGetLastError());
     }
