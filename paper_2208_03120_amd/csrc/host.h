@@ -241,6 +241,7 @@ struct mot_plan_s {
     float2 *twiddle = nullptr;
     // statistics
     int32_t *sweep_ctr = nullptr, *flag = nullptr, *flag_hist = nullptr;
+    mot::SweepStatus *status = nullptr;
     double *S_hist = nullptr, *err_hist = nullptr;
     double *s_partial = nullptr, *l1_partial = nullptr;
     int hist_cap = 0;

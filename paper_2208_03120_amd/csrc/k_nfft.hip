@@ -72,51 +72,73 @@ __global__ void make_keys_kernel(int64_t npts, int64_t npad, const int32_t *__re
     keys[i] = i < npts ? (hi << 32) | (uint64_t)i : ~0ull;
 }
 
-// One global compare-exchange step (k, j) of the bitonic network.
-__global__ void bitonic_global_kernel(uint64_t *keys, int64_t npad, int64_t k, int64_t j)
+// The bitonic network over npad keys: blocks of kSortBlock keys in LDS, wider strides in global
+// memory, two to a launch.  A sort of this size is bound by its launches and barriers (npad = 32768:
+// 17 launches, 22 with one stride to a launch).  Wider blocks save launches but leave most of the
+// chip idle in the long chain of strides inside a block: creating a tree plan of 46000 points and
+// sweeping it took 10.1 ms with 4096 or 2048 keys, 9.7 with 1024.
+constexpr int kSortBlock = 1024, kSortThreads = 512;
+
+__device__ __forceinline__ void order_keys(uint64_t &a, uint64_t &b, bool up)
 {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= npad) return;
-    int64_t p = i ^ j;
-    if (p > i) {
-        uint64_t a = keys[i], b = keys[p];
-        bool up = (i & k) == 0;
-        if ((a > b) == up) {
-            keys[i] = b;
-            keys[p] = a;
-        }
+    const uint64_t x = a, y = b;
+    const bool swap = (x > y) == up;
+    a = swap ? y : x;
+    b = swap ? x : y;
+}
+
+// The strides j and, with TWO, j / 2 of stage k in global memory: a thread holds the two or four keys
+// that they join.
+template <bool TWO>
+__global__ __launch_bounds__(256) void bitonic_global_kernel(uint64_t *keys, int64_t threads, int64_t k, int64_t j)
+{
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= threads) return;
+    const int64_t s = TWO ? j / 2 : j;                            // the smaller stride
+    const int64_t i = (q & ~(s - 1)) * (TWO ? 4 : 2) + (q & (s - 1));  // s is a power of two
+    const bool up = (i & k) == 0;
+    if constexpr (TWO) {
+        uint64_t a = keys[i], b = keys[i + s], c = keys[i + 2 * s], d = keys[i + 3 * s];
+        order_keys(a, c, up);
+        order_keys(b, d, up);
+        order_keys(a, b, up);
+        order_keys(c, d, up);
+        keys[i] = a;
+        keys[i + s] = b;
+        keys[i + 2 * s] = c;
+        keys[i + 3 * s] = d;
+    } else {
+        uint64_t a = keys[i], b = keys[i + s];
+        order_keys(a, b, up);
+        keys[i] = a;
+        keys[i + s] = b;
     }
 }
 
-// All steps with j < 1024 of stage k (or the full sort of 1024-element blocks when
-// k_full != 0) inside LDS.
-__global__ __launch_bounds__(512) void bitonic_local_kernel(uint64_t *keys, int64_t npad,
-                                                            int64_t k, int k_full)
+// Stages k_lo .. k_hi inside LDS, from stride min(k, nb) / 2 on; a block holds nb <= kSortBlock keys.
+// A wavefront's pairs of strides up to 64 lie in its own 128 keys, so those strides need no
+// barrier between them.
+__global__ __launch_bounds__(kSortThreads) void bitonic_local_kernel(uint64_t *keys, int nb, int64_t k_lo, int64_t k_hi)
 {
-    __shared__ uint64_t sk[1024];
-    int64_t base = (int64_t)blockIdx.x * 1024;
-    for (int t = threadIdx.x; t < 1024; t += blockDim.x) sk[t] = keys[base + t];
+    __shared__ uint64_t sk[kSortBlock];
+    const int64_t base = (int64_t)blockIdx.x * nb;
+    for (int t = threadIdx.x; t < nb; t += kSortThreads) sk[t] = keys[base + t];
     __syncthreads();
-    int64_t kk0 = k_full ? 2 : k, kk1 = k_full ? 1024 : k;
-    for (int64_t kk = kk0; kk <= kk1; kk <<= 1) {
-        int64_t j0 = k_full ? kk / 2 : 512;
-        for (int64_t j = j0; j > 0; j >>= 1) {
-            for (int t = threadIdx.x; t < 1024; t += blockDim.x) {
-                int p = t ^ (int)j;
-                if (p > t) {
-                    int64_t gi = base + t;
-                    bool up = (gi & kk) == 0;
-                    uint64_t a = sk[t], b = sk[p];
-                    if ((a > b) == up) {
-                        sk[t] = b;
-                        sk[p] = a;
-                    }
-                }
+    for (int64_t k = k_lo; k <= k_hi; k <<= 1) {
+        for (int j = (int)(k < nb ? k : nb) / 2; j > 0; j >>= 1) {
+            for (int q = threadIdx.x; q < nb / 2; q += kSortThreads) {
+                const int i = 2 * (q & ~(j - 1)) + (q & (j - 1));
+                order_keys(sk[i], sk[i + j], ((base + i) & k) == 0);
             }
-            __syncthreads();
+            // the next stride: j / 2, or the next stage's widest
+            if (j > 64 || (j == 1 && k >= 128 && k < k_hi))
+                __syncthreads();
+            else
+                wave_sync();
         }
     }
-    for (int t = threadIdx.x; t < 1024; t += blockDim.x) keys[base + t] = sk[t];
+    __syncthreads();
+    for (int t = threadIdx.x; t < nb; t += kSortThreads) keys[base + t] = sk[t];
 }
 
 // perm[i] = index of the i-th sorted key (i < npts); tile_off[t] = first sorted position
@@ -208,14 +230,22 @@ hipError_t stable_tile_sort(int64_t npts, const int32_t *tile, int64_t ntiles, i
     int blocks = (int)((npad + 255) / 256);
     hipLaunchKernelGGL(make_keys_kernel, dim3(blocks), dim3(256), 0, st, npts, npad, tile, cell, d, sub_dim,
                        T, keys);
-    int lblocks = (int)(npad / 1024);
-    hipLaunchKernelGGL(bitonic_local_kernel, dim3(lblocks), dim3(512), 0, st, keys, npad,
-                       (int64_t)0, 1);
-    for (int64_t k = 2048; k <= npad; k <<= 1) {
-        for (int64_t j = k / 2; j >= 1024; j >>= 1)
-            hipLaunchKernelGGL(bitonic_global_kernel, dim3(blocks), dim3(256), 0, st, keys, npad,
-                               k, j);
-        hipLaunchKernelGGL(bitonic_local_kernel, dim3(lblocks), dim3(512), 0, st, keys, npad, k, 0);
+    const int nb = (int)std::min<int64_t>(npad, kSortBlock);
+    const dim3 lblocks((unsigned)(npad / nb));
+    hipLaunchKernelGGL(bitonic_local_kernel, lblocks, dim3(kSortThreads), 0, st, keys, nb, (int64_t)2, (int64_t)nb);
+    for (int64_t k = 2 * (int64_t)nb; k <= npad; k <<= 1) {
+        for (int64_t j = k / 2; j >= nb;) {
+            if (j / 2 >= nb) {
+                hipLaunchKernelGGL(bitonic_global_kernel<true>, dim3((unsigned)(npad / 4 / 256)), dim3(256), 0, st, keys,
+                                   npad / 4, k, j);
+                j /= 4;
+            } else {
+                hipLaunchKernelGGL(bitonic_global_kernel<false>, dim3((unsigned)(npad / 2 / 256)), dim3(256), 0, st,
+                                   keys, npad / 2, k, j);
+                j /= 2;
+            }
+        }
+        hipLaunchKernelGGL(bitonic_local_kernel, lblocks, dim3(kSortThreads), 0, st, keys, nb, k, k);
     }
     const int64_t nthr = std::max<int64_t>(npts, ntiles + 1);
     int pblocks = (int)((nthr + 255) / 256);

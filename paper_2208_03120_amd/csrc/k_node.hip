@@ -496,6 +496,23 @@ hipError_t launch_tree_pair(const double *u, const double *xa, const int32_t *pe
     return hipGetLastError();
 }
 
+// What a caller of sweeps is told after them, gathered for one copy: the last two values of S, the
+// last error, the sweeps of the plan so far and the flag (a copy of a few bytes to pageable memory
+// costs the host about 12 us; five of them were read one by one).
+__global__ void sweep_status_kernel(const int32_t *ctr, const int32_t *flag, int hist_cap, const double *S_hist,
+                                    const double *err_hist, SweepStatus *out)
+{
+    const int r = *ctr, idx = (r - 1 + hist_cap) % hist_cap, idxp = (r - 2 + hist_cap) % hist_cap;
+    *out = {S_hist[idxp], S_hist[idx], err_hist[idx], r, *flag};
+}
+
+hipError_t launch_sweep_status(const int32_t *ctr, const int32_t *flag, int hist_cap, const double *S_hist,
+                               const double *err_hist, SweepStatus *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(sweep_status_kernel, dim3(1), dim3(1), 0, s, ctr, flag, hist_cap, S_hist, err_hist, out);
+    return hipGetLastError();
+}
+
 // max exponent of a vector into a slot (for products requested outside a sweep)
 __global__ void vec_exp_kernel(const double *__restrict__ v, int64_t n, int32_t *slot)
 {

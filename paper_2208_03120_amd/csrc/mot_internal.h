@@ -219,6 +219,12 @@ hipError_t launch_node(const NodeJob *jobs_dev, const int2 *items, int n_items, 
 hipError_t launch_finalize(const FinalJob *jobs, const int2 *items, int n_items, int n_jobs, bool small, hipStream_t s);
 bool finalize_small(int64_t n0);
 hipError_t launch_fill_int(int32_t *p, int32_t value, int64_t count, hipStream_t s);
+struct SweepStatus {
+    double S_before, S_last, err;
+    int32_t sweeps, flag;
+};
+hipError_t launch_sweep_status(const int32_t *ctr, const int32_t *flag, int hist_cap, const double *S_hist,
+                               const double *err_hist, SweepStatus *out, hipStream_t s);
 hipError_t launch_fill_double(double *p, double value, int64_t count, hipStream_t s);
 hipError_t launch_vec_exp(const double *v, int64_t n, int32_t *slot, hipStream_t s);
 // Tree edge pair marginal: out[perm_a[i] * nb + perm_b[j]] = u_i exp(-|x_i - y_j|^2 / eta) w_j

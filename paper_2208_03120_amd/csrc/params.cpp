@@ -8,6 +8,7 @@
 // its derivatives 1..p vanish at tau (this reproduces the worked example of Fig. 1).
 #include <algorithm>
 #include <cmath>
+#include <map>
 #include <mutex>
 
 #include "host.h"
@@ -257,21 +258,92 @@ int build_box(int d, const Extent &ext, NfftParams *P)
 //   exp(-2 pi m sqrt(1 - 1/sigma)).
 // Cost model: spreading and interpolation touch (2m)^d cells per point; the pruned FFT
 // costs about box^d log n.  The cheapest candidate meeting the target is chosen.
-static double fourier_err_1d(int M, double eta, double tau, double eps_B, int p, double diag)
-{
-    std::vector<double> kh;
-    kappa_hat_even(1, M, eta, tau, eps_B, p, kh);
-    double worst = 0.0;
-    const int R = 96;
-    for (int i = 0; i <= R; ++i) {
-        const double r = diag * i / R;
-        double s = kh[0];
-        for (int k = 1; k < M; ++k) s += 2.0 * kh[k] * std::cos(M_PI * k * r / tau);
-        s += kh[M] * std::cos(M_PI * M * r / tau);  // the unpaired -M term (real part)
-        worst = std::max(worst, std::fabs(s - std::exp(-r * r / eta)));
+//
+// FourierErr evaluates the Fourier part for the candidates of one resolution.  The cosines, which
+// are nearly all of its work, depend on M alone (the transform of the samples) or on tau alone (the
+// series at the test points) and are kept for the other candidates; a candidate is given up at
+// the first block of test points whose error exceeds the limit.  Every sum keeps its order.
+class FourierErr {
+  public:
+    FourierErr(int d, double eta, double diag) : d_(d), eta_(eta)
+    {
+        for (int i = 0; i < kBlocks * kBlock; ++i) {
+            r_[i] = diag * std::min(i, kPoints - 1) / (kPoints - 1);
+            want_[i] = std::exp(-r_[i] * r_[i] / eta);
+        }
     }
-    return worst;
-}
+
+    // The regularised kernel of the candidates that follow.
+    void kernel(double tau, double eps_B, int p)
+    {
+        tau_ = tau;
+        eps_B_ = eps_B;
+        kappa_B_shifted(eta_, tau, eps_B, p, q_);
+    }
+
+    // d times the largest error of the series of M coefficients, or any value above limit if that is.
+    double error(int M, double limit)
+    {
+        coefficients(M);
+        std::vector<std::vector<double>> &at = series_[tau_];
+        at.resize(kBlocks);
+        double worst = 0.0;
+        for (int b = 0; b < kBlocks; ++b) {
+            std::vector<double> &c = at[b];  // cos(pi k r / tau) of a block's points, k = 1 ..
+            const double *r = r_ + b * kBlock;
+            for (int k = (int)(c.size() / kBlock) + 1; k <= M; ++k)
+                for (int i = 0; i < kBlock; ++i) c.push_back(std::cos(M_PI * k * r[i] / tau_));
+            double s[kBlock];
+            for (int i = 0; i < kBlock; ++i) s[i] = khat_[0];
+            for (int k = 1; k < M; ++k) {
+                const double h = 2.0 * khat_[k], *ck = &c[(size_t)(k - 1) * kBlock];
+                for (int i = 0; i < kBlock; ++i) s[i] += h * ck[i];
+            }
+            const double *cM = &c[(size_t)(M - 1) * kBlock];
+            for (int i = 0; i < kBlock; ++i) {
+                s[i] += khat_[M] * cM[i];  // the unpaired -M term (real part)
+                worst = std::max(worst, std::fabs(s[i] - want_[b * kBlock + i]));
+            }
+            if (d_ * worst > limit) break;
+        }
+        return d_ * worst;
+    }
+
+  private:
+    static constexpr int kPoints = 97, kBlock = 16, kBlocks = (kPoints + kBlock - 1) / kBlock;
+
+    // khat_: kappa_hat_even in one dimension
+    void coefficients(int M)
+    {
+        const int S = 2 * M, H = M + 1;
+        std::vector<double> &C = dft_[M];  // [j][k] cos(pi k (j - M) / M), j = M .. 2 M
+        if (C.empty()) {
+            C.resize((size_t)H * H);
+            for (int j = M; j <= S; ++j)
+                for (int k = 0; k < H; ++k) C[(size_t)(j - M) * H + k] = std::cos(M_PI * k * (double)(j - M) / M);
+        }
+        std::vector<double> v(H);
+        for (int j = M; j <= S; ++j) {
+            const double x = tau_ * (double)(j - M) / M;
+            v[j - M] = kappa_R(x, eta_, tau_, eps_B_, q_);
+        }
+        khat_.assign(H, 0.0);
+        for (int j = 0; j < S; ++j) {
+            const int e = std::abs(j - M);
+            const double *c = &C[(size_t)e * H], x = v[e];
+            for (int k = 0; k < H; ++k) khat_[k] += c[k] * x;
+        }
+        const double norm = std::pow(2.0 * M, -1);
+        for (double &h : khat_) h *= norm;
+    }
+
+    int d_;
+    double eta_, tau_ = 0.0, eps_B_ = 0.0;
+    double r_[kBlocks * kBlock], want_[kBlocks * kBlock];
+    std::vector<double> q_, khat_;
+    std::map<int, std::vector<double>> dft_;
+    std::map<double, std::vector<std::vector<double>>> series_;
+};
 
 static double kb_err(int m, double sigma)
 {
@@ -350,15 +422,19 @@ int resolve_params(int d, double eta, const Extent &ext, const mot_fastsum_param
     else
         for (int M : {4, 6, 8, 10, 12, 14, 16, 20, 24, 28, 32, 40, 48, 56, 64, 80, 96, 112, 127})
             M_list.push_back(M);
+    FourierErr err_lo(d, eta, ext.diag), err_hi(d, eta_hi > eta ? eta_hi : eta, ext.diag);
     for (int p : p_list)
         for (double eb : eb_list) {
             double tau = F.tau > 0 ? F.tau : (diag + eb) * (1.0 + 1e-9);
             if (tau <= eb + ext.diag) return MOT_EDOMAIN;
             int Mfound = -1;
             double ferr = 0.0;
+            const double limit = F.M > 0 ? INFINITY : 0.5 * target;
+            err_lo.kernel(tau, eb, p);
+            if (eta_hi > eta) err_hi.kernel(tau, eb, p);
             for (int M : M_list) {
-                ferr = d * fourier_err_1d(M, eta, tau, eb, p, ext.diag);
-                if (eta_hi > eta) ferr = std::max(ferr, d * fourier_err_1d(M, eta_hi, tau, eb, p, ext.diag));
+                ferr = err_lo.error(M, limit);
+                if (eta_hi > eta && !(ferr > limit)) ferr = std::max(ferr, err_hi.error(M, limit));
                 if (F.M > 0 || ferr <= 0.5 * target) {
                     Mfound = M;
                     break;

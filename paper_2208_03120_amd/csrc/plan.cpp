@@ -264,21 +264,69 @@ static void xcd_group(std::vector<T> &v, int group)
     v.swap(out);
 }
 
+// Tables of a plan on their way to the device.  An allocation and a copy from pageable memory cost
+// the host about 30 us, whatever their size, and a plan has some sixty small tables: small ones
+// share blocks of device memory (of kFirst bytes, then twice the last up to kMost) that go in
+// one copy each.  flush() before their first use.
+struct Uploads {
+    static constexpr size_t kFirst = (size_t)4 << 10, kMost = (size_t)64 << 10;
+    struct Block {
+        char *dev;
+        std::vector<char> host;  // its bytes so far
+        size_t size;
+    };
+    std::vector<Block> blocks;
+
+    template <class T>
+    int add(Arena &arena, const std::vector<T> &v, T **dev)
+    {
+        const size_t bytes = v.size() * sizeof(T), taken = (bytes + 255) / 256 * 256 + 256;  // as Arena::get_n pads
+        if (taken > kMost / 4) {
+            MOT_TRY(arena.get_n(v.size(), dev));
+            MOT_HIP(hipMemcpy(*dev, v.data(), bytes, hipMemcpyHostToDevice));
+            return MOT_OK;
+        }
+        if (blocks.empty() || blocks.back().host.size() + taken > blocks.back().size) {
+            size_t size = blocks.empty() ? kFirst : std::min(kMost, 2 * blocks.back().size);
+            while (size < taken) size *= 2;
+            char *d = nullptr;
+            MOT_TRY(arena.get(size, (void **)&d));
+            blocks.push_back({d, {}, size});
+        }
+        Block &b = blocks.back();
+        const size_t at = b.host.size();
+        b.host.resize(at + taken);
+        memcpy(b.host.data() + at, v.data(), bytes);
+        *dev = (T *)(b.dev + at);
+        return MOT_OK;
+    }
+
+    int flush()
+    {
+        for (const Block &b : blocks) MOT_HIP(hipMemcpy(b.dev, b.host.data(), b.host.size(), hipMemcpyHostToDevice));
+        blocks.clear();
+        return MOT_OK;
+    }
+};
+
 struct StepBuilder {
     Arena *arena;
     std::vector<Step> *out;
     int rc = MOT_OK;
+    Uploads up;
 
     template <class T>
     const T *upload(const std::vector<T> &v)
     {
         if (rc < 0 || v.empty()) return nullptr;
         T *d = nullptr;
-        rc = arena->get_n<T>(v.size(), &d);
-        if (rc < 0) return nullptr;
-        if (hipMemcpy(d, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice) != hipSuccess)
-            rc = MOT_EDEVICE;
-        return d;
+        rc = up.add(*arena, v, &d);
+        return rc < 0 ? nullptr : d;
+    }
+
+    int finish()  // the tables on the device
+    {
+        return rc < 0 ? rc : up.flush();
     }
 
     void node(const NodeJob *jobs_dev, const std::vector<NodeJob> &host_jobs,
@@ -673,7 +721,7 @@ int product_steps(Arena &arena, const ProdJob *jobs_dev, const std::vector<ProdJ
 {
     StepBuilder B{&arena, &out};
     B.products(jobs_dev, jobs_host, ids);
-    return B.rc;
+    return B.finish();
 }
 
 // ---------------------------------------------------------------------------------------
@@ -714,6 +762,7 @@ int tree_build_schedule(mot_plan_s *P)
     }
     T->njobs.resize(4 * K);
     int slot = 0;
+    Uploads up;
     // device pointer arrays per node: child betas, child down sources, child exp slots
     for (int k = 0; k < K; ++k) {
         const auto &ch = P->children[k];
@@ -729,12 +778,9 @@ int tree_build_schedule(mot_plan_s *P)
         double **ddev = nullptr;
         int32_t **edev = nullptr;
         if (!ch.empty()) {
-            MOT_TRY(P->arena.get_n(ch.size(), &bdev));
-            MOT_TRY(P->arena.get_n(ch.size(), &ddev));
-            MOT_TRY(P->arena.get_n(ch.size(), &edev));
-            MOT_HIP(hipMemcpy(bdev, bptr.data(), ch.size() * sizeof(void *), hipMemcpyHostToDevice));
-            MOT_HIP(hipMemcpy(ddev, dptr.data(), ch.size() * sizeof(void *), hipMemcpyHostToDevice));
-            MOT_HIP(hipMemcpy(edev, eptr.data(), ch.size() * sizeof(void *), hipMemcpyHostToDevice));
+            MOT_TRY(up.add(P->arena, bptr, &bdev));
+            MOT_TRY(up.add(P->arena, dptr, &ddev));
+            MOT_TRY(up.add(P->arena, eptr, &edev));
         }
         NodeJob base{};
         base.nchild = (int)ch.size();
@@ -807,12 +853,9 @@ int tree_build_schedule(mot_plan_s *P)
         F.eta = P->eta;
         T->fjob.push_back(F);
     }
-    MOT_TRY(P->arena.get_n(T->njobs.size(), &T->njobs_dev));
-    MOT_HIP(hipMemcpy(T->njobs_dev, T->njobs.data(), T->njobs.size() * sizeof(NodeJob),
-                      hipMemcpyHostToDevice));
-    MOT_TRY(P->arena.get_n(1, &T->fjob_dev));
-    MOT_HIP(hipMemcpy(T->fjob_dev, T->fjob.data(), sizeof(FinalJob), hipMemcpyHostToDevice));
-    return MOT_OK;
+    MOT_TRY(up.add(P->arena, T->njobs, &T->njobs_dev));
+    MOT_TRY(up.add(P->arena, T->fjob, &T->fjob_dev));
+    return up.flush();
 }
 
 // Steps of one sweep / the initial upward pass / the marginal pass for a set of tree
@@ -915,7 +958,7 @@ int tree_steps(const std::vector<TreeRef> &refs, const std::vector<ProdJob> &pj,
         B.node(nj_dev, nj, nodes_at(l, 3, false, false));
         if (l < maxD) B.products(pj_dev, pj, prods_at(l + 1, 0));
     }
-    return B.rc;
+    return B.finish();
 }
 
 }  // namespace mot
@@ -963,15 +1006,24 @@ static int validate_common(int K, int d, const int64_t *n, double eta, const std
 static Extent extent_of(int d, const std::vector<double> &pts, int64_t total)
 {
     Extent E;
-    for (int c = 0; c < d; ++c) {
-        E.lo[c] = INFINITY;
-        E.hi[c] = -INFINITY;
-    }
-    for (int64_t i = 0; i < total; ++i)
-        for (int c = 0; c < d; ++c) {
-            E.lo[c] = std::min(E.lo[c], pts[i * d + c]);
-            E.hi[c] = std::max(E.hi[c], pts[i * d + c]);
+    for (int c = 0; c < d; ++c) {  // four chains of comparisons a coordinate
+        double lo[4], hi[4];
+        std::fill(lo, lo + 4, INFINITY);
+        std::fill(hi, hi + 4, -INFINITY);
+        const double *x = pts.data() + c;
+        int64_t i = 0;
+        for (; i + 4 <= total; i += 4)
+            for (int u = 0; u < 4; ++u) {
+                lo[u] = std::min(lo[u], x[(i + u) * d]);
+                hi[u] = std::max(hi[u], x[(i + u) * d]);
+            }
+        for (; i < total; ++i) {
+            lo[0] = std::min(lo[0], x[i * d]);
+            hi[0] = std::max(hi[0], x[i * d]);
         }
+        E.lo[c] = std::min(std::min(lo[0], lo[1]), std::min(lo[2], lo[3]));
+        E.hi[c] = std::max(std::max(hi[0], hi[1]), std::max(hi[2], hi[3]));
+    }
     double s2 = 0.0;
     for (int c = 0; c < d; ++c) {
         E.ctr[c] = 0.5 * (E.lo[c] + E.hi[c]);
@@ -983,8 +1035,9 @@ static Extent extent_of(int d, const std::vector<double> &pts, int64_t total)
     return E;
 }
 
-// Bin one marginal's points (original order, device) and build its binned layout.  The
-// temporaries (sort keys in scratch, cells, tile ids, box tile ranges) belong to the caller.
+// Bin one marginal's points (original order, device): its sorted points, window rows and the sorted
+// range of every box tile.  The temporaries (sort keys in scratch, cells, tile ids, box tile
+// ranges) belong to the caller.
 static int bin_marginal(mot_plan_s *P, int k, const double *pts_orig_dev, void *scratch,
                         size_t scratch_bytes, int32_t *cell_tmp, int32_t *tile_tmp,
                         int32_t *box_lo, int32_t *box_hi)
@@ -1006,22 +1059,24 @@ static int bin_marginal(mot_plan_s *P, int k, const double *pts_orig_dev, void *
     MOT_HIP(launch_gather_rows(pts_orig_dev, G.perm, G.n, d, G.pts, P->stream));
     MOT_HIP(launch_window_rows(d, G.n, G.pts, Q.s, Q.o, T, Q.m, Q.kb_b, G.win, P->stream));
     // sorted ranges of the active box's tiles only (the box is a small part of the grid)
-    int64_t nbox = 1;
-    for (int c = 0; c < d; ++c) nbox *= Q.ntile[c];
     MOT_HIP(launch_box_tile_ranges(G.n, scratch, sub, d, tpd, Q.tmin, Q.ntile, box_lo, box_hi, P->stream));
-    std::vector<int32_t> lo_h(nbox), hi_h(nbox);
-    MOT_HIP(hipMemcpyAsync(lo_h.data(), box_lo, nbox * sizeof(int32_t), hipMemcpyDeviceToHost, P->stream));
-    MOT_HIP(hipMemcpyAsync(hi_h.data(), box_hi, nbox * sizeof(int32_t), hipMemcpyDeviceToHost, P->stream));
-    MOT_HIP(hipStreamSynchronize(P->stream));
-    // Chunks over the box tiles in row-major order (coordinate 0 slowest).  Box tiles in
-    // that order are a monotone subsequence of the global tile order the points are
-    // sorted by, and every point lies in a box tile, so consecutive chunks are
-    // consecutive ranges of the sorted points: chunk c = [starts[c], starts[c+1]).
+    return MOT_OK;
+}
+
+// Chunks of a binned marginal over the box tiles in row-major order (coordinate 0 slowest),
+// from the tiles' sorted ranges [lo, hi).  Box tiles in that order are a monotone subsequence of
+// the global tile order the points are sorted by, and every point lies in a box tile, so
+// consecutive chunks are consecutive ranges of the sorted points: chunk c = [starts[c],
+// starts[c+1]).
+static int chunk_marginal(mot_plan_s *P, int k, int64_t nbox, const int32_t *lo, const int32_t *hi, Uploads &up)
+{
+    MargDev &G = P->marg[k];
+    const NfftParams &Q = P->P;
     std::vector<int32_t> starts, tiles, tch2;
     tch2.push_back(0);
     int64_t covered = 0;
     for (int64_t bt = 0; bt < nbox; ++bt) {
-        const int a = lo_h[bt], b = hi_h[bt];
+        const int a = lo[bt], b = hi[bt];
         if (a != covered && b > a) return MOT_EDOMAIN;
         for (int s = a; s < b; s += Q.chunk) {
             starts.push_back(s);
@@ -1037,12 +1092,9 @@ static int bin_marginal(mot_plan_s *P, int k, const double *pts_orig_dev, void *
     G.nchunks = (int)starts.size();
     G.h_chunk_tile = tiles;
     G.h_chunk_start = bounds;
-    MOT_TRY(P->arena.get_n(bounds.size() + 2, &G.chunk_start));
-    MOT_TRY(P->arena.get_n(tiles.size() + 1, &G.chunk_tile));
-    MOT_TRY(P->arena.get_n(tch2.size() + 1, &G.tile_chunks));
-    MOT_HIP(hipMemcpy(G.chunk_start, bounds.data(), bounds.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    MOT_HIP(hipMemcpy(G.chunk_tile, tiles.data(), tiles.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-    MOT_HIP(hipMemcpy(G.tile_chunks, tch2.data(), tch2.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+    MOT_TRY(up.add(P->arena, bounds, &G.chunk_start));
+    MOT_TRY(up.add(P->arena, tiles, &G.chunk_tile));
+    MOT_TRY(up.add(P->arena, tch2, &G.tile_chunks));
     return MOT_OK;
 }
 
@@ -1168,6 +1220,7 @@ static int plan_stats_alloc(mot_plan_s *P, int n_partials_hint)
     P->hist_cap = 1 << 16;
     MOT_TRY(P->arena.get_n(4, &P->sweep_ctr));
     MOT_TRY(P->arena.get_n(4, &P->flag));
+    MOT_TRY(P->arena.get_n(1, &P->status));
     MOT_TRY(P->arena.get_n(P->hist_cap, &P->flag_hist));
     MOT_TRY(P->arena.get_n(P->hist_cap, &P->S_hist));
     MOT_TRY(P->arena.get_n(P->hist_cap, &P->err_hist));
@@ -1177,6 +1230,8 @@ static int plan_stats_alloc(mot_plan_s *P, int n_partials_hint)
     MOT_HIP(launch_fill_int(P->flag, 0, 1, P->stream));
     return MOT_OK;
 }
+
+constexpr int64_t kBoxRanges = (int64_t)1 << 18;  // 2 MiB of ranges at most, unless one marginal has more
 
 // Per-marginal device state shared by both topologies: parameters (NFFT path), binned
 // point layout (NFFT) or identity order, weights, phi = 1, statistics buffers.
@@ -1265,14 +1320,27 @@ int mot::setup_marginals(mot_plan_s *P, const std::vector<double> &pts_h, const 
         }
         const size_t sb = stable_tile_sort_scratch(nmax, ntiles);
         void *scratch = nullptr;
-        int32_t *cell_tmp = nullptr, *tile_tmp = nullptr, *blo = nullptr, *bhi = nullptr;
+        int32_t *cell_tmp = nullptr, *tile_tmp = nullptr, *box = nullptr;
+        // the tile ranges of as many marginals as kBoxRanges tiles hold are read back in one copy
+        const int per = (int)std::max<int64_t>(1, std::min<int64_t>(K, kBoxRanges / nbox));
         MOT_TRY(tmp.a.get(sb, &scratch));
         MOT_TRY(tmp.a.get_n((size_t)nmax * d, &cell_tmp));
         MOT_TRY(tmp.a.get_n((size_t)nmax, &tile_tmp));
-        MOT_TRY(tmp.a.get_n((size_t)nbox, &blo));
-        MOT_TRY(tmp.a.get_n((size_t)nbox, &bhi));
-        for (int k = 0; k < K; ++k)
-            MOT_TRY(bin_marginal(P, k, pts_dev + P->off[k] * d, scratch, sb, cell_tmp, tile_tmp, blo, bhi));
+        MOT_TRY(tmp.a.get_n((size_t)(2 * per * nbox), &box));
+        std::vector<int32_t> box_h((size_t)(2 * per * nbox));
+        Uploads up;
+        for (int k0 = 0; k0 < K; k0 += per) {
+            const int kn = std::min(per, K - k0);
+            for (int q = 0; q < kn; ++q)
+                MOT_TRY(bin_marginal(P, k0 + q, pts_dev + P->off[k0 + q] * d, scratch, sb, cell_tmp, tile_tmp,
+                                     box + 2 * q * nbox, box + (2 * q + 1) * nbox));
+            MOT_HIP(hipMemcpyAsync(box_h.data(), box, (size_t)(2 * kn * nbox) * sizeof(int32_t), hipMemcpyDeviceToHost,
+                                   P->stream));
+            MOT_HIP(hipStreamSynchronize(P->stream));
+            for (int q = 0; q < kn; ++q)
+                MOT_TRY(chunk_marginal(P, k0 + q, nbox, &box_h[2 * q * nbox], &box_h[(2 * q + 1) * nbox], up));
+        }
+        MOT_TRY(up.flush());
     } else if (P->path == MOT_TRUNC) {
         // a1's binning with tile edge 1: points sorted by cell, cell ranges kept
         const TruncParams &T = P->TP;
@@ -1690,9 +1758,6 @@ int mot_sinkhorn(mot_plan P, int32_t max_sweeps, double delta_S, double tol_marg
     if (check_every < 1) check_every = 1;
     const bool stopping = delta_S > 0.0 || tol_marginal > 0.0;
     int done = 0, status = MOT_MAXITER;
-    int32_t ctr0 = 0;
-    MOT_HIP(hipMemcpyAsync(&ctr0, P->sweep_ctr, 4, hipMemcpyDeviceToHost, P->stream));
-    MOT_HIP(hipStreamSynchronize(P->stream));
     double lastS = NAN, lastE = NAN;
     while (done < max_sweeps) {
         const int batch = stopping ? std::min(check_every, max_sweeps - done) : max_sweeps - done;
@@ -1701,26 +1766,21 @@ int mot_sinkhorn(mot_plan P, int32_t max_sweeps, double delta_S, double tol_marg
         if (rc < 0) return rc;
         done += batch;
         // read the last recorded values
-        const int idx = (ctr0 + done - 1) % P->hist_cap;
-        const int idxp = (ctr0 + done - 2 + P->hist_cap) % P->hist_cap;
-        double h[2] = {0, 0}, e = 0;
-        int32_t fl = 0;
-        MOT_HIP(hipMemcpyAsync(&h[1], P->S_hist + idx, 8, hipMemcpyDeviceToHost, P->stream));
-        MOT_HIP(hipMemcpyAsync(&h[0], P->S_hist + idxp, 8, hipMemcpyDeviceToHost, P->stream));
-        MOT_HIP(hipMemcpyAsync(&e, P->err_hist + idx, 8, hipMemcpyDeviceToHost, P->stream));
-        MOT_HIP(hipMemcpyAsync(&fl, P->flag, 4, hipMemcpyDeviceToHost, P->stream));
+        SweepStatus last{};
+        MOT_HIP(launch_sweep_status(P->sweep_ctr, P->flag, P->hist_cap, P->S_hist, P->err_hist, P->status, P->stream));
+        MOT_HIP(hipMemcpyAsync(&last, P->status, sizeof last, hipMemcpyDeviceToHost, P->stream));
         MOT_HIP(hipStreamSynchronize(P->stream));
-        lastS = h[1];
-        lastE = e;
-        if (fl) {
+        lastS = last.S_last;
+        lastE = last.err;
+        if (last.flag) {
             status = MOT_ENUMERIC;
             break;
         }
-        if (tol_marginal > 0.0 && e <= tol_marginal) {
+        if (tol_marginal > 0.0 && last.err <= tol_marginal) {
             status = MOT_OK;
             break;
         }
-        if (delta_S > 0.0 && (ctr0 + done) >= 2 && std::fabs(h[1] - h[0]) < delta_S) {
+        if (delta_S > 0.0 && last.sweeps >= 2 && std::fabs(last.S_last - last.S_before) < delta_S) {
             status = MOT_OK;
             break;
         }
@@ -1795,9 +1855,10 @@ int mot_get_S_history(mot_plan P, double *S_out, int32_t count)
     const int avail = std::min(ctr, P->hist_cap);
     const int nout = std::min(avail, (int)count);
     const int first = ctr - avail;
-    for (int i = 0; i < nout; ++i) {
-        const int slot = (first + i) % P->hist_cap;
-        MOT_HIP(hipMemcpyAsync(S_out + i, P->S_hist + slot, 8, hipMemcpyDeviceToHost, P->stream));
+    for (int i = 0; i < nout;) {  // a range up to the ring's end, then one from its start
+        const int slot = (first + i) % P->hist_cap, run = std::min(nout - i, P->hist_cap - slot);
+        MOT_HIP(hipMemcpyAsync(S_out + i, P->S_hist + slot, run * sizeof(double), hipMemcpyDeviceToHost, P->stream));
+        i += run;
     }
     MOT_HIP(hipStreamSynchronize(P->stream));
     return nout;
@@ -1940,7 +2001,7 @@ int mot_apply_kernel(mot_plan P, int32_t t, int32_t s, const double *v, double *
     std::vector<ProdJob> hj(2 * P->K + 1);
     hj[2 * P->K] = J;
     B.products(P->jobs_dev, hj, {2 * P->K});
-    if (B.rc < 0) return B.rc;
+    MOT_TRY(B.finish());
     MOT_TRY(run_steps(steps, P->stream));
     MOT_HIP(launch_scatter_vec(P->apply_out, P->marg[t].perm, P->n[t], tmp + P->n[s], P->stream));
     MOT_HIP(hipMemcpyAsync(out, tmp + P->n[s], P->n[t] * sizeof(double),
