@@ -618,13 +618,22 @@ __global__ __launch_bounds__(64 * kSpreadWaves, G == 1 ? 6 : (G == 2 ? 5 : 4)) v
 // is shorter than a wavefront); item = (job, first cell).  The job's tile -> chunk table
 // is staged in LDS when it fits, so the chunk lookups of a thread's covering tiles cost
 // LDS rather than global latency.
+// PARTS = 2: in 3-D the leading tiles that cover a cell go to two threads in turn, as each is a
+// sequence of dependent lookups and loads that one thread waits for (30^3 box, tiles of 7 cells, one
+// or two jobs: 12.6 us with one thread to a cell, 7.7 here, 8.8 with four).  A launch that fills
+// the chip is bound by its loads and gains nothing (nine jobs on a 41^3 box: 27.2 us, 40 with four), so
+// the split ends at kFoldSplitItems items.
+constexpr int kFoldSplitItems = 1024;
+
 // One item of the fold.
-template <int D, class Tab>
-__device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch)
+template <int D, int PARTS, class Tab>
+__device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch, float *s_part)
 {
     const int Ll = J.L[D - 1];
     const int nl = D == 3 ? J.L[0] * J.L[1] : (D == 2 ? J.L[0] : 1);
-    const int f = f0 + (int)threadIdx.x;
+    const int cell = (int)threadIdx.x % kFoldCellsPerItem, part = (int)threadIdx.x / kFoldCellsPerItem;
+    if (D < 3 && part > 0) return;
+    const int f = D == 3 && PARTS == 2 ? min(f0 + cell, nl * Ll - 1) : f0 + cell;
     if (f >= nl * Ll) return;
     const int line = f / Ll, g = f - line * Ll;
     int gu[2] = {0, 0};  // line coordinates in the leading dimensions
@@ -634,15 +643,23 @@ __device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch)
     } else if (D == 2) {
         gu[0] = line;
     }
-    gp(J.grid)[f] = fold_cell<D>(J, gu, g, tch);
+    if constexpr (D == 3 && PARTS == 2) {
+        const float sum = fold_cell<D>(J, gu, g, tch, part, PARTS);
+        if (part > 0) s_part[cell] = sum;
+        __syncthreads();
+        if (part == 0 && f0 + cell < nl * Ll) gp(J.grid)[f] = sum + s_part[cell];
+    } else {
+        gp(J.grid)[f] = fold_cell<D>(J, gu, g, tch);
+    }
 }
 
 // D = 0: every item takes its job's own d (batches of plans of several dimensions).
-template <int D>
-__global__ __launch_bounds__(kFoldCellsPerItem) void fold_kernel(const ProdJob *__restrict__ jobs,
+template <int D, int PARTS>
+__global__ __launch_bounds__(kFoldCellsPerItem *PARTS) void fold_kernel(const ProdJob *__restrict__ jobs,
                                                                  const int2 *__restrict__ items, int n_items)
 {
     __shared__ int32_t s_tab[kFoldTab];
+    __shared__ float s_part[PARTS == 2 ? kFoldCellsPerItem : 1];
     for (int it = blockIdx.x; it < n_items; it += gridDim.x) {
         const int2 itm = items[it];
         const ProdJob &J = jobs[itm.x];
@@ -656,15 +673,17 @@ __global__ __launch_bounds__(kFoldCellsPerItem) void fold_kernel(const ProdJob *
             const MOT_GLOBAL int32_t *tg = gp(J.src_tile_chunks);
             for (int i = threadIdx.x; i < ntab; i += blockDim.x) s_tab[i] = tg[i];
             __syncthreads();
+        } else if (PARTS == 2) {
+            __syncthreads();  // the previous item's reads of the partial sums are done
         }
         const int32_t *lt = static_cast<const int32_t *>(s_tab);
         const MOT_GLOBAL int32_t *gt = gp(J.src_tile_chunks);
         if (d == 3) {
-            if (staged) fold_item<3>(J, itm.y, lt); else fold_item<3>(J, itm.y, gt);
+            if (staged) fold_item<3, PARTS>(J, itm.y, lt, s_part); else fold_item<3, PARTS>(J, itm.y, gt, s_part);
         } else if (d == 2) {
-            if (staged) fold_item<2>(J, itm.y, lt); else fold_item<2>(J, itm.y, gt);
+            if (staged) fold_item<2, PARTS>(J, itm.y, lt, s_part); else fold_item<2, PARTS>(J, itm.y, gt, s_part);
         } else {
-            if (staged) fold_item<1>(J, itm.y, lt); else fold_item<1>(J, itm.y, gt);
+            if (staged) fold_item<1, PARTS>(J, itm.y, lt, s_part); else fold_item<1, PARTS>(J, itm.y, gt, s_part);
         }
     }
 }
@@ -1187,18 +1206,17 @@ hipError_t launch_interp_group(int d, const ProdJob *jobs, const int32_t *gids, 
 hipError_t launch_fold(int d, const ProdJob *jobs, const int2 *items, int n_items, hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
+    const dim3 grid(nfft_grid(n_items)), block(kFoldCellsPerItem);
     if (d == 0)
-        hipLaunchKernelGGL(fold_kernel<0>, dim3(nfft_grid(n_items)), dim3(kFoldCellsPerItem), 0, s, jobs, items,
-                           n_items);
+        hipLaunchKernelGGL((fold_kernel<0, 1>), grid, block, 0, s, jobs, items, n_items);
+    else if (d == 3 && n_items <= kFoldSplitItems)
+        hipLaunchKernelGGL((fold_kernel<3, 2>), grid, dim3(2 * kFoldCellsPerItem), 0, s, jobs, items, n_items);
     else if (d == 3)
-        hipLaunchKernelGGL(fold_kernel<3>, dim3(nfft_grid(n_items)), dim3(kFoldCellsPerItem), 0, s, jobs, items,
-                           n_items);
+        hipLaunchKernelGGL((fold_kernel<3, 1>), grid, block, 0, s, jobs, items, n_items);
     else if (d == 2)
-        hipLaunchKernelGGL(fold_kernel<2>, dim3(nfft_grid(n_items)), dim3(kFoldCellsPerItem), 0, s, jobs, items,
-                           n_items);
+        hipLaunchKernelGGL((fold_kernel<2, 1>), grid, block, 0, s, jobs, items, n_items);
     else
-        hipLaunchKernelGGL(fold_kernel<1>, dim3(nfft_grid(n_items)), dim3(kFoldCellsPerItem), 0, s, jobs, items,
-                           n_items);
+        hipLaunchKernelGGL((fold_kernel<1, 1>), grid, block, 0, s, jobs, items, n_items);
     return hipGetLastError();
 }
 

@@ -73,3 +73,20 @@ def test_circle_rows(mot, d, eta, N):
         for a, b in zip(P, oP):
             assert rel_to_max(a, b) < 1e-5
     plan.close()
+
+
+@pytest.mark.parametrize("K", [2, 6])  # 3-D fold launches of about 300 and 1600 items: split cells and whole ones
+@pytest.mark.parametrize("m", [4, 6, 8])
+def test_fold_of_few_and_many_jobs(mot, K, m):
+    r = rng(m + K)
+    inst = W.make_instance(r, K, [600] + [500] * (K - 1), 3, W.TREE, 0.08, parent=W.star_parent(K))
+    fs = mot.fastsum_params(M=16, n=64, m=m, p=4, tau=1.25, eps_B=0.25, chunk=16)
+    plan = mot.Plan(inst.points, inst.weights, W.TREE, inst.parent, inst.eta, path=mot.NFFT, fastsum=fs)
+    ophi, oS, _, _ = oracle.tree_sinkhorn(inst.points, inst.weights, inst.parent, inst.eta, 2)
+    plan.sinkhorn(2)
+    # a product's error is relative to its largest value, a corner's is an eighth of that or less,
+    # and the root divides by five products of each sweep
+    tol = 100 * (2e-5 if m == 4 else TOL)
+    for a, b in zip(plan.scalings(), ophi):
+        np.testing.assert_allclose(a, b, rtol=tol)
+    plan.close()
