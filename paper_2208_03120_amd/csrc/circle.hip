@@ -832,19 +832,28 @@ __global__ void circle_pair_kernel(const T *__restrict__ Yg, const T *__restrict
     }
 }
 
-// NFFT path: src[i][l] = A[i][l] phi_l and the row's max exponent (one block per row).
-__global__ __launch_bounds__(256) void scale_rows_kernel(const double *__restrict__ A, int64_t nl,
-                                                         const double *__restrict__ phi, double *__restrict__ src,
-                                                         int32_t *__restrict__ rexp)
+// NFFT path: the largest exponent of every row of A diag(phi) (one block per row).  The products are
+// formed again where they are spread: writing them here cost as much again as reading A (4000 x
+// 4000: 51.2 us a pass, here 23.2).
+__global__ __launch_bounds__(256) void row_exponents_kernel(const double *__restrict__ A, int64_t nl,
+                                                            const double *__restrict__ phi,
+                                                            int32_t *__restrict__ rexp)
 {
     __shared__ int red[4];
     const int64_t i = blockIdx.x;
-    int m = INT32_MIN;
-    for (int64_t l = threadIdx.x; l < nl; l += blockDim.x) {
-        const double v = A[i * nl + l] * phi[l];
-        src[i * nl + l] = v;
-        if (v > 0.0 && v < INFINITY) m = max(m, ilogb(v));
+    double most = 0.0;
+    for (int64_t l = threadIdx.x; l < nl; l += 256 * 4) {
+        double v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // columns beyond the row repeat its last
+            const int64_t j = min(l + 256 * u, nl - 1);
+            v[u] = A[i * nl + j] * phi[j];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (v[u] < INFINITY) most = fmax(most, v[u]);
     }
+    int m = most > 0.0 ? ilogb(most) : INT32_MIN;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) m = max(m, lane_xor(m, o));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
@@ -883,7 +892,6 @@ struct CircleState {
     int ns = 0;
     double *m_part = nullptr;      // scratch partials of marginal-only evaluations
     // NFFT path: per-row product jobs for each product position
-    double *src = nullptr;
     int32_t *rowexp = nullptr;
     std::vector<std::vector<Step>> steps_g, steps_b;  // [k]
 };
@@ -999,8 +1007,8 @@ static int circle_product(mot_plan_s *P, CircleState &C, int gamma, int k)
         return MOT_OK;
     }
     const double *A = (const double *)Ymat(C, gamma, l);
-    hipLaunchKernelGGL(scale_rows_kernel, dim3((unsigned)C.n1), dim3(256), 0, st, A, (int64_t)P->n[l],
-                       (const double *)P->marg[l].phi, C.src, C.rowexp);
+    hipLaunchKernelGGL(row_exponents_kernel, dim3((unsigned)C.n1), dim3(256), 0, st, A, (int64_t)P->n[l],
+                       (const double *)P->marg[l].phi, C.rowexp);
     MOT_HIP(hipGetLastError());
     return run_steps(gamma ? C.steps_g[k] : C.steps_b[k], st);
 }
@@ -1100,15 +1108,16 @@ static int kmat16(mot_plan_s *P, CircleState &C, int a, int b, unsigned short **
     return hipGetLastError() == hipSuccess ? MOT_OK : MOT_EDEVICE;
 }
 
-// NFFT path: n1 product jobs (one per matrix row) for out = K^{(t,s)} rows.
-static int nfft_position(mot_plan_s *P, CircleState &C, int t, int s, double *out, std::vector<ProdJob> &tmpl,
-                         std::vector<Step> &steps)
+// NFFT path: n1 product jobs (one per matrix row) for out = K^{(t,s)} (A diag(phi^s)) rows.
+static int nfft_position(mot_plan_s *P, CircleState &C, int t, int s, const double *A, double *out,
+                         std::vector<ProdJob> &tmpl, std::vector<Step> &steps)
 {
     const int64_t n1 = C.n1;
     std::vector<ProdJob> jobs(n1);
     for (int64_t i = 0; i < n1; ++i) {
         ProdJob &J = jobs[i];
-        MOT_TRY(make_prod_job(P, t, s, C.src + i * P->n[s], C.rowexp + i, out + i * P->n[t], &J, nullptr, false));
+        MOT_TRY(make_prod_job(P, t, s, A + i * P->n[s], C.rowexp + i, out + i * P->n[t], &J, nullptr, false));
+        J.v_mul = P->marg[s].phi;
         J.patches = tmpl[i].patches;
         J.grid = tmpl[i].grid;
         J.spec0 = tmpl[i].spec0;
@@ -1207,7 +1216,6 @@ int circle_create(mot_plan_s *P, const std::vector<double> &pts_h, const std::ve
     MOT_TRY(P->arena.get_n(2 * (size_t)slot, &C.s_part));
     MOT_TRY(P->arena.get_n(2 * (size_t)((nmax + kColPhiCols - 1) / kColPhiCols), &C.m_part));
     if (C.nfft) {
-        MOT_TRY(P->arena.get_n((size_t)C.n1 * nmax, &C.src));
         MOT_TRY(P->arena.get_n((size_t)C.n1, &C.rowexp));
         // work buffers per row, shared by all product positions
         std::vector<ProdJob> tmpl(C.n1);
@@ -1222,8 +1230,10 @@ int circle_create(mot_plan_s *P, const std::vector<double> &pts_h, const std::ve
         C.steps_g.assign(K, {});
         C.steps_b.assign(K, {});
         for (int k = 2; k <= K - 1; ++k)
-            MOT_TRY(nfft_position(P, C, k, k - 1, (double *)Ymat(C, 1, k), tmpl, C.steps_g[k]));
-        for (int k = 1; k <= K - 2; ++k) MOT_TRY(nfft_position(P, C, k, k + 1, (double *)C.Yb[k], tmpl, C.steps_b[k]));
+            MOT_TRY(nfft_position(P, C, k, k - 1, (double *)Ymat(C, 1, k - 1), (double *)Ymat(C, 1, k), tmpl,
+                                  C.steps_g[k]));
+        for (int k = 1; k <= K - 2; ++k)
+            MOT_TRY(nfft_position(P, C, k, k + 1, (double *)C.Yb[k + 1], (double *)C.Yb[k], tmpl, C.steps_b[k]));
     }
     MOT_TRY(circle_up(P, C));
     MOT_HIP(hipStreamSynchronize(st));

@@ -374,11 +374,12 @@ struct Stage {
     static constexpr int kPer = (kRow4 + 255) / 256;        // per thread (256 threads)
     static constexpr int kBytes = kRow4 * 16 + (WITH_V ? kStage * 4 : 0);
     f32x4 r[kPer];
-    double v;  // scaled only when stored, so that the loads stay in flight
+    double v, w;  // source value and factor, joined only when stored, so that the loads stay in flight
 
     // Registers <- global: points pb .. pb + kStage - 1 (zeros past p1), and for
     // spreading the source values.
-    __device__ __forceinline__ void load(const float *rows, const double *vsrc, int64_t pb, int64_t p1)
+    __device__ __forceinline__ void load(const float *rows, const double *vsrc, const double *wsrc, int64_t pb,
+                                         int64_t p1)
     {
         const MOT_GLOBAL f32x4 *g = reinterpret_cast<const MOT_GLOBAL f32x4 *>(gp(rows)) + pb * (D * 4);
 #pragma unroll
@@ -389,8 +390,12 @@ struct Stage {
         }
         if constexpr (WITH_V) {
             v = 0.0;
+            w = 1.0;
             const int64_t p = pb + threadIdx.x;
-            if (threadIdx.x < kStage && p < p1) v = gp(vsrc)[p];
+            if (threadIdx.x < kStage && p < p1) {
+                v = gp(vsrc)[p];
+                if (wsrc) w = gp(wsrc)[p];
+            }
         }
     }
     // LDS <- registers; source values are stored as FP32 v 2^-e.  In 3-D the dimension-1
@@ -409,7 +414,8 @@ struct Stage {
             }
         }
         if constexpr (WITH_V)
-            if (threadIdx.x < kStage) reinterpret_cast<float *>(buf + kRow4 * 16)[threadIdx.x] = (float)ldexp(v, -e);
+            if (threadIdx.x < kStage)
+                reinterpret_cast<float *>(buf + kRow4 * 16)[threadIdx.x] = (float)ldexp(v * w, -e);
     }
 };
 
@@ -434,12 +440,12 @@ __global__ __launch_bounds__(64 * kSpreadWaves, 4) void spread_kernel(const Prod
         const int nstages = (int)((p1 - p0 + kStage - 1) / kStage);
         f32x4 acc = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         St stg;
-        stg.load(J.src_win, J.v, p0, p1);
+        stg.load(J.src_win, J.v, J.v_mul, p0, p1);
         stg.store(smem, e);
         __syncthreads();
         for (int k = 0; k < nstages; ++k) {
             const bool more = k + 1 < nstages;
-            if (more) stg.load(J.src_win, J.v, p0 + (int64_t)(k + 1) * kStage, p1);
+            if (more) stg.load(J.src_win, J.v, J.v_mul, p0 + (int64_t)(k + 1) * kStage, p1);
             const unsigned char *buf = smem + (k & 1) * St::kBytes;
             const float *rl = reinterpret_cast<const float *>(buf);
             const float *vl = reinterpret_cast<const float *>(buf + St::kRow4 * 16);
@@ -506,11 +512,12 @@ struct SpreadStage3 {
     static constexpr int kPer = (kRow4 + 255) / 256;        // per thread (256 threads)
     static constexpr int kBytes = kRow4 * 16 + G * kStage * 4;
     f32x4 r[kPer];
-    double v;  // value of job q = threadIdx.x / kStage (the wave), scaled only when stored
+    double v, w;  // value and factor of job q = threadIdx.x / kStage (the wave), joined only when stored
 
     // Registers <- global: points pb .. pb + kStage - 1 (zeros past p1); wave q < G loads
-    // job q's values from vq (the job's pointer, selected by the caller).
-    __device__ __forceinline__ void load(const float *rows, const double *vq, int64_t pb, int64_t p1)
+    // job q's values from vq (the job's pointer, selected by the caller), factors from wq if any.
+    __device__ __forceinline__ void load(const float *rows, const double *vq, const double *wq, int64_t pb,
+                                         int64_t p1)
     {
         const MOT_GLOBAL f32x4 *g = reinterpret_cast<const MOT_GLOBAL f32x4 *>(gp(rows)) + pb * 12;
 #pragma unroll
@@ -520,8 +527,12 @@ struct SpreadStage3 {
             if (idx < kRow4 && pb + idx / 12 < p1) r[i] = g[idx];
         }
         v = 0.0;
+        w = 1.0;
         const int64_t p = pb + (threadIdx.x % kStage);
-        if (threadIdx.x / kStage < G && p < p1) v = gp(vq)[p];
+        if (threadIdx.x / kStage < G && p < p1) {
+            v = gp(vq)[p];
+            if (wq) w = gp(wq)[p];
+        }
     }
     // LDS <- registers (dimension-1 rows transposed, store_piece3); job q's values are
     // stored as FP32 v 2^-eq.
@@ -532,7 +543,8 @@ struct SpreadStage3 {
             const int idx = threadIdx.x + 256 * i;
             if (idx < kRow4) store_piece3(buf, idx, r[i]);
         }
-        if (threadIdx.x / kStage < G) reinterpret_cast<float *>(buf + kRow4 * 16)[threadIdx.x] = (float)ldexp(v, -eq);
+        if (threadIdx.x / kStage < G)
+            reinterpret_cast<float *>(buf + kRow4 * 16)[threadIdx.x] = (float)ldexp(v * w, -eq);
     }
 };
 
@@ -564,12 +576,12 @@ __global__ __launch_bounds__(64 * kSpreadWaves, G == 1 ? 6 : (G == 2 ? 5 : 4)) v
 #pragma unroll
             for (int t = 0; t < 4; ++t) acc[g][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         St stg;
-        stg.load(J.src_win, vq, p0, p1);
+        stg.load(J.src_win, vq, J.v_mul, p0, p1);
         stg.store(smem, eq);
         __syncthreads();
         for (int k = 0; k < nstages; ++k) {
             const bool more = k + 1 < nstages;
-            if (more) stg.load(J.src_win, vq, p0 + (int64_t)(k + 1) * kStage, p1);
+            if (more) stg.load(J.src_win, vq, J.v_mul, p0 + (int64_t)(k + 1) * kStage, p1);
             const unsigned char *buf = smem + (k & 1) * St::kBytes;
             const float *rl = reinterpret_cast<const float *>(buf);
             const float *vl = reinterpret_cast<const float *>(buf + St::kRow4 * 16);
@@ -757,12 +769,12 @@ __global__ __launch_bounds__(64 * kInterpWaves, 4) void interp_kernel(const Prod
         } else {
             const int nstages = (int)((p1 - p0 + kStage - 1) / kStage);
             St stg;
-            stg.load(J.tgt_win, nullptr, p0, p1);
+            stg.load(J.tgt_win, nullptr, nullptr, p0, p1);
             stg.store(smem, 0);
             __syncthreads();
             for (int k = 0; k < nstages; ++k) {
                 const bool more = k + 1 < nstages;
-                if (more) stg.load(J.tgt_win, nullptr, p0 + (int64_t)(k + 1) * kStage, p1);
+                if (more) stg.load(J.tgt_win, nullptr, nullptr, p0 + (int64_t)(k + 1) * kStage, p1);
                 const float *rl = reinterpret_cast<const float *>(smem + (k & 1) * St::kBytes);
                 // this wave's group: stage points 16 wave .. 16 wave + 15
                 const float *grow = rl + (16 * wave) * (D * kPatch);
@@ -840,12 +852,12 @@ __global__ __launch_bounds__(64 * kInterpWaves, 6) void interp3_kernel(const Pro
         MOT_GLOBAL double *out = gp(J.out);
         const int nstages = (int)((p1 - p0 + kStage - 1) / kStage);
         St stg;
-        stg.load(J.tgt_win, nullptr, p0, p1);
+        stg.load(J.tgt_win, nullptr, nullptr, p0, p1);
         stg.store(smem, 0);
         __syncthreads();
         for (int k = 0; k < nstages; ++k) {
             const bool more = k + 1 < nstages;
-            if (more) stg.load(J.tgt_win, nullptr, p0 + (int64_t)(k + 1) * kStage, p1);
+            if (more) stg.load(J.tgt_win, nullptr, nullptr, p0 + (int64_t)(k + 1) * kStage, p1);
             const float *rl = reinterpret_cast<const float *>(smem + (k & 1) * St::kBytes);
 #pragma unroll 1
             for (int g = 0; g < 4; ++g) {
@@ -936,17 +948,19 @@ __global__ __launch_bounds__(256, 4) void spread_group_kernel(const ProdJob *__r
             vnext = j >= 0 ? jobs[j].v : nullptr;
             enext = j >= 0 ? source_exponent(jobs[j]) : 0;
         };
-        double v[S::PV];
+        const double *wsrc = J0.v_mul;  // the jobs' common factor
+        double v[S::PV], w[S::PV];
         auto load_v = [&](int64_t pb) {
 #pragma unroll
             for (int q = 0; q < S::PV; ++q) {
                 const int64_t p = pb + vp + q;
                 v[q] = vsrc && p < p1 ? gp(vsrc)[p] : 0.0;
+                w[q] = wsrc && p < p1 ? gp(wsrc)[p] : 1.0;
             }
         };
         auto store_v = [&](float *buf, int ex) {
 #pragma unroll
-            for (int q = 0; q < S::PV; ++q) buf[(vp + q) * S::kPitch + tid % S::J] = (float)ldexp(v[q], -ex);
+            for (int q = 0; q < S::PV; ++q) buf[(vp + q) * S::kPitch + tid % S::J] = (float)ldexp(v[q] * w[q], -ex);
         };
         f32x4 acc[NA];
 #pragma unroll
@@ -955,7 +969,7 @@ __global__ __launch_bounds__(256, 4) void spread_group_kernel(const ProdJob *__r
         job_of(0);
         vsrc = vnext;
         e = enext;
-        stg.load(J0.src_win, nullptr, p0, p1);
+        stg.load(J0.src_win, nullptr, nullptr, p0, p1);
         load_v(p0);
         job_of(1);
         __syncthreads();  // the previous item's reads of LDS are done
@@ -975,7 +989,7 @@ __global__ __launch_bounds__(256, 4) void spread_group_kernel(const ProdJob *__r
                     }
                     const int64_t pn = last ? p0 : p0 + (int64_t)(k + 1) * kStage;
                     load_v(pn);
-                    if (nst > 1) stg.load(J0.src_win, nullptr, pn, p1);
+                    if (nst > 1) stg.load(J0.src_win, nullptr, nullptr, pn, p1);
                 }
                 const float *rl = reinterpret_cast<const float *>(rows[nst > 1 ? buf : 0]);
                 const float *vl = vals[buf];
@@ -1074,7 +1088,7 @@ __global__ __launch_bounds__(256, 4) void interp_group_kernel(const ProdJob *__r
         };
         St stg;
         job_of(0);
-        stg.load(J0.tgt_win, nullptr, p0, p1);
+        stg.load(J0.tgt_win, nullptr, nullptr, p0, p1);
         load_g();
         __syncthreads();  // the previous item's reads of LDS are done
         stg.store(rows, 0);
@@ -1096,7 +1110,7 @@ __global__ __launch_bounds__(256, 4) void interp_group_kernel(const ProdJob *__r
             for (int k = 0; k < nst; ++k) {
                 const int64_t pb = p0 + (int64_t)k * kStage;
                 if (nst > 1 && g + k > 0) {
-                    stg.load(J0.tgt_win, nullptr, pb, p1);
+                    stg.load(J0.tgt_win, nullptr, nullptr, pb, p1);
                     __syncthreads();
                     stg.store(rows, 0);
                     __syncthreads();

@@ -106,6 +106,9 @@ struct ProdJob {
     int32_t diff;      // mixed direct / truncated paths: exponent formed in FP64
     // vectors
     const double *v;   // source vector, n_s entries
+    // NFFT path, null: none.  The source is v times this; jobs of one launch that spread from the
+    // same points share it
+    const double *v_mul;
     int32_t *v_exp;    // slot holding max_j exponent(|v_j|) (atomicMax), reset per sweep
     double *out;       // target vector, n_t entries
     int64_t ns, nt;

@@ -33,3 +33,20 @@ def test_small_dense_circles(mot, prec, bound, sizes):
     assert max_rel(gauge_fix(plan.scalings(), inst.weights), gauge_fix(ophi, inst.weights)) < bound
     assert abs(plan.S_history()[-1] - oS[-1]) < 50 * bound * abs(oS[-1])
     plan.close()
+
+
+@pytest.mark.parametrize("d,sizes", [
+    (1, (10, 130, 65, 90)), (2, (10, 130, 65, 90)),   # spread row by row
+    (1, (70, 40, 129, 17)), (2, (17, 130, 65, 90)),   # in groups, the last with one row
+    (3, (7, 60, 33, 45)),                             # 3-D: two or three rows to an item
+])
+def test_fast_summation_circle_rows(mot, d, sizes):
+    """Products of A diag(phi), the scaling applied where the rows are spread."""
+    inst = W.make_instance(np.random.Generator(np.random.PCG64(sum(sizes))), len(sizes), list(sizes), d, W.CIRCLE, 0.1)
+    ophi, oS, _, _ = oracle.circle_sinkhorn(inst.points, inst.weights, inst.eta, 5)
+    plan = mot.Plan(inst.points, inst.weights, W.CIRCLE, None, inst.eta, path=mot.NFFT)
+    plan.sinkhorn(5)
+    # the bound that circles on this path hold elsewhere
+    assert max_rel(gauge_fix(plan.scalings(), inst.weights), gauge_fix(ophi, inst.weights)) < 1e-5
+    np.testing.assert_allclose(plan.S_history(), oS, rtol=1e-6)
+    plan.close()
