@@ -656,7 +656,7 @@ __device__ __forceinline__ void fold_item(const ProdJob &J, int f0, Tab tch, flo
         gu[0] = line;
     }
     if constexpr (D == 3 && PARTS == 2) {
-        const float sum = fold_cell<D>(J, gu, g, tch, part, PARTS);
+        const float sum = fold_cell<D, PARTS>(J, gu, g, tch, part);
         if (part > 0) s_part[cell] = sum;
         __syncthreads();
         if (part == 0 && f0 + cell < nl * Ll) gp(J.grid)[f] = sum + s_part[cell];

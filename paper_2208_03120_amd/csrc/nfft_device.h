@@ -19,12 +19,15 @@ __device__ __forceinline__ int div_small(int a, float rT) { return (int)(((float
 // together and then added, so a round of loads waits once.  Absent tiles and chunks read entry
 // 0 and add zero: predicated loads cost a branch each, which bound small folds (30 x 30 cells
 // in 2-D: 8.8 us per launch with branches).  In 3-D every second leading tile goes to a sum of its
-// own, so that the two threads of a cell (part = 0 and 1 of parts = 2) give the same bits as one.
-template <int D, int COV, class Tab>
-__device__ __forceinline__ float fold_cover(const ProdJob &J, const int (&gu)[2], int g, Tab tch, int part, int parts)
+// own, so that the two threads of a cell (part = 0 and 1 of PARTS = 2) give the same bits as one.
+template <int D, int COV, int PARTS, class Tab>
+__device__ __forceinline__ float fold_cover(const ProdJob &J, const int (&gu)[2], int g, Tab tch, int part)
 {
     constexpr int W = 16, NU = D >= 2 ? COV : 1, pe = D == 3 ? 4096 : (D == 2 ? 256 : 16);
-    constexpr int NR = D == 1 ? 4 : (D == 3 ? 2 : 1);  // chunks of a tile loaded together
+    // chunks of a tile loaded together; in 3-D two only where two threads share a cell: launches that
+    // fill the chip lose more to the absent second chunks than the loads in flight give (ten sweeps
+    // of nine jobs on a 46^3 box: 4.92 ms with one, 5.02 with two)
+    constexpr int NR = D == 1 ? 4 : (PARTS == 2 ? 2 : 1);
     constexpr int lead = D == 3 ? 1 : 0;  // index of the u dimension among the leading ones
     const int T = J.T, ntl = J.ntile[D - 1];
     const float rT = 1.0f / (float)T;
@@ -41,7 +44,7 @@ __device__ __forceinline__ float fold_cover(const ProdJob &J, const int (&gu)[2]
     const int tl_b = ua * ntl + ka;
     const int loc_b = (D >= 2 ? (gu[lead] - ua * T) * W : 0) + (g - ka * T);
     float acc = 0.0f, other = 0.0f;  // of every second leading tile
-    for (int t0 = t0a + part; t0 <= t0b; t0 += parts) {
+    for (int t0 = t0a + part; t0 <= t0b; t0 += PARTS) {
         const int tl0 = (D == 3 ? t0 * J.ntile[1] * ntl : 0) + tl_b;
         const int loc0 = (D == 3 ? (gu[0] - t0 * T) * W * W : 0) + loc_b;
         uint32_t at[NU][COV];
@@ -75,7 +78,7 @@ __device__ __forceinline__ float fold_cover(const ProdJob &J, const int (&gu)[2]
 #pragma unroll
                     for (int k = 0; k < COV; ++k) acc += nc[u][k] > r0 + r ? val[r][u][k] : 0.0f;
         }
-        if (D == 3 && parts == 1) {
+        if (D == 3 && PARTS == 1) {
             const float t = acc;
             acc = other;
             other = t;
@@ -85,8 +88,8 @@ __device__ __forceinline__ float fold_cover(const ProdJob &J, const int (&gu)[2]
 }
 
 // The same for any cover (narrow tiles) and any count of chunks.
-template <int D, class Tab>
-__device__ __forceinline__ float fold_any(const ProdJob &J, const int (&gu)[2], int g, Tab tch, int part, int parts)
+template <int D, int PARTS, class Tab>
+__device__ __forceinline__ float fold_any(const ProdJob &J, const int (&gu)[2], int g, Tab tch, int part)
 {
     const int W = J.W, T = J.T, ntl = J.ntile[D - 1];
     int tlo[2] = {0, 0}, thi[2] = {0, 0};
@@ -98,7 +101,7 @@ __device__ __forceinline__ float fold_any(const ProdJob &J, const int (&gu)[2], 
     const MOT_GLOBAL float *pat = gp(J.patches);
     const int t2lo = max(0, g - W + T) / T, t2hi = min(ntl - 1, g / T);
     float acc = 0.0f, other = 0.0f;
-    for (int t0 = tlo[0] + part; t0 <= thi[0]; t0 += parts) {
+    for (int t0 = tlo[0] + part; t0 <= thi[0]; t0 += PARTS) {
         for (int t1 = tlo[1]; t1 <= thi[1]; ++t1) {
             int lead_tile = 0, lead_loc = 0;
             if constexpr (D == 3) {
@@ -115,7 +118,7 @@ __device__ __forceinline__ float fold_any(const ProdJob &J, const int (&gu)[2], 
                 for (int ch = ca; ch < cb; ++ch) acc += pat[(int64_t)ch * pe + lc];
             }
         }
-        if (D == 3 && parts == 1) {
+        if (D == 3 && PARTS == 1) {
             const float t = acc;
             acc = other;
             other = t;
@@ -124,18 +127,18 @@ __device__ __forceinline__ float fold_any(const ProdJob &J, const int (&gu)[2], 
     return acc + other;
 }
 
-template <int D, class Tab>
-__device__ __forceinline__ float fold_cell(const ProdJob &J, const int (&gu)[2], int g, Tab tch, int part = 0, int parts = 1)
+template <int D, int PARTS = 1, class Tab>
+__device__ __forceinline__ float fold_cell(const ProdJob &J, const int (&gu)[2], int g, Tab tch, int part = 0)
 {
     // patch entries are addressed in 32 bits by fold_cover
     if (J.T >= 8) {
-        if (J.src_nchunks < (1 << 20)) return fold_cover<D, 2>(J, gu, g, tch, part, parts);
+        if (J.src_nchunks < (1 << 20)) return fold_cover<D, 2, PARTS>(J, gu, g, tch, part);
     } else if (J.T >= 6) {
-        if (J.src_nchunks < (1 << 20)) return fold_cover<D, 3>(J, gu, g, tch, part, parts);
+        if (J.src_nchunks < (1 << 20)) return fold_cover<D, 3, PARTS>(J, gu, g, tch, part);
     } else if (J.T >= 4) {
-        if (J.src_nchunks < (1 << 20)) return fold_cover<D, 4>(J, gu, g, tch, part, parts);
+        if (J.src_nchunks < (1 << 20)) return fold_cover<D, 4, PARTS>(J, gu, g, tch, part);
     }
-    return fold_any<D>(J, gu, g, tch, part, parts);
+    return fold_any<D, PARTS>(J, gu, g, tch, part);
 }
 
 }  // namespace mot
