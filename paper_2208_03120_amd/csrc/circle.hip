@@ -509,8 +509,7 @@ __global__ __launch_bounds__(256) void scale_rows16_kernel(const float *__restri
         m = fmax(m, fabs((double)a4.z * phi[l + 2]));
         m = fmax(m, fabs((double)a4.w * phi[l + 3]));
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = fmax(m, lane_xor(m, o));
+    m = wave_all(m, [](double a, double b) { return fmax(a, b); });
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     const double mm = fmax(fmax(red[0], red[1]), fmax(red[2], red[3]));
@@ -630,8 +629,7 @@ __global__ __launch_bounds__(256) void rowsum_k_kernel(const T *__restrict__ Yg1
     double s = 0.0;
     for (int64_t j = threadIdx.x; j < n1c; j += blockDim.x)
         s += (double)Yg1[i * ld + j] * phi1[j] * (double)Yb1[i * ld + j];
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) s += lane_xor(s, o);
+    s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -673,11 +671,8 @@ __global__ __launch_bounds__(256) void circle_phi_kernel(const double *__restric
             phi[j] = nv;
         }
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        s1 += lane_xor(s1, o);
-        s2 += lane_xor(s2, o);
-    }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
     if ((threadIdx.x & 63) == 0) {
         red[0][threadIdx.x >> 6] = s1;
         red[1][threadIdx.x >> 6] = s2;
@@ -756,8 +751,10 @@ __global__ __launch_bounds__(1024) void colsum_phi_kernel(const T *__restrict__ 
             phi[j] = nv;
         }
     }
-#pragma unroll
-    for (int o = 8; o >= 1; o >>= 1) s1 += lane_xor(s1, o);
+    s1 += lane_xor(s1, 8);
+    s1 += lane_xor(s1, 4);
+    s1 += lane_xor(s1, 2);
+    s1 += lane_xor(s1, 1);
     if (threadIdx.x == 0) {
         s_out[2 * blockIdx.x] = s1;
         s_out[2 * blockIdx.x + 1] = 0.0;
@@ -786,12 +783,9 @@ __global__ __launch_bounds__(1024) void circle_final_kernel(const double *__rest
         s1 += s_part[2 * p];
         s2 += s_part[2 * p + 1];
     }
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        s1 += lane_xor(s1, o);
-        s2 += lane_xor(s2, o);
-        e += lane_xor(e, o);
-    }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    e = wave_sum(e);
     if ((threadIdx.x & 63) == 0) {
         red[0][threadIdx.x >> 6] = s1;
         red[1][threadIdx.x >> 6] = s2;
@@ -854,8 +848,7 @@ __global__ __launch_bounds__(256) void row_exponents_kernel(const double *__rest
             if (v[u] < INFINITY) most = fmax(most, v[u]);
     }
     int m = most > 0.0 ? ilogb(most) : INT32_MIN;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) m = max(m, lane_xor(m, o));
+    m = wave_max_int(m);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
     __syncthreads();
     if (threadIdx.x == 0) rexp[i] = max(max(red[0], red[1]), max(red[2], red[3]));

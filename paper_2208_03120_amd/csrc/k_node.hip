@@ -29,29 +29,6 @@ __device__ __forceinline__ int exp_of(double v)
     return (v > 0.0 && v < INFINITY) ? ilogb(v) : INT32_MIN;
 }
 
-// Written out: in node_kernel<16> the compiler left the loop over the strides standing, with a ladder
-// of branches for each exchange (100000 points, nine children: 22.4 us, 18 with the exchanges
-// through LDS before them, 15.1 written out; 500 points, no children: 4.4 and 3.5 us).
-__device__ __forceinline__ int wave_max_int(int v)
-{
-    v = max(v, lane_xor(v, 32));
-    v = max(v, lane_xor(v, 16));
-    v = max(v, lane_xor(v, 8));
-    v = max(v, lane_xor(v, 4));
-    v = max(v, lane_xor(v, 2));
-    return max(v, lane_xor(v, 1));
-}
-
-__device__ __forceinline__ double wave_sum(double v)
-{
-    v += lane_xor(v, 32);
-    v += lane_xor(v, 16);
-    v += lane_xor(v, 8);
-    v += lane_xor(v, 4);
-    v += lane_xor(v, 2);
-    return v + lane_xor(v, 1);
-}
-
 // Sum over the four wavefronts of a 256-thread group whose wavefronts wrote their sums to red.
 __device__ __forceinline__ double group_sum(const double *red)
 {
