@@ -36,20 +36,20 @@ PEAK_FP32_TFLOPS = 157.3  # dense FP32 MFMA
 # for fold and the FFT passes also of plan.cpp, whose launch item order sets their traffic).
 COPY_MIB = 256
 TRAFFIC = {
-    "spread": {"bytes_per_launch": 231944683, "source": "k_nfft.hip",
-             "sha256": "e95beabf6ee9f74433a7bef0ca9f0ae0990f9eeddcb4f03e4c0070d85db2cefe"},
-    "spread_g3": {"bytes_per_launch": 110942743, "source": "k_nfft.hip",
-                "sha256": "e95beabf6ee9f74433a7bef0ca9f0ae0990f9eeddcb4f03e4c0070d85db2cefe"},
-    "interp": {"bytes_per_launch": 213263908, "source": "k_nfft.hip",
-             "sha256": "e95beabf6ee9f74433a7bef0ca9f0ae0990f9eeddcb4f03e4c0070d85db2cefe"},
-    "fold": {"bytes_per_launch": 61193355, "source": "k_nfft.hip+plan.cpp",
-           "sha256": "a50644c4b46fca7e35a1c7346401ca21e0aaeb0ff38ae98507b4ee0d7e003034"},
-    "fft6": {"bytes_per_launch": 10823506, "source": "k_fft.hip+plan.cpp",
-           "sha256": "b36e97569b327f182bae76981ba8e27a0de1b2b778b57b21267438e78693c3ee"},
-    "fft5": {"bytes_per_launch": 26586437, "source": "k_fft.hip+plan.cpp",
-           "sha256": "b36e97569b327f182bae76981ba8e27a0de1b2b778b57b21267438e78693c3ee"},
-    "fft7": {"bytes_per_launch": 10822049, "source": "k_fft.hip+plan.cpp",
-           "sha256": "b36e97569b327f182bae76981ba8e27a0de1b2b778b57b21267438e78693c3ee"}
+    "spread": {"bytes_per_launch": 231948942, "source": "k_nfft.hip",
+             "sha256": "2a2795ee313b9c72a3657c3c38614d1a18e2fef0f9cee724bd0500b273160b9e"},
+    "spread_g3": {"bytes_per_launch": 110945099, "source": "k_nfft.hip",
+                "sha256": "2a2795ee313b9c72a3657c3c38614d1a18e2fef0f9cee724bd0500b273160b9e"},
+    "interp": {"bytes_per_launch": 201324982, "source": "k_nfft.hip",
+             "sha256": "2a2795ee313b9c72a3657c3c38614d1a18e2fef0f9cee724bd0500b273160b9e"},
+    "fold": {"bytes_per_launch": 61190708, "source": "k_nfft.hip+nfft_device.h+plan.cpp",
+           "sha256": "a865a9e38fb371aa767931a60191f218b0aa0d520db62b92a23e4e48f8794892"},
+    "fft6": {"bytes_per_launch": 10820451, "source": "k_fft.hip+plan.cpp",
+           "sha256": "579e3fd5b8c5d12a3606813f3e26f23d9b3d04b1909cf4f57273acfc7ac754d2"},
+    "fft5": {"bytes_per_launch": 26585388, "source": "k_fft.hip+plan.cpp",
+           "sha256": "579e3fd5b8c5d12a3606813f3e26f23d9b3d04b1909cf4f57273acfc7ac754d2"},
+    "fft7": {"bytes_per_launch": 10818874, "source": "k_fft.hip+plan.cpp",
+           "sha256": "579e3fd5b8c5d12a3606813f3e26f23d9b3d04b1909cf4f57273acfc7ac754d2"}
 }
 
 

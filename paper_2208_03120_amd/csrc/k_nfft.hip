@@ -810,9 +810,7 @@ __global__ __launch_bounds__(64 * kInterpWaves, 4) void interp_kernel(const Prod
 // the point along the lanes.  Each lane weights its four a by the point's w_0,p[a] and the
 // four lane groups are added by two lane exchanges; the four waves' partial sums of a
 // point are added in wave order through LDS after the stage's barrier, and wave 0 stores
-// out = 2^e beta.  (With the bound of 6 blocks per CU the compiler keeps one register pair
-// in scratch, stored once per wavefront and read once per item; the allocation it makes
-// without that spill, under a bound of 5, measured 4 % slower.)
+// out = 2^e beta.  (A bound of 5 blocks per CU measured 4 % slower than 6.)
 __global__ __launch_bounds__(64 * kInterpWaves, 6) void interp3_kernel(const ProdJob *__restrict__ jobs,
                                                                    const int2 *__restrict__ items,
                                                                    int n_items)
