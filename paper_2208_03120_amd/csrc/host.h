@@ -124,11 +124,10 @@ int trunc_row_range(int d, const TruncParams &T, const int cc[3], int B, int ri,
                     int *xa, int *xb);
 // Launch shape of a product; lam_t / lam_s: targets / sources per grid cell; sch =
 // sqrt(log2(e) / eta) h.  FP64: cells per run B and targets per lane R of the cheapest (wide:
-// unused).  Mixed: cells per run, and whether the run is too long for one exponent shift;
-// returns the cost.
+// unused).  Mixed: cells per run; returns the cost.
 void trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, int max_r, double sch, bool fp64,
                       int *B, int *R, int *wide);
-double trunc_choose_mixed(int d, const TruncParams &T, double lam_t, double lam_s, double sch, int *B, int *wide);
+double trunc_choose_mixed(int d, const TruncParams &T, double lam_t, double lam_s, int *B);
 void kappa_B_shifted(double eta, double tau, double eps_B, int p, std::vector<double> &q);
 double kappa_R(double r, double eta, double tau, double eps_B, const std::vector<double> &q);
 void kappa_hat_even(int d, int M, double eta, double tau, double eps_B, int p,

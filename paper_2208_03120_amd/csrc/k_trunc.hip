@@ -19,12 +19,14 @@
 //
 // Mixed precision: the exponents of 16 sources x 16 targets are one 16x16x4 FP64 MFMA.  With
 // c = log2(e) / eta and coordinates relative to the centre of the item's run of cells,
-//   -c |x - y|^2 = -c |x|^2 + r,  r = x.(2 c y) - c |y|^2
-// and r is the contraction of (x, 1) with (2 c y, -c |y|^2); it is rounded to FP32 once, for
-// v_exp_f32.  r lies between c |x|^2 - log2(1 / eps) and c |x|^2, so with the item's shift s (half the
-// largest c |x|^2 of its cells, the MFMA's addend) 2^(r - s) stays in FP32 range up to
-// c |x|^2 = 196 and the factor 2^(s - c |x|^2) is applied once per target; longer runs (WIDE) put
-// every target's -c |x|^2 into the addend.  Values are scaled by 2^-e (e = exponent of max v);
+//   -c |x - y|^2 = -c |x|^2 + x.(2 c y) - c |y|^2
+// is the contraction of (x, 1) with (2 c y, -c |y|^2) on top of the target's -c |x|^2, the MFMA's
+// addend; it is rounded to FP32 once, for v_exp_f32.  It is formed in full, without a part kept
+// back for a factor per target: the largest terms of a sum have exponents near 0 and little
+// rounding, and the smallest, log2(eps) (about -41 at the default target), leave 2^-85 of
+// FP32's range to the values.  (A shift common to a run, half the largest c |x|^2 of its cells,
+// rounds every exponent at the shift's size and takes as much off that range: sparse clouds have
+// shifts up to 98.  It saves registers, 0.5 to 2 % of a launch in 3-D and nothing in 2-D.)  Values are scaled by 2^-e (e = exponent of max v);
 // a lane sums 16 of a stage's 64 sources in FP32 and adds that to its FP64 accumulator.  A
 // pair costs the vector unit a conversion, v_exp_f32 and an FMA, and targets come in tiles of
 // 16 where one per lane left half of the lanes idle in sparse cells.  Star trees in 3-D, time
@@ -108,7 +110,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kSrcPitch = 64 + 8;  // staged component rows, in doubles (LDS banks)
 
-template <int D, bool WIDE>
+template <int D>
 __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const ProdJob *__restrict__ jobs,
                                                                           const int4 *__restrict__ items,
                                                                           int n_items)
@@ -129,14 +131,9 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
         int cc[3];
         trunc_cell<D>(J, itm.y, cc);
         const double c2 = 1.4426950408889634 / J.eta;  // log2(e) / eta
-        double ctr[3] = {0.0, 0.0, 0.0}, half2 = 0.0;    // centre and squared half-diagonal of the run
+        double ctr[3] = {0.0, 0.0, 0.0};  // centre of the run
 #pragma unroll
-        for (int c = 0; c < D; ++c) {
-            const double half = (c == D - 1 ? 0.5 * B : 0.5) * J.h;
-            ctr[c] = J.glo[c] + cc[c] * J.h + half;
-            half2 += half * half;
-        }
-        const double shift = WIDE ? 0.0 : 0.5 * c2 * half2;
+        for (int c = 0; c < D; ++c) ctr[c] = J.glo[c] + (cc[c] + (c == D - 1 ? 0.5 * B : 0.5)) * J.h;
         int e = *gp(J.v_exp);
         if (e == INT32_MIN) e = 0;
         const MOT_GLOBAL double *tgt = gp(J.tgt_pts);
@@ -162,24 +159,21 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
         }
         if (lane == 0) rp[nr] = total;
         wave_sync();
-        // targets: 16-wide tile t, lane l has component l / 16 of target l % 16
-        auto target = [&](int t, double &mine) {  // component of target 16 t + li; returns -c |x|^2
-            const bool act = 16 * t + li < cnt;
-            const int64_t i = (int64_t)itm.z + 16 * t + li;
-            double nrm = 0.0;
-            mine = lk == 3 ? 1.0 : 0.0;
-#pragma unroll
-            for (int c = 0; c < D; ++c) {
-                const double dx = act ? tgt[i * D + c] - ctr[c] : 0.0;
-                if (lk == c) mine = dx;
-                nrm += dx * dx;
-            }
-            return -c2 * nrm;
-        };
+        // targets: 16-wide tile t, lane l has component l / 16 of target l % 16, and its -c |x|^2
         double xt[4], ax[4], acc[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            ax[t] = target(t, xt[t]);
+            const bool act = 16 * t + li < cnt;
+            const int64_t i = (int64_t)itm.z + 16 * t + li;
+            double nrm = 0.0;
+            xt[t] = lk == 3 ? 1.0 : 0.0;
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                const double dx = act ? tgt[i * D + c] - ctr[c] : 0.0;
+                if (lk == c) xt[t] = dx;
+                nrm += dx * dx;
+            }
+            ax[t] = -c2 * nrm;
             acc[t] = 0.0;
         }
         // stages of 64 consecutive list entries; each lane follows its entry's row with a
@@ -223,10 +217,8 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
                     const f32x4 w = reinterpret_cast<const f32x4 *>(sv)[4 * m + lk];
                     f64x4 g[NT];
 #pragma unroll
-                    for (int t = 0; t < NT; ++t) {
-                        const double c0 = WIDE ? ax[t] : -shift;
-                        g[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, xt[t], f64x4{c0, c0, c0, c0}, 0, 0, 0);
-                    }
+                    for (int t = 0; t < NT; ++t)
+                        g[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, xt[t], f64x4{ax[t], ax[t], ax[t], ax[t]}, 0, 0, 0);
 #pragma unroll
                     for (int t = 0; t < NT; ++t)
 #pragma unroll
@@ -250,10 +242,6 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
             double s = acc[t];
             s += lane_xor(s, 16);
             s += lane_xor(s, 32);
-            if constexpr (!WIDE) {
-                double x;
-                s *= exp2(target(t, x) + shift);
-            }
             if (lk == 0 && 16 * t + li < cnt) out[(int64_t)itm.z + 16 * t + li] = ldexp(s, e);
         }
     }
@@ -322,8 +310,7 @@ __global__ __launch_bounds__(64) void trunc_fp64_kernel(const ProdJob *__restric
 }
 
 template <int D>
-static void launch_trunc_d(int precision, int R, int wide, const ProdJob *jobs, const int4 *items, int n_items,
-                           hipStream_t s)
+static void launch_trunc_d(int precision, int R, const ProdJob *jobs, const int4 *items, int n_items, hipStream_t s)
 {
     if (precision == MOT_PREC_FP64) {
         const dim3 grid(n_items < (1 << 20) ? n_items : (1 << 20)), block(64);
@@ -332,21 +319,18 @@ static void launch_trunc_d(int precision, int R, int wide, const ProdJob *jobs, 
     } else {
         const int blocks = (n_items + kTruncWaves - 1) / kTruncWaves;
         const dim3 grid(blocks < (1 << 20) ? blocks : (1 << 20)), block(64 * kTruncWaves);
-        if (wide)
-            hipLaunchKernelGGL((trunc_mixed_kernel<D, true>), grid, block, 0, s, jobs, items, n_items);
-        else
-            hipLaunchKernelGGL((trunc_mixed_kernel<D, false>), grid, block, 0, s, jobs, items, n_items);
+        hipLaunchKernelGGL(trunc_mixed_kernel<D>, grid, block, 0, s, jobs, items, n_items);
     }
 }
 
-hipError_t launch_trunc(int d, int precision, int R, int wide, const ProdJob *jobs_dev, const int4 *items,
-                        int n_items, hipStream_t s)
+hipError_t launch_trunc(int d, int precision, int R, const ProdJob *jobs_dev, const int4 *items, int n_items,
+                        hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
     if (R != 1 && (R != 2 || precision != MOT_PREC_FP64)) return hipErrorInvalidValue;
-    if (d == 1) launch_trunc_d<1>(precision, R, wide, jobs_dev, items, n_items, s);
-    if (d == 2) launch_trunc_d<2>(precision, R, wide, jobs_dev, items, n_items, s);
-    if (d == 3) launch_trunc_d<3>(precision, R, wide, jobs_dev, items, n_items, s);
+    if (d == 1) launch_trunc_d<1>(precision, R, jobs_dev, items, n_items, s);
+    if (d == 2) launch_trunc_d<2>(precision, R, jobs_dev, items, n_items, s);
+    if (d == 3) launch_trunc_d<3>(precision, R, jobs_dev, items, n_items, s);
     return hipGetLastError();
 }
 

@@ -598,10 +598,7 @@ static double trunc_cost_mixed(int d, const TruncParams &T, double lam_t, double
                    expected_chunks(lam_t * B, 16) * src * 8.2);
 }
 
-// Scaled half-diagonal up to which a mixed run's exponents share one shift (k_trunc.hip).
-constexpr double kTruncShiftExtent = 14.0;
-
-double trunc_choose_mixed(int d, const TruncParams &T, double lam_t, double lam_s, double sch, int *B, int *wide)
+double trunc_choose_mixed(int d, const TruncParams &T, double lam_t, double lam_s, int *B)
 {
     double best = -1.0;
     *B = 1;
@@ -613,7 +610,6 @@ double trunc_choose_mixed(int d, const TruncParams &T, double lam_t, double lam_
             *B = b;
         }
     }
-    *wide = run_extent(d, T, sch, *B) > kTruncShiftExtent;
     return best;
 }
 
@@ -685,7 +681,7 @@ int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params
             cost = trunc_cost(d, C, lam, lam, C.B, C.R, wide != 0);
         } else {
             C.R = 1;
-            cost = trunc_choose_mixed(d, C, lam, lam, sch, &C.B, &wide);
+            cost = trunc_choose_mixed(d, C, lam, lam, &C.B);
         }
         if (best < 0 || cost < best) {
             best = cost;

@@ -221,7 +221,7 @@ int run_steps(const std::vector<Step> &steps, hipStream_t s0, const Lanes *lanes
             MOT_HIP(launch_fill_int(st.fill_ptr, st.fill_value, st.fill_count, s));
             break;
         case ST_TRUNC:
-            MOT_HIP(launch_trunc(st.d, st.precision, st.trunc_r, st.diff, (const ProdJob *)st.jobs,
+            MOT_HIP(launch_trunc(st.d, st.precision, st.trunc_r, (const ProdJob *)st.jobs,
                                  (const int4 *)st.items, st.n_items, s));
             break;
         }
@@ -382,7 +382,7 @@ struct StepBuilder {
     {
         std::map<std::tuple<int, int, int, bool>, std::vector<int4>> direct;  // (d, precision, diff, small)
         std::map<std::tuple<int, int, int, bool>, std::vector<int2>> direct_red;  // range sums
-        std::map<std::tuple<int, int, int, int>, std::vector<std::pair<double, int4>>> trunc;  // (d, prec, R, wide)
+        std::map<std::tuple<int, int, int>, std::vector<std::pair<double, int4>>> trunc;  // (d, prec, R)
         std::map<int, std::vector<int2>> spread, fold, interp;   // d
         // 3-D spreading: jobs by the points they spread from (a binned marginal's rows)
         std::map<const float *, std::vector<int>> spread3_src;
@@ -417,7 +417,7 @@ struct StepBuilder {
             if (J.path == MOT_TRUNC) {
                 // items of at most 64 R targets from a run of B consecutive cells of one
                 // row (contiguous in the sorted order), costed by the sources they scan
-                auto &v = trunc[std::make_tuple(J.d, J.precision, J.trunc_r, J.diff)];
+                auto &v = trunc[std::make_tuple(J.d, J.precision, J.trunc_r)];
                 TruncParams TQ;
                 TQ.nc = J.nc;
                 TQ.w = J.tw;
@@ -518,7 +518,6 @@ struct StepBuilder {
             st.d = std::get<0>(kv.first);
             st.precision = std::get<1>(kv.first);
             st.trunc_r = std::get<2>(kv.first);
-            st.diff = std::get<3>(kv.first);
             st.jobs = jobs_dev;
             st.items = upload(its);
             st.n_items = (int)its.size();
@@ -1171,17 +1170,18 @@ int mot::make_prod_job(mot_plan_s *P, int t, int s, const double *v, int32_t *sl
         Q.h = T.h;
         Q.q2 = T.q2;
         for (int c = 0; c < 3; ++c) Q.glo[c] = T.glo[c];
-        // run length, targets per lane and exponent form from the cost model at this pair's
-        // densities (points per grid cell)
+        // run length and targets per lane from the cost model at this pair's densities (points
+        // per grid cell)
         double cells = 1.0;  // full cells covering the cloud's box
         for (int c = 0; c < P->d; ++c) cells *= T.box_cells[c];
         const double lam_t = (double)Q.nt / cells, lam_s = (double)Q.ns / cells;
-        const double sch = std::sqrt(1.4426950408889634 / Q.eta) * T.h;
         if (P->precision == MOT_PREC_FP64) {
-            trunc_choose_run(P->d, T, lam_t, lam_s, 2, sch, true, &Q.trunc_b, &Q.trunc_r, &Q.diff);
+            int wide = 0;
+            trunc_choose_run(P->d, T, lam_t, lam_s, 2, std::sqrt(1.4426950408889634 / Q.eta) * T.h, true, &Q.trunc_b,
+                             &Q.trunc_r, &wide);
         } else {
             Q.trunc_r = 1;
-            (void)trunc_choose_mixed(P->d, T, lam_t, lam_s, sch, &Q.trunc_b, &Q.diff);
+            (void)trunc_choose_mixed(P->d, T, lam_t, lam_s, &Q.trunc_b);
         }
         return MOT_OK;
     }
