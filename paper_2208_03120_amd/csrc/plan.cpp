@@ -870,35 +870,46 @@ int tree_steps(const std::vector<TreeRef> &refs, const std::vector<ProdJob> &pj,
     for (auto &r : refs) maxD = std::max(maxD, r.P->depth_max);
     // Lanes of a batched sweep: plans do not depend on each other, so kLanes lanes of them,
     // balanced by their points, run on their own streams between the fork and the
-    // finalisation, and one lane's latency-bound passes overlap another's spreading and
+    // finalisation, at most, and one lane's latency-bound passes overlap another's spreading and
     // interpolation.  (Splitting one plan's root subtrees the same way measured slower: the
     // lanes' launches hold a fraction of the jobs each.)  Plan r is in lane lane[r].
-    const int nl = (int)std::min<size_t>(refs.size(), std::max(1, std::min(max_lanes, kLanes)));
+    int nl = (int)std::min<size_t>(refs.size(), std::max(1, std::min(max_lanes, kLanes)));
     std::vector<int> lane(refs.size(), 0);
     {
         // The kernels of the passes differ by dimension, so a lane of several dimensions has two to
         // three times the launches of a lane of one, and a lane's launches wait for each other: with
         // enough lanes each dimension has its own, and the others go one by one to the dimension
-        // with the most work to a lane.  Ten sweeps of 24 trees of 1000 to 50000 points: 19.6 ms
-        // with every dimension in each of four lanes, 16.1 ms here (17.6 with three lanes, 19.0
-        // with six); of 300 to 4000 points 16.1 and 10.1 ms.
+        // with the most work to a lane among those with more plans than lanes.  Ten sweeps of 24
+        // trees of 1000 to 50000 points: 19.6 ms with every dimension in each of four lanes, 15.2
+        // here (16.1 with three lanes).
+        // A lane more adds its launches, some 4 us each, and is worth them from kLaneWork on (work of
+        // all 3-D plans of a batch, one lane and two for them, ten sweeps; beside 1-D and 2-D plans
+        // 1.0e6: 8.7 and 10.2 ms, 3.1e6: 11.1 and 12.2, 5.2e6: 13.3 and 12.6, 8.7e6: 16.1 and 15.2;
+        // beside 2-D plans alone 1.0e6: 3.1 and 4.7, 3.1e6: 5.5 and 5.2 ms).
+        constexpr double kLaneWork = 3e6;
         const double cost[4] = {0.0, 1.0, 2.0, 8.0};  // of a point's window taps, by dimension
         double work[4] = {0.0, 0.0, 0.0, 0.0};
-        int lanes_of[4] = {0, 0, 0, 0}, first[4] = {0, 0, 0, 0}, dims = 0;
+        int lanes_of[4] = {0, 0, 0, 0}, plans_of[4] = {0, 0, 0, 0}, first[4] = {0, 0, 0, 0}, dims = 0;
         std::vector<double> pts(refs.size(), 0.0);
         for (size_t r = 0; r < refs.size(); ++r) {
             const int d = refs[r].P->d;
             for (int k = 0; k < refs[r].P->K; ++k) pts[r] += cost[d] * (double)refs[r].P->marg[k].n;
             if (!lanes_of[d]) ++dims;
             lanes_of[d] = 1;
+            ++plans_of[d];
             work[d] += pts[r];
         }
         const bool apart = dims > 1 && nl >= dims;
-        for (int more = nl - dims; apart && more > 0; --more) {
-            int most = 1;
-            for (int d = 2; d <= 3; ++d)
-                if (work[d] * lanes_of[most] > work[most] * lanes_of[d]) most = d;
+        for (int used = dims; apart && used < nl;) {
+            int most = 0;
+            for (int d = 1; d <= 3; ++d)
+                if (lanes_of[d] < plans_of[d] && (!most || work[d] * lanes_of[most] > work[most] * lanes_of[d])) most = d;
+            if (!most || work[most] < kLaneWork * lanes_of[most]) {
+                nl = used;
+                break;
+            }
             ++lanes_of[most];
+            ++used;
         }
         first[2] = lanes_of[1];
         first[3] = lanes_of[1] + lanes_of[2];

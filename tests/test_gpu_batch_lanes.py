@@ -34,3 +34,29 @@ def test_lanes_by_dimension(dims):
     batch.close()
     for p in plans:
         p.close()
+
+
+@pytest.mark.parametrize("dims,sizes,lanes", [
+    ([2, 3, 3], [400, 90000, 90000], [2, 3, 3]),        # no 1-D plan; the 3-D plans are worth two lanes
+    ([2, 2, 3, 3], [400, 400, 90000, 90000], [2, 3, 3]),
+    ([2, 2, 3, 3], [400, 400, 400, 400], [2, 3]),       # too little work for a lane more
+    ([1, 1, 3], [400, 400, 180000], [1, 3]),            # most work in a dimension of one plan
+])
+def test_lanes_beyond_one_a_dimension(dims, sizes, lanes):
+    """A lane's launches are those of one of its plans, as trees of one shape share theirs; the
+    finalisation is shared by all lanes."""
+    from paper_2208_03120_amd import mot
+    plans, own = [], {}
+    for i, (d, n) in enumerate(zip(dims, sizes)):
+        inst = W.make_instance(np.random.Generator(np.random.PCG64(i)), 3, [n] * 3, d, W.TREE, 0.1,
+                               parent=W.star_parent(3))
+        plans.append(mot.Plan(inst.points, inst.weights, W.TREE, inst.parent, inst.eta, path=mot.NFFT))
+        alone = mot.Batch(plans[-1:])
+        own[d] = alone.launches() - 1
+        alone.close()
+    batch = mot.Batch(plans)
+    launches = batch.launches() - 1
+    batch.close()
+    for p in plans:
+        p.close()
+    assert launches == sum(own[d] for d in lanes)
