@@ -1326,7 +1326,7 @@ size_t circle_footprint(int K, const int64_t *n, int path, int precision)
         b += (size_t)ldmax * ldmax * 2 * (2 * (K - 2)) * parts;  // kernel matrices
         b += (size_t)n1 * ldmax * 2 * parts;                       // scaled left operand
     }
-    else b += (size_t)n1 * ldmax * 8 + (size_t)n1 * 8;  // product sources, row exponents
+    else b += (size_t)n1 * 8;  // row exponents
     b += (size_t)((n[0] + kColRowsMin - 1) / kColRowsMin) * ldmax * 8;  // column-sum partials
     return b;
 }
