@@ -122,12 +122,9 @@ int64_t trunc_cells(int d, const TruncParams &T);  // nc^d
 // host mirror of the kernel's neighbour rows of a run of B cells starting at cc
 int trunc_row_range(int d, const TruncParams &T, const int cc[3], int B, int ri, int64_t *row_base,
                     int *xa, int *xb);
-// Launch shape of a product; lam_t / lam_s: targets / sources per grid cell; sch =
-// sqrt(log2(e) / eta) h.  FP64: cells per run B and targets per lane R of the cheapest (wide:
-// unused).  Mixed: cells per run; returns the cost.
-void trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, int max_r, double sch, bool fp64,
-                      int *B, int *R, int *wide);
-double trunc_choose_mixed(int d, const TruncParams &T, double lam_t, double lam_s, int *B);
+// Cheapest launch shape of a product and its modelled cost: cells per run B and targets per
+// lane R (1 in mixed precision, 1 or 2 in FP64); lam_t / lam_s: targets / sources per grid cell.
+double trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, int precision, int *B, int *R);
 void kappa_B_shifted(double eta, double tau, double eps_B, int p, std::vector<double> &q);
 double kappa_R(double r, double eta, double tau, double eps_B, const std::vector<double> &q);
 void kappa_hat_even(int d, int M, double eta, double tau, double eps_B, int p,

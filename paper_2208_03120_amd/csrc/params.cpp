@@ -568,24 +568,16 @@ static void trunc_run_sources(int d, const TruncParams &T, double lam_s, int B, 
     *runs_out = runs;
 }
 
-// Modelled wave cycles of one FP64 product (and the model its cell side is chosen with): per row ~100, per 64-source stage ~200, per source
-// and target slot ~40 (FP32 coordinate differences) or ~66 (FP64 exponent).  Points are
-// taken as Poisson counts per cell: lam_t / lam_s targets / sources per full cell (the
-// cloud's density times h^d).  A run of B cells holding k targets takes ceil(k / 64R)
-// items; the runs are those of the cells covering the cloud's box.
-static double trunc_cost(int d, const TruncParams &T, double lam_t, double lam_s, int B, int R, bool wide)
+// Modelled wave cycles of one FP64 product: per row ~100, per 64-source stage ~200, per source
+// and target slot ~66.  Points are taken as Poisson counts per cell: lam_t / lam_s targets /
+// sources per full cell (the cloud's density times h^d).  A run of B cells holding k targets
+// takes ceil(k / 64R) items; the runs are those of the cells covering the cloud's box.
+static double trunc_cost_fp64(int d, const TruncParams &T, double lam_t, double lam_s, int B, int R)
 {
     double rows, src, runs;
     trunc_run_sources(d, T, lam_s, B, &rows, &src, &runs);
     const double items = runs * expected_chunks(lam_t * B, 64 * R);
-    return items * (rows * 100.0 + (src / 64.0 + rows) * 200.0 + src * R * (wide ? 66.0 : 40.0));
-}
-
-// sqrt(log2(e) / eta) times the half-diagonal of a run of B cells: the largest scaled
-// coordinate of a target relative to the run's centre.  The FP32 form is used up to 3.
-static double run_extent(int d, const TruncParams &T, double sch, int B)
-{
-    return sch * std::sqrt(0.25 * B * B + 0.25 * (d - 1));
+    return items * (rows * 100.0 + (src / 64.0 + rows) * 200.0 + src * R * 66.0);
 }
 
 // The same for a mixed product: per row ~100 and per 64-source stage ~300 of an item of up to
@@ -598,44 +590,24 @@ static double trunc_cost_mixed(int d, const TruncParams &T, double lam_t, double
                    expected_chunks(lam_t * B, 16) * src * 8.2);
 }
 
-double trunc_choose_mixed(int d, const TruncParams &T, double lam_t, double lam_s, int *B)
-{
-    double best = -1.0;
-    *B = 1;
-    for (int b : {1, 2, 3, 4, 6, 8, 12, 16}) {
-        if (b > T.nc) break;
-        const double c = trunc_cost_mixed(d, T, lam_t, lam_s, b);
-        if (best < 0 || c < best) {
-            best = c;
-            *B = b;
-        }
-    }
-    return best;
-}
-
-void trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, int max_r, double sch, bool fp64,
-                      int *B, int *R, int *wide)
+double trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, int precision, int *B, int *R)
 {
     double best = -1.0;
     *B = 1;
     *R = 1;
-    *wide = 0;
     for (int b : {1, 2, 3, 4, 6, 8, 12, 16}) {
         if (b > T.nc) break;
-        for (int r : {1, 2, 4}) {
-            if (r > max_r) break;
-            for (int w = 0; w < 2; ++w) {
-                if (!fp64 && w == 0 && run_extent(d, T, sch, b) > 3.0) continue;
-                const double c = trunc_cost(d, T, lam_t, lam_s, b, r, fp64 || w == 1);
-                if (best < 0 || c < best) {
-                    best = c;
-                    *B = b;
-                    *R = r;
-                    *wide = fp64 ? 0 : w;
-                }
+        for (int r = 1; r <= (precision == MOT_PREC_FP64 ? 2 : 1); ++r) {
+            const double c = precision == MOT_PREC_FP64 ? trunc_cost_fp64(d, T, lam_t, lam_s, b, r)
+                                                        : trunc_cost_mixed(d, T, lam_t, lam_s, b);
+            if (best < 0 || c < best) {
+                best = c;
+                *B = b;
+                *R = r;
             }
         }
     }
+    return best;
 }
 
 int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params *fs, double n_mean,
@@ -673,16 +645,7 @@ int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params
             Vb *= wc;
         }
         const double lam = std::max(n_mean, 1.0) * std::pow(C.h, d) / Vb;  // points per full cell
-        const double sch = std::sqrt(1.4426950408889634 / eta) * C.h;
-        int wide = 0;
-        double cost;
-        if (precision == MOT_PREC_FP64) {
-            trunc_choose_run(d, C, lam, lam, 4, sch, false, &C.B, &C.R, &wide);
-            cost = trunc_cost(d, C, lam, lam, C.B, C.R, wide != 0);
-        } else {
-            C.R = 1;
-            cost = trunc_choose_mixed(d, C, lam, lam, &C.B);
-        }
+        const double cost = trunc_choose_run(d, C, lam, lam, precision, &C.B, &C.R);
         if (best < 0 || cost < best) {
             best = cost;
             *out = C;

@@ -1186,14 +1186,7 @@ int mot::make_prod_job(mot_plan_s *P, int t, int s, const double *v, int32_t *sl
         double cells = 1.0;  // full cells covering the cloud's box
         for (int c = 0; c < P->d; ++c) cells *= T.box_cells[c];
         const double lam_t = (double)Q.nt / cells, lam_s = (double)Q.ns / cells;
-        if (P->precision == MOT_PREC_FP64) {
-            int wide = 0;
-            trunc_choose_run(P->d, T, lam_t, lam_s, 2, std::sqrt(1.4426950408889634 / Q.eta) * T.h, true, &Q.trunc_b,
-                             &Q.trunc_r, &wide);
-        } else {
-            Q.trunc_r = 1;
-            (void)trunc_choose_mixed(P->d, T, lam_t, lam_s, &Q.trunc_b);
-        }
+        (void)trunc_choose_run(P->d, T, lam_t, lam_s, P->precision, &Q.trunc_b, &Q.trunc_r);
         return MOT_OK;
     }
     if (P->path != MOT_NFFT) return MOT_OK;

@@ -54,3 +54,20 @@ def test_sweeps(d, eta, side):
     ophi, oS, _, _ = oracle.tree_sinkhorn(pts, wts, [-1, 0], eta, 12)
     assert max_rel(gauge_fix(phi, wts), gauge_fix(ophi, wts)) < 1e-5
     np.testing.assert_allclose(S, oS, rtol=1e-5)
+
+
+@pytest.mark.parametrize("d,n,eta", [(2, 1000, 0.5), (2, 9000, 0.03), (3, 3000, 0.1), (3, 3000, 1e-3), (1, 5000, 1e-4)])
+def test_fp64_launch_shape(d, n, eta):
+    """FP64 plans report a launch shape that their kernel has (one or two targets per lane), and
+    their products hold the cutoff's bracket."""
+    from paper_2208_03120_amd import mot
+    r, pts, wts = clouds(320 + d, n, d, 0.5)
+    plan = mot.Plan(pts, wts, W.TREE, [-1, 0], eta, path=mot.TRUNC, precision=mot.PREC_FP64)
+    info = plan.info()
+    _, rc = cutoff(pts, eta)
+    v = r.uniform(0.5, 1.5, n)
+    got = plan.apply(0, 1, v)
+    plan.close()
+    assert info["m"] in (1, 2)
+    assert np.all(got >= oracle.kernel_apply_truncated(pts[0], pts[1], v, eta, rc) * (1 - 1e-12))
+    assert np.all(got <= oracle.kernel_apply(pts[0], pts[1], v, eta) * (1 + 1e-12))
