@@ -23,7 +23,7 @@
 //   2 FUSE spec1[H][B][L0]       -> spec0[L0][H][B]      (axis 0: forward, multiply, inverse)
 //   3 INV  spec0[L0][H][B]       -> spec1[L0][L1][H]     (axis 1)
 //   4 C2R  spec1[L0][L1][H]      -> grid[L0][L1][L2]     (axis 2, Hermitian half spectrum)
-// 2-D uses 0, 2, 4 and 1-D uses 0 and 4 (which then applies the multiplier).
+// 2-D uses 0, 2, 4 where launch_plane does not take the job; 1-D is always launch_plane's.
 //
 // When a box slab's half spectrum fits in LDS, 3-D uses three passes instead:
 //   6 SLAB grid[L0][L1][L2]  -> spec1[L0][H][B]   (per slab g0: R2C axis 2, FWD axis 1)
@@ -155,13 +155,10 @@ __device__ __forceinline__ PassGeom pass_geom(const ProdJob &J)
         if (KIND == 2 || KIND == 5) { P.A2 = H; P.A1 = B; P.LA = J.L[0]; P.lo_in = J.lo[0]; P.Kout = J.L[0]; P.lo_out = J.lo[0]; P.in_c = J.spec1; P.out_c = J.spec0; }
         if (KIND == 3) { P.A2 = J.L[0]; P.A1 = H; P.LA = B; P.Kout = J.L[1]; P.lo_out = J.lo[1]; P.in_c = J.spec0; P.out_c = J.spec1; }
         if (KIND == 4) { P.A2 = J.L[0]; P.A1 = J.L[1]; P.LA = H; P.Kout = J.L[2]; P.lo_out = J.lo[2]; P.in_c = J.spec1; }
-    } else if (J.d == 2) {
+    } else {
         if (KIND == 0) { P.A2 = 1; P.A1 = J.L[0]; P.LA = J.L[1]; P.lo_in = J.lo[1]; P.Kout = H; P.out_c = J.spec0; }
         if (KIND == 2) { P.A2 = 1; P.A1 = H; P.LA = J.L[0]; P.lo_in = J.lo[0]; P.Kout = J.L[0]; P.lo_out = J.lo[0]; P.in_c = J.spec0; P.out_c = J.spec1; }
         if (KIND == 4) { P.A2 = 1; P.A1 = J.L[0]; P.LA = H; P.Kout = J.L[1]; P.lo_out = J.lo[1]; P.in_c = J.spec1; }
-    } else {
-        if (KIND == 0) { P.A2 = 1; P.A1 = 1; P.LA = J.L[0]; P.lo_in = J.lo[0]; P.Kout = H; P.out_c = J.spec0; }
-        if (KIND == 4) { P.A2 = 1; P.A1 = 1; P.LA = H; P.Kout = J.L[0]; P.lo_out = J.lo[0]; P.in_c = J.spec0; }
     }
     return P;
 }
@@ -221,13 +218,9 @@ __device__ __forceinline__ void fft_pass_item(const ProdJob &J, const int4 itm, 
                             const int la = a10 + 2 * li, lb = la + 1;
                             const int fa = fs >= 0 ? fs : -fs;
                             if (fa <= M) {
-                                float2 A = ld2(P.in_c, ((int64_t)a2 * P.A1 + la) * P.LA + fa);
-                                float2 Bv = lb < a10 + nl ? ld2(P.in_c, ((int64_t)a2 * P.A1 + lb) * P.LA + fa)
-                                                          : make_float2(0.0f, 0.0f);
-                                if (J.d == 1) {
-                                    const float dm = gp(J.D)[fa];
-                                    A.x *= dm; A.y *= dm; Bv.x *= dm; Bv.y *= dm;
-                                }
+                                const float2 A = ld2(P.in_c, ((int64_t)a2 * P.A1 + la) * P.LA + fa);
+                                const float2 Bv = lb < a10 + nl ? ld2(P.in_c, ((int64_t)a2 * P.A1 + lb) * P.LA + fa)
+                                                                : make_float2(0.0f, 0.0f);
                                 if (fa == 0) {
                                     v = make_float2(A.x, Bv.x);
                                 } else if (fs > 0) {
@@ -558,7 +551,8 @@ __global__ __launch_bounds__(kSlabThreads) void fft_slab_mixed_kernel(const Prod
 template <int N>
 static hipError_t launch_n(int kind, const ProdJob *jobs, const int4 *items, int n_items,
                            const float2 *tw, hipStream_t s)
-{    const int grid = n_items < 8192 ? n_items : 8192;
+{
+    const int grid = n_items < 8192 ? n_items : 8192;
     switch (kind) {
     case 0: hipLaunchKernelGGL((fft_pass_kernel<N, 0>), dim3(grid), dim3(256), 0, s, jobs, items, n_items, tw); break;
     case 1: hipLaunchKernelGGL((fft_pass_kernel<N, 1>), dim3(grid), dim3(256), 0, s, jobs, items, n_items, tw); break;

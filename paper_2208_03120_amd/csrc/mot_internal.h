@@ -339,6 +339,7 @@ constexpr int64_t plane_lds(int d, int n, const int32_t *L, int M)
     const PlaneGeom P(L[0], L[1], M);
     return (int64_t)8 * n + 4 * ((int64_t)P.ry + P.xz);
 }
+static_assert(8 * kMaxN + 4 * (kMaxN + 1) + 8 * (kMaxN / 2 + 1) <= kPlaneLds, "every 1-D job fits");
 // MFMAs of a 2-D job on that path.
 constexpr int64_t plane_mfmas(const int32_t *L, int M)
 {

@@ -367,12 +367,9 @@ struct StepBuilder {
             const int a1[5] = {J.L[1], J.L[0], B, H, J.L[1]};
             *A2 = a2[kind];
             *A1 = a1[kind];
-        } else if (J.d == 2) {
-            *A2 = 1;
-            *A1 = kind == 2 ? H : J.L[0];
         } else {
             *A2 = 1;
-            *A1 = 1;
+            *A1 = kind == 2 ? H : J.L[0];
         }
     }
 
@@ -478,9 +475,9 @@ struct StepBuilder {
             max_patch[J.d] = std::max(max_patch[J.d], pe);
             // 3-D boxes whose slab half spectrum fits in LDS take the three-pass chain
             const bool slab = J.d == 3 && (int64_t)J.L[1] * (J.M + 1) * 8 <= kSlabLds;
-            const int kinds3[5] = {0, 1, 2, 3, 4}, kinds2[3] = {0, 2, 4}, kinds1[2] = {0, 4};
-            const int *kinds = J.d == 3 ? kinds3 : (J.d == 2 ? kinds2 : kinds1);
-            const int nk = J.d == 3 ? 5 : (J.d == 2 ? 3 : 2);
+            const int kinds3[5] = {0, 1, 2, 3, 4}, kinds2[3] = {0, 2, 4};
+            const int *kinds = J.d == 3 ? kinds3 : kinds2;
+            const int nk = J.d == 3 ? 5 : 3;
             if (plane) {
                 planes.push_back(make_int2(j, plane_fold ? 1 : 0));
                 plane_bytes = std::max(plane_bytes, (int)plane_lds(J.d, J.n, J.L, J.M));
@@ -2097,7 +2094,7 @@ static int64_t fft_items_of(int d, int n, int M, const int L[3])
         const int per = mot::fft_lines_per_item(kind, n);
         return a2 * ((a1 + per - 1) / per);
     };
-    if (d == 1) return 2;
+    if (d == 1) return 0;  // launch_plane's
     if (d == 2) return items(0, 1, L[0]) + items(2, 1, H) + items(4, 1, L[0]);
     if ((int64_t)L[1] * H * 8 <= mot::kSlabLds) return 2 * (int64_t)L[0] + items(5, H, B);
     return items(0, L[0], L[1]) + items(1, H, L[0]) + items(2, H, B) + items(3, L[0], H) + items(4, L[0], L[1]);
