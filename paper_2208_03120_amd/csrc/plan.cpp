@@ -1785,6 +1785,7 @@ int mot_sinkhorn(mot_plan P, int32_t max_sweeps, double delta_S, double tol_marg
     const bool stopping = delta_S > 0.0 || tol_marginal > 0.0;
     int done = 0, status = MOT_MAXITER;
     double lastS = NAN, lastE = NAN;
+    if (max_sweeps == 0) MOT_HIP(hipStreamSynchronize(P->stream));  // as after the last sweeps below
     while (done < max_sweeps) {
         const int batch = stopping ? std::min(check_every, max_sweeps - done) : max_sweeps - done;
         int rc = P->topology == MOT_TREE ? tree_run_sweeps(P, batch, use_graphs())
