@@ -321,8 +321,9 @@ __global__ __launch_bounds__(256, 4) void direct_mixed_kernel(const ProdJob *__r
             ax[t] = -c2 * nrm;
             acc[t] = 0.0;
         }
-        // source tid of the next stage, loaded one stage ahead
-        double ly[3] = {0.0, 0.0, 0.0}, lv = 0.0;
+        // source tid of the next stage, loaded one stage ahead; places past the range's end hold the
+        // centre or a source of before, whose exponents are finite, with the value 0
+        double ly[3] = {J.ctr[0], J.ctr[1], J.ctr[2]}, lv = 0.0;
         auto fetch = [&](int64_t j) {
             lv = 0.0;
             if (j < jb) {
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(64 * kSmallWaves) void direct_mixed_small_kernel(co
         const int ns = (int)J.ns;
         const int per = (ns + 16 * kSmallWaves - 1) / (16 * kSmallWaves) * 16;
         const int ja = min(ns, wave * per), jb = min(ns, ja + per);
-        double ly[3] = {0.0, 0.0, 0.0}, lv = 0.0;
+        double ly[3] = {J.ctr[0], J.ctr[1], J.ctr[2]}, lv = 0.0;  // past the end: as above
         auto fetch = [&](int j) {
             lv = 0.0;
             if (j < jb) {

@@ -179,7 +179,7 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
         // stages of 64 consecutive list entries; each lane follows its entry's row with a
         // pointer that only moves forward, and loads its source one stage ahead
         int row = 0;
-        double ly[3] = {0.0, 0.0, 0.0}, lv = 0.0;
+        double ly[3] = {ctr[0], ctr[1], ctr[2]}, lv = 0.0;
         auto fetch = [&](int q) {
             lv = 0.0;
             if (q < total) {
@@ -197,7 +197,9 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
                 const int steps = (min(64, total - s0) + 15) >> 4;
                 wave_sync();
                 {
-                    double nrm = 0.0;  // entries past the list's end have the value 0
+                    // entries past the list's end have the value 0 and the place of the run's centre
+                    // or of a source of before, whose exponents are finite
+                    double nrm = 0.0;
 #pragma unroll
                     for (int c = 0; c < 3; ++c) {
                         const double dy = c < D ? ly[c] - ctr[c] : 0.0;
