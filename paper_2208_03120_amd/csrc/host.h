@@ -119,9 +119,12 @@ int build_box(int d, const Extent &ext, NfftParams *P);
 int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params *fs,
                   double n_mean, int precision, TruncParams *out);
 int64_t trunc_cells(int d, const TruncParams &T);  // nc^d
-// host mirror of the kernel's neighbour rows of a run of B cells starting at cc
-int trunc_row_range(int d, const TruncParams &T, const int cc[3], int B, int ri, int64_t *row_base,
-                    int *xa, int *xb);
+// The kernel's neighbour rows of a run of cells: offsets in the leading coordinates and the
+// cells reached beyond the run along the last one.
+struct TruncRow {
+    int del[2], wl;
+};
+std::vector<TruncRow> trunc_rows(int d, int w, double q2);
 // Cheapest launch shape of a product and its modelled cost: cells per run B and targets per
 // lane R (1 in mixed precision, 1 or 2 in FP64); lam_t / lam_s: targets / sources per grid cell.
 double trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, int precision, int *B, int *R);

@@ -500,33 +500,17 @@ int64_t trunc_cells(int d, const TruncParams &T)
     return c;
 }
 
-int trunc_row_range(int d, const TruncParams &T, const int cc[3], int B, int ri, int64_t *row_base,
-                    int *xa, int *xb)
+std::vector<TruncRow> trunc_rows(int d, int w, double q2)
 {
-    const int w = T.w, span = 2 * w + 1;
-    int del[2] = {0, 0};
-    if (d == 3) {
-        del[0] = ri / span - w;
-        del[1] = ri % span - w;
-    } else if (d == 2) {
-        del[0] = ri - w;
-    }
-    double used = 0.0;
-    int64_t base = 0;
-    for (int c = 0; c < d - 1; ++c) {
-        const int x = cc[c] + del[c];
-        if (x < 0 || x >= T.nc) return 0;
-        const int e = std::abs(del[c]) - 1;
-        if (e > 0) used += (double)e * e;
-        base = base * T.nc + x;
-    }
-    const double rem = T.q2 - used;
-    if (rem < 0.0) return 0;
-    const int wl = std::min(w, 1 + (int)std::floor(std::sqrt(rem)));
-    *row_base = base * T.nc;
-    *xa = std::max(cc[d - 1] - wl, 0);
-    *xb = std::min(cc[d - 1] + B - 1 + wl, T.nc - 1);
-    return 1;
+    const int w0 = d > 1 ? w : 0, w1 = d > 2 ? w : 0;
+    std::vector<TruncRow> rows;
+    for (int a = -w0; a <= w0; ++a)
+        for (int b = -w1; b <= w1; ++b) {
+            const int ea = std::max(std::abs(a) - 1, 0), eb = std::max(std::abs(b) - 1, 0);
+            const double rem = q2 - ((double)ea * ea + (double)eb * eb);
+            if (rem >= 0.0) rows.push_back({{a, b}, std::min(w, 1 + (int)std::floor(std::sqrt(rem)))});
+        }
+    return rows;
 }
 
 // E[ceil(X / cap)] for a Poisson count X with mean lam (pmf in log space).
@@ -547,23 +531,13 @@ static double expected_chunks(double lam, int cap)
 static void trunc_run_sources(int d, const TruncParams &T, double lam_s, int B, double *rows_out, double *src_out,
                               double *runs_out)
 {
-    const int span = 2 * T.w + 1;
-    const int rows_total = d == 1 ? 1 : (d == 2 ? span : span * span);
-    TruncParams U = T;
-    U.nc = 1 << 20;  // no clipping at the grid edge
-    const int cc[3] = {1 << 19, 1 << 19, 1 << 19};
-    double cells = 0.0, rows = 0.0;
-    for (int ri = 0; ri < rows_total; ++ri) {
-        int64_t base;
-        int xa, xb;
-        if (!trunc_row_range(d, U, cc, B, ri, &base, &xa, &xb)) continue;
-        rows += 1.0;
-        cells += xb - xa + 1;
-    }
+    const std::vector<TruncRow> rows = trunc_rows(d, T.w, T.q2);
+    double cells = 0.0;
+    for (const TruncRow &r : rows) cells += B + 2 * r.wl;
     double runs = 1.0;
     for (int c = 0; c < d - 1; ++c) runs *= T.box_cells[c];
     runs *= std::ceil(T.box_cells[d - 1] / B);
-    *rows_out = rows;
+    *rows_out = (double)rows.size();
     *src_out = cells * lam_s;
     *runs_out = runs;
 }

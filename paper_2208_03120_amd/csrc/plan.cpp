@@ -415,15 +415,10 @@ struct StepBuilder {
                 // items of at most 64 R targets from a run of B consecutive cells of one
                 // row (contiguous in the sorted order), costed by the sources they scan
                 auto &v = trunc[std::make_tuple(J.d, J.precision, J.trunc_r)];
-                TruncParams TQ;
-                TQ.nc = J.nc;
-                TQ.w = J.tw;
-                TQ.q2 = J.q2;
+                const std::vector<TruncRow> rows = trunc_rows(J.d, J.tw, J.q2);
                 int64_t nrow_cells = 1;
                 for (int c = 0; c < J.d - 1; ++c) nrow_cells *= J.nc;
                 const int cap = 64 * J.trunc_r;
-                const int span = 2 * J.tw + 1;
-                const int nrows = J.d == 1 ? 1 : (J.d == 2 ? span : span * span);
                 for (int64_t row = 0; row < nrow_cells; ++row)
                     for (int x0 = 0; x0 < J.nc; x0 += J.trunc_b) {
                         const int B = std::min(J.trunc_b, J.nc - x0);
@@ -437,10 +432,17 @@ struct StepBuilder {
                             rem /= J.nc;
                         }
                         double srcs = 0.0;
-                        for (int ri = 0; ri < nrows; ++ri) {
-                            int64_t base;
-                            int xa, xb;
-                            if (!trunc_row_range(J.d, TQ, cc, B, ri, &base, &xa, &xb)) continue;
+                        for (const TruncRow &r : rows) {
+                            int64_t base = 0;
+                            bool in = true;
+                            for (int c = 0; c < J.d - 1; ++c) {
+                                const int x = cc[c] + r.del[c];
+                                in = in && x >= 0 && x < J.nc;
+                                base = base * J.nc + x;
+                            }
+                            if (!in) continue;
+                            base *= J.nc;
+                            const int xa = std::max(x0 - r.wl, 0), xb = std::min(x0 + B - 1 + r.wl, J.nc - 1);
                             srcs += J.h_src_cell_off[base + xb + 1] - J.h_src_cell_off[base + xa] + 64.0;
                         }
                         for (int s0 = a; s0 < b; s0 += cap)
