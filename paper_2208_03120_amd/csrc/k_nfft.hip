@@ -902,8 +902,13 @@ __global__ __launch_bounds__(64 * kInterpWaves, 6) void interp3_kernel(const Pro
 // job (one per job and four points, a sixteenth in 1-D), but a chunk's rows are staged once for
 // 16 jobs (64 in 1-D) and there is one operand product for 16 jobs' MFMA, where the kernels
 // above read 128 bytes of rows per point and job from L2: 4000 jobs of 4000 points in 2-D, 184 us
-// to spread and 194 us to interpolate, take 93 and 120 us (the values read and the patches
+// to spread and 194 us to interpolate, take 99 and 128 us (the values read and the patches
 // written are 78 us of the spreading at the card's copy rate, the MFMAs 52 us of each).
+//
+// A result is one long FP32 sum here, where the kernels above split it over wavefronts and
+// dimensions; it is kept as exact by several chains and an order from small terms to large
+// (scalings of a circle of 1500 points after three sweeps: 5.4e-8 with one chain for a quarter of a
+// row's cells and rows in order, 3.7e-8 as below, 3.8e-8 job by job).
 //
 // gids: job indices, kGroupJobs1 (1-D) or kGroupJobs2 per group, -1 for absent ones.  An item
 // (first group, groups, chunk) takes several groups one after another: the next group's
@@ -960,9 +965,9 @@ __global__ __launch_bounds__(256, 4) void spread_group_kernel(const ProdJob *__r
 #pragma unroll
             for (int q = 0; q < S::PV; ++q) buf[(vp + q) * S::kPitch + tid % S::J] = (float)ldexp(v[q] * w[q], -ex);
         };
-        f32x4 acc[NA];
+        f32x4 acc[2][NA];  // two chains for every other four points
 #pragma unroll
-        for (int u = 0; u < NA; ++u) acc[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int u = 0; u < 2 * NA; ++u) acc[u / NA][u % NA] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         St stg;
         job_of(0);
         vsrc = vnext;
@@ -1014,7 +1019,7 @@ __global__ __launch_bounds__(256, 4) void spread_group_kernel(const ProdJob *__r
                     for (int q = 0; q < 4; ++q)
 #pragma unroll
                         for (int u = 0; u < NA; ++u)
-                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q][u], b[q], acc[u], 0, 0, 0);
+                            acc[q & 1][u] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[q][u], b[q], acc[q & 1][u], 0, 0, 0);
                 }
                 if (more) {
                     store_v(vals[buf ^ 1], e);
@@ -1028,10 +1033,10 @@ __global__ __launch_bounds__(256, 4) void spread_group_kernel(const ProdJob *__r
                         MOT_GLOBAL f32x4 *out = reinterpret_cast<MOT_GLOBAL f32x4 *>(gp(jobs[jo].patches)) +
                                                 (int64_t)c * (D == 2 ? 64 : 4);
 #pragma unroll
-                        for (int u = 0; u < NA; ++u) out[(D == 2 ? (4 * wave + u) * 4 : 0) + lk] = acc[u];
+                        for (int u = 0; u < NA; ++u) out[(D == 2 ? (4 * wave + u) * 4 : 0) + lk] = acc[0][u] + acc[1][u];
                     }
 #pragma unroll
-                    for (int u = 0; u < NA; ++u) acc[u] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                    for (int u = 0; u < 2 * NA; ++u) acc[u / NA][u % NA] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
                 }
                 __syncthreads();
             }
@@ -1128,22 +1133,30 @@ __global__ __launch_bounds__(256, 4) void interp_group_kernel(const ProdJob *__r
 #pragma unroll
                         for (int s = 0; s < 4; ++s) w1[s] = row[kPatch + 4 * s + lk];
                         const float *gc = cells + lk * kGPitch + li;
+                        // a chain for each quarter s of a row's cells, two for the inner ones, and rows from
+                        // the patch's edges inward, where the windows are largest: the chains round at
+                        // the size of the small terms until the last rows
+                        f32x4 w0[4], mid[2] = {f32x4{0.0f, 0.0f, 0.0f, 0.0f}, f32x4{0.0f, 0.0f, 0.0f, 0.0f}};
 #pragma unroll
-                        for (int a4 = 0; a4 < 4; ++a4) {
-                            const f32x4 w0 = reinterpret_cast<const f32x4 *>(row)[a4];
+                        for (int a4 = 0; a4 < 4; ++a4) w0[a4] = reinterpret_cast<const f32x4 *>(row)[a4];
 #pragma unroll
-                            for (int u = 0; u < 4; ++u)
+                        for (int j = 0; j < 16; ++j) {
+                            const int a = j & 1 ? 15 - j / 2 : j / 2;
 #pragma unroll
-                                for (int s = 0; s < 4; ++s)
-                                    acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(
-                                        w0[u] * w1[s], gc[((4 * a4 + u) * 16 + 4 * s) * kGPitch], acc[s], 0, 0, 0);
+                            for (int s = 0; s < 4; ++s) {
+                                f32x4 &c = (s == 1 || s == 2) && (j & 1) ? mid[s - 1] : acc[s];
+                                c = __builtin_amdgcn_mfma_f32_16x16x4f32(w0[a / 4][a % 4] * w1[s],
+                                                                         gc[(a * 16 + 4 * s) * kGPitch], c, 0, 0, 0);
+                            }
                         }
+                        acc[1] += mid[0];
+                        acc[2] += mid[1];
                     } else {
 #pragma unroll
                         for (int s = 0; s < 4; ++s)
                             acc[s] = __builtin_amdgcn_mfma_f32_16x16x4f32(row[4 * s + lk], gb[s], acc[s], 0, 0, 0);
                     }
-                    const f32x4 z = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+                    const f32x4 z = D == 2 ? (acc[0] + acc[3]) + (acc[1] + acc[2]) : (acc[0] + acc[1]) + (acc[2] + acc[3]);
                     // z[r]: point 16 q + 4 lk + r of the stage, the lane's job
                     if (out)
 #pragma unroll

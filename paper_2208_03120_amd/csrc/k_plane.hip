@@ -32,7 +32,11 @@ __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c)
 
 // Steps of four of a contraction over K entries: four steps at a time, whose operands are read
 // together before their MFMAs (a loop around an MFMA is not unrolled by the compiler), then
-// the rest.  f(first entry, steps as a constant).
+// the rest.  f(first entry, steps as a constant).  The real cosine sums over cells (xr and pr
+// below) hold the sum of all cells, whose error is common to every result of the product and
+// shifts the scalings of every sweep: step u of a round goes to the u-th of four chains of
+// theirs (standard deviation of a product's mean relative error over problems of 1000 to 2300
+// points: 4.6e-8 with one chain, 2.6e-8 here, 2.2e-8 by radix-2 lines).
 template <class F>
 __device__ __forceinline__ void k_steps(int K, F f)
 {
@@ -72,7 +76,7 @@ __device__ __forceinline__ void plane2(const ProdJob &J, const float2 *tw, float
         const int k = k0 + li;
         const float *a = ry + (m0 + li) * P.p1 + lk;
         int idx = k * (lk + lo1);
-        f32x4 xr = zero, xi = zero;
+        f32x4 xr4[4] = {zero, zero, zero, zero}, xi = zero;
         k_steps(L1, [&](int s, auto U) {
             float2 w[U];
             float v[U];
@@ -83,11 +87,12 @@ __device__ __forceinline__ void plane2(const ProdJob &J, const float2 *tw, float
             }
 #pragma unroll
             for (int u = 0; u < U; ++u) {
-                xr = mfma4(v[u], w[u].x, xr);
+                xr4[u] = mfma4(v[u], w[u].x, xr4[u]);
                 xi = mfma4(v[u], w[u].y, xi);
             }
             idx += 4 * k * U;
         });
+        const f32x4 xr = (xr4[0] + xr4[1]) + (xr4[2] + xr4[3]);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             float *x = xz + (m0 + 4 * lk + r) * P.px + k;
@@ -112,11 +117,7 @@ __device__ __forceinline__ void plane2(const ProdJob &J, const float2 *tw, float
         }
         const float *b = xz + lk * P.px + k;
         int idx = f * (lk + lo0);
-        // cos X and sin X, w = cos - i sin.  The real cosine sums hold the sum of all cells, whose
-        // error is common to every result of the product and shifts the scalings of every sweep:
-        // step u of a round goes to the u-th of four chains (standard deviation of a product's
-        // mean relative error over 50 problems: 5.0e-8 with one chain, 2.7e-8 here and by radix-2
-        // lines)
+        // cos X and sin X, w = cos - i sin
         f32x4 pr4[4] = {zero, zero, zero, zero}, pi = zero, qr = zero, qi = zero;
         k_steps(L0, [&](int s, auto U) {
             float2 w[U];
@@ -141,14 +142,13 @@ __device__ __forceinline__ void plane2(const ProdJob &J, const float2 *tw, float
         for (int r = 0; r < 4; ++r) {
             const int fr = f0 + 4 * lk + r;
             if (fr >= P.H4) continue;
-            // X(f) = P - i Q = (pr + qi, pi - qr), X(-f) = P + i Q = (pr - qi, pi + qr)
-            const float ar = (pr[r] + qi[r]) * dp[r], ai = (pi[r] - qr[r]) * dp[r];
-            const float br = (pr[r] - qi[r]) * dn[r], bi = (pi[r] + qr[r]) * dn[r];
+            // E and O of X(+-f) = P -+ i Q times dp, dn; t = 0 but at the band's edge and f = 0
+            const float s = dp[r] + dn[r], t = dp[r] - dn[r];
             float *y = ry + fr * P.py + k;
-            y[0] = ar + br;
-            y[yst] = ai + bi;
-            y[2 * yst] = ar - br;
-            y[3 * yst] = ai - bi;
+            y[0] = fmaf(qi[r], t, pr[r] * s);
+            y[yst] = fmaf(-qr[r], t, pi[r] * s);
+            y[2 * yst] = fmaf(pr[r], t, qi[r] * s);
+            y[3 * yst] = fmaf(pi[r], t, -qr[r] * s);
         }
     }
     __syncthreads();

@@ -244,7 +244,7 @@ constexpr int kXcds = 8;
 // job: from kPlaneMfmas MFMAs on the fold and three passes, which spread a job over the chip,
 // are faster for a tree's few jobs (70 x 70 box, M = 32, 2200 MFMAs: 20 us against 15 us for
 // the three passes; 30 x 30, M = 16, 300: 7 us against 14 us); a circle's rows fill the chip
-// whatever their size (4000 rows of 43 x 43: fold and passes 200 us, 105 us in one launch).
+// whatever their size (4000 rows of 43 x 43: fold and passes 200 us, 112 us in one launch).
 constexpr int64_t kPlaneMfmas = 1300;
 constexpr int kPlaneRows = 64;
 constexpr int kPlaneRounds = 4;
