@@ -15,7 +15,8 @@
 // the 16-bit operand (scale_rows16_kernel); C = A' B^T is then a 16-bit GEMM with FP32
 // accumulation and output on the MFMA units (v_mfma_f32_32x32x16_bf16 / _f16):
 // gemm_big_kernel / gemm_big_split_kernel for products whose dimensions are multiples of
-// 256 with enough 256 x 256 tiles to fill the chip, gemm_kernel (64 x 64 tiles) otherwise.
+// 256 with enough 256 x 256 tiles to fill the chip, gemm_kernel (64 x 64 tiles) otherwise, and
+// gemm_tiny_kernel (32 x 32 tiles) for products of few of those.
 // Precision modes: BF16, FP16 and split BF16 (A' = Ah + Al, B = Bh + Bl,
 // C = Ah Bh + Ah Bl + Al Bh).  The
 // FP32 matrices carry a power-of-two scale per row: before each product the rows of
@@ -907,7 +908,7 @@ static int dense_pad(int64_t n) { return n >= 2048 ? pad_to(n, 256) : pad_to(n, 
 
 // A dense product's GEMM runs on gemm_big_kernel / gemm_big_split_kernel when M, N and K
 // are multiples of 256, 256 and 128 and the product has at least kBigMinTiles tiles of
-// 256 x 256, else on the 64 x 64 tiles of gemm_kernel.  Below about 96 tiles the large
+// 256 x 256, else on the kernels of small tiles (kSplitK2Tiles).  Below about 96 tiles the large
 // kernel leaves most compute units idle: at 81 tiles (2304 rows) split BF16 ran 857 sweeps/s
 // on it and 1095 on the small tiles; at 121 tiles (2816 rows) 692 against 617.
 constexpr int kBigMinTiles = 96;

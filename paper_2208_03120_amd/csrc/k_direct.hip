@@ -82,7 +82,7 @@ __device__ __forceinline__ void direct_range(const ProdJob &J, int range, int qu
 // 2^y for y = d2 c, c = -log2(e) / eta given as c_hi + c_lo, d2 >= 0.  n = rint(y) and the
 // remainder f = d2 c - n by two FMAs, which keeps the low part of c, so f is exact to one
 // rounding; 2^f on [-1/2, 1/2] is its Chebyshev interpolant of degree 11 (relative error
-// 4e-18, below the FP64 rounding).  dmax = 1100 / |c| bounds y: terms below 2^-1100 are zero.
+// 2e-17 with its coefficients rounded, below the FP64 rounding).  dmax = 1100 / |c| bounds y: terms below 2^-1100 are zero.
 struct ExpScale {
     double c_hi, c_lo, dmax;
 };

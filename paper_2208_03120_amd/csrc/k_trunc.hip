@@ -26,10 +26,11 @@
 // rounding, and the smallest, log2(eps) (about -41 at the default target), leave 2^-85 of
 // FP32's range to the values.  (A shift common to a run, half the largest c |x|^2 of its cells,
 // rounds every exponent at the shift's size and takes as much off that range: sparse clouds have
-// shifts up to 98.  It saves registers, 0.5 to 2 % of a launch in 3-D and nothing in 2-D.)  Values are scaled by 2^-e (e = exponent of max v);
-// a lane sums 16 of a stage's 64 sources in FP32 and adds that to its FP64 accumulator.  A
-// pair costs the vector unit a conversion, v_exp_f32 and an FMA, and targets come in tiles of
-// 16 where one per lane left half of the lanes idle in sparse cells.  Star trees in 3-D, time
+// shifts up to 98.  It saves registers, 0.5 to 2 % of a launch in 3-D and nothing in 2-D.)
+// Values are scaled by 2^-e (e = exponent of max v); a lane sums 16 of a stage's 64 sources in
+// FP32 and adds that to its FP64 accumulator.  A pair costs the vector unit a conversion,
+// v_exp_f32 and an FMA, and targets come in tiles of 16 where one per lane left half of the
+// lanes idle in sparse cells.  Star trees in 3-D, time
 // per launch against FP32 coordinate differences with a target per lane: nine jobs of 1e5
 // points, eta = 1e-3 5.1 -> 5.0 ms, eta = 3e-4 2.0 -> 1.8 ms; three jobs of 20000 points 0.45 -> 0.27
 // ms, of 5000 points at eta = 3e-4 0.12 -> 0.06 ms.  Bound by vector issue (about 160 cycles per

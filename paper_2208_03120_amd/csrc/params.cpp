@@ -394,6 +394,12 @@ static double product_cost(int d, int64_t n_max, int n, int m, double box)
     return 2.0 * (double)n_max * std::pow(2.0 * m, d) + 10.0 * box * std::log2((double)n) * d;
 }
 
+// Points of a spreading or interpolation item: a stage of 64 for every kChunkLoad points of a launch,
+// 8 in 3-D and 32 below at most.  Few points in large chunks leave the chip to a few dozen long
+// items (512 points in 3-D and 2048 below for all sizes: seven 3-D marginals of 6000 points 10.1 ms
+// for twenty sweeps, 7.5 here; 2-D star of 50000 points 5.4 and 3.8); smaller chunks than this lose
+// to an item's own chain of lookups and to the patches (12 3-D marginals of 50000 points 3.67 ms
+// with 6000, 3.59 here, 3.99 with 25000; 2-D barycenter 6.1, 6.3 and 6.9).
 constexpr int64_t kChunkLoad = 12500;
 
 int resolve_params(int d, double eta, const Extent &ext, const mot_fastsum_params *fs,

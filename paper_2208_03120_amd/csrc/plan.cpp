@@ -867,9 +867,9 @@ int tree_steps(const std::vector<TreeRef> &refs, const std::vector<ProdJob> &pj,
 {
     int maxD = 0;
     for (auto &r : refs) maxD = std::max(maxD, r.P->depth_max);
-    // Lanes of a batched sweep: plans do not depend on each other, so kLanes lanes of them,
-    // balanced by their points, run on their own streams between the fork and the
-    // finalisation, at most, and one lane's latency-bound passes overlap another's spreading and
+    // Lanes of a batched sweep: plans do not depend on each other, so up to kLanes lanes of
+    // them, balanced by their points, run on their own streams between the fork and the
+    // finalisation, and one lane's latency-bound passes overlap another's spreading and
     // interpolation.  (Splitting one plan's root subtrees the same way measured slower: the
     // lanes' launches hold a fraction of the jobs each.)  Plan r is in lane lane[r].
     int nl = (int)std::min<size_t>(refs.size(), std::max(1, std::min(max_lanes, kLanes)));
