@@ -893,9 +893,9 @@ __global__ __launch_bounds__(64 * kInterpWaves, 6) void interp3_kernel(const Pro
 }
 
 // ---------------------------------------------------------------------------------------
-// 1-D and 2-D jobs in groups that share their points (the rows of a circle's matrix, the
-// products of a node of many children): spreading and interpolation as matrix products with
-// the window matrix, whose entries are formed once for 16 jobs.
+// 1-D and 2-D jobs in groups that share their points (the rows of a circle's matrix): spreading
+// and interpolation as matrix products with the window matrix, whose entries are formed once
+// for 16 jobs.
 //   spreading      G[cell][job] = sum_p W[cell][p] v_p[job]      (K = points)
 //   interpolation  beta[p][job] = sum_cell W[cell][p] G[cell][job]  (K = cells)
 // with W[(a, c')][p] = w_0,p[a] w_1,p[c'] in 2-D and w_0,p[c'] in 1-D.  As many MFMAs as job by

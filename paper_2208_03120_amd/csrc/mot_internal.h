@@ -299,7 +299,12 @@ hipError_t launch_spread3(int group, const ProdJob *jobs, const int4 *items, int
 // groups of kGroupJobs1 / kGroupJobs2: gids the groups' job indices (-1: absent, never the
 // first), items int4 (first group, groups, chunk, 0).
 constexpr int kGroupJobs1 = 64, kGroupJobs2 = 16;
-constexpr int kGroupMin = 16;  // jobs sharing their points from which they are grouped
+// Jobs sharing their points from which they are grouped.  Groups of fewer jobs are too few items to
+// fill the chip, each a long one.  Sweeps of three-marginal circles with as many rows, job by
+// job and grouped: 2-D, 3000 points 63 rows 89 and 128 us, 400 rows 174 and 184, 500 rows 192 and
+// 187, 650 rows 219 and 203; 1-D, 3000 points 100 rows 72 and 114 us, 1000 rows 161 and 162, 1500 rows
+// 223 and 197, 1000 points 1000 rows 94 and 101, 1500 rows 145 and 121.
+constexpr int kGroupMin1 = 1280, kGroupMin2 = 512;
 hipError_t launch_spread_group(int d, const ProdJob *jobs, const int32_t *gids, const int4 *items, int n_items,
                                hipStream_t s);
 hipError_t launch_interp_group(int d, const ProdJob *jobs, const int32_t *gids, const int4 *items, int n_items,

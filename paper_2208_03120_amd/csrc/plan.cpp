@@ -548,7 +548,7 @@ struct StepBuilder {
             for (size_t i = 0; i < ord.size(); ++i) out[i] = v[ord[i]];
             v.swap(out);
         };
-        // 1-D and 2-D: sets of at least kGroupMin jobs go in groups that share a chunk's window
+        // 1-D and 2-D: sets of at least kGroupMin1 or kGroupMin2 jobs go in groups that share a chunk's window
         // rows and operand products; a partly filled group costs as much as a full one
         std::vector<int32_t> sgids[3], igids[3];
         std::vector<std::pair<int64_t, int4>> sgroup[3], igroup[3];  // with the item's work
@@ -559,7 +559,7 @@ struct StepBuilder {
                 const ProdJob &J = host_jobs[js[0]];
                 const int nch = source ? J.src_nchunks : J.tgt_nchunks;
                 const int32_t *start = source ? J.h_src_chunk_start : J.h_tgt_chunk_start;
-                if ((int)js.size() < kGroupMin) {
+                if ((int)js.size() < (J.d == 1 ? kGroupMin1 : kGroupMin2)) {
                     for (int j : js)
                         for (int c = 0; c < nch; ++c) {
                             solo[J.d].push_back(make_int2(j, c));

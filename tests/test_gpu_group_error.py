@@ -49,3 +49,19 @@ def test_circle_2d(seed):
     plan.close()
     want = exact_circle(inst.points, inst.weights, inst.eta, 3)
     assert np.linalg.norm(got - want) < 3.8e-8 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("d,rows", [(2, 511), (2, 512), (2, 545), (1, 1279), (1, 1280), (1, 1345)])
+def test_rows_around_the_grouping(d, rows):
+    """Circles of as many rows as are still spread and interpolated job by job, the fewest that are
+    grouped, and a number that leaves a last group of one; marginals down to one point."""
+    import oracle
+    from paper_2208_03120_amd import mot
+    inst = W.make_instance(np.random.Generator(np.random.PCG64(rows)), 4, [rows, 130, 17, 1], d, W.CIRCLE, 0.1)
+    plan = mot.Plan(inst.points, inst.weights, W.CIRCLE, None, inst.eta, path=mot.NFFT)
+    plan.sinkhorn(2)
+    got = plan.scalings()
+    plan.close()
+    want = oracle.circle_sinkhorn(inst.points, inst.weights, inst.eta, 2)[0]
+    for a, b in zip(got, want):
+        np.testing.assert_allclose(a, b, rtol=1e-5)
