@@ -36,20 +36,20 @@ PEAK_FP32_TFLOPS = 157.3  # dense FP32 MFMA
 # for fold and the FFT passes also of plan.cpp, whose launch item order sets their traffic).
 COPY_MIB = 256
 TRAFFIC = {
-    "spread": {"bytes_per_launch": 231948942, "source": "k_nfft.hip",
-             "sha256": "2a2795ee313b9c72a3657c3c38614d1a18e2fef0f9cee724bd0500b273160b9e"},
-    "spread_g3": {"bytes_per_launch": 110945099, "source": "k_nfft.hip",
-                "sha256": "2a2795ee313b9c72a3657c3c38614d1a18e2fef0f9cee724bd0500b273160b9e"},
-    "interp": {"bytes_per_launch": 201324982, "source": "k_nfft.hip",
-             "sha256": "2a2795ee313b9c72a3657c3c38614d1a18e2fef0f9cee724bd0500b273160b9e"},
-    "fold": {"bytes_per_launch": 61190708, "source": "k_nfft.hip+nfft_device.h+plan.cpp",
-           "sha256": "a865a9e38fb371aa767931a60191f218b0aa0d520db62b92a23e4e48f8794892"},
+    "spread": {"bytes_per_launch": 231942389, "source": "k_nfft.hip",
+             "sha256": "17eef7bd667c0c0f7ecd01bc4d7c49af4d1eb0cd26357e3ab824a6d2927ce40b"},
+    "spread_g3": {"bytes_per_launch": 110945509, "source": "k_nfft.hip",
+                "sha256": "17eef7bd667c0c0f7ecd01bc4d7c49af4d1eb0cd26357e3ab824a6d2927ce40b"},
+    "interp": {"bytes_per_launch": 201620983, "source": "k_nfft.hip",
+             "sha256": "17eef7bd667c0c0f7ecd01bc4d7c49af4d1eb0cd26357e3ab824a6d2927ce40b"},
+    "fold": {"bytes_per_launch": 61179650, "source": "k_nfft.hip+nfft_device.h+plan.cpp",
+           "sha256": "7c77194299bec5fb2e8d79474ca57459699211ba5a5093eb88968288fab497e9"},
     "fft6": {"bytes_per_launch": 10820451, "source": "k_fft.hip+plan.cpp",
-           "sha256": "579e3fd5b8c5d12a3606813f3e26f23d9b3d04b1909cf4f57273acfc7ac754d2"},
-    "fft5": {"bytes_per_launch": 26585388, "source": "k_fft.hip+plan.cpp",
-           "sha256": "579e3fd5b8c5d12a3606813f3e26f23d9b3d04b1909cf4f57273acfc7ac754d2"},
+           "sha256": "f054b15bde99422e3e3e1f0797dda550ffd5d5d1092cfb98a005e30c6c4c4e56"},
+    "fft5": {"bytes_per_launch": 26585797, "source": "k_fft.hip+plan.cpp",
+           "sha256": "f054b15bde99422e3e3e1f0797dda550ffd5d5d1092cfb98a005e30c6c4c4e56"},
     "fft7": {"bytes_per_launch": 10818874, "source": "k_fft.hip+plan.cpp",
-           "sha256": "579e3fd5b8c5d12a3606813f3e26f23d9b3d04b1909cf4f57273acfc7ac754d2"}
+           "sha256": "f054b15bde99422e3e3e1f0797dda550ffd5d5d1092cfb98a005e30c6c4c4e56"}
 }
 
 

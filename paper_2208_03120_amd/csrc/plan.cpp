@@ -548,8 +548,9 @@ struct StepBuilder {
             for (size_t i = 0; i < ord.size(); ++i) out[i] = v[ord[i]];
             v.swap(out);
         };
-        // 1-D and 2-D: sets of at least kGroupMin1 or kGroupMin2 jobs go in groups that share a chunk's window
-        // rows and operand products; a partly filled group costs as much as a full one
+        // 1-D and 2-D: sets of at least kGroupMin1 or kGroupMin2 jobs go in groups that share a
+        // chunk's window rows and operand products; a partly filled group costs as much as a full
+        // one
         std::vector<int32_t> sgids[3], igids[3];
         std::vector<std::pair<int64_t, int4>> sgroup[3], igroup[3];  // with the item's work
         auto place = [&](const std::vector<std::vector<int>> &sets, bool source, std::map<int, std::vector<int2>> &solo,
