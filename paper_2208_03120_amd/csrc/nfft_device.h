@@ -2,6 +2,8 @@
 // transforms.
 #pragma once
 
+#include <type_traits>
+
 #include "mot_internal.h"
 
 namespace mot {
@@ -18,8 +20,12 @@ __device__ __forceinline__ int div_small(int a, float rT) { return (int)(((float
 // of one leading tile) are looked up together, and the r-th chunks of all pairs are loaded
 // together and then added, so a round of loads waits once.  Absent tiles and chunks read entry
 // 0 and add zero: predicated loads cost a branch each, which bound small folds (30 x 30 cells
-// in 2-D: 8.8 us per launch with branches).  In 3-D every second leading tile goes to a sum of its
-// own, so that the two threads of a cell (part = 0 and 1 of PARTS = 2) give the same bits as one.
+// in 2-D: 8.8 us per launch with branches).  3-D launches that fill the chip (PARTS = 1) are bound
+// by the loads themselves, a third of them of absent tiles when tiles have 5 cells, and predicate
+// them, with the lookups where the table is in global memory: nine jobs on a 46^3 box 29.3 us
+// without and 26.1 with, nine on a 111^3 box, whose table does not fit in LDS, 519 and 389.  In 3-D
+// every second leading tile goes to a sum of its own, so that the two threads of a cell (part = 0 and
+// 1 of PARTS = 2) give the same bits as one.
 template <int D, int COV, int PARTS, class Tab>
 __device__ __forceinline__ float fold_cover(const ProdJob &J, const int (&gu)[2], int g, Tab tch, int part)
 {
@@ -29,6 +35,8 @@ __device__ __forceinline__ float fold_cover(const ProdJob &J, const int (&gu)[2]
     // of nine jobs on a 46^3 box: 4.92 ms with one, 5.02 with two)
     constexpr int NR = D == 1 ? 4 : (PARTS == 2 ? 2 : 1);
     constexpr int lead = D == 3 ? 1 : 0;  // index of the u dimension among the leading ones
+    constexpr bool kPickPatch = D == 3 && PARTS == 1;                        // predicated loads
+    constexpr bool kPickTab = std::is_same<Tab, const MOT_GLOBAL int32_t *>::value;  // and lookups
     const int T = J.T, ntl = J.ntile[D - 1];
     const float rT = 1.0f / (float)T;
     const MOT_GLOBAL float *pat = gp(J.patches);
@@ -55,7 +63,11 @@ __device__ __forceinline__ float fold_cover(const ProdJob &J, const int (&gu)[2]
             for (int k = 0; k < COV; ++k) {
                 const bool ok = ua + u <= ub && ka + k <= kb;
                 const int tl = ok ? tl0 + u * ntl + k : 0;
-                const int c0 = tch[tl], c1 = tch[tl + 1];
+                int c0 = 0, c1 = 0;
+                if (!kPickTab || ok) {
+                    c0 = tch[tl];
+                    c1 = tch[tl + 1];
+                }
                 nc[u][k] = ok ? c1 - c0 : 0;
                 at[u][k] = (uint32_t)c0 * pe + (uint32_t)(loc0 - u * T * W - k * T);
                 most = max(most, nc[u][k]);
@@ -68,7 +80,9 @@ __device__ __forceinline__ float fold_cover(const ProdJob &J, const int (&gu)[2]
                 for (int u = 0; u < NU; ++u)
 #pragma unroll
                     for (int k = 0; k < COV; ++k) {
-                        val[r][u][k] = pat[(uint64_t)(nc[u][k] > r0 + r ? at[u][k] : 0u)];
+                        const bool there = nc[u][k] > r0 + r;
+                        val[r][u][k] = 0.0f;
+                        if (!kPickPatch || there) val[r][u][k] = pat[(uint64_t)(there ? at[u][k] : 0u)];
                         at[u][k] += pe;
                     }
 #pragma unroll
