@@ -7,6 +7,7 @@
 #include <cstring>
 #include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "mot_internal.h"
@@ -256,6 +257,9 @@ struct mot_plan_s {
     double *stage = nullptr;
     int64_t apply_cap = 0;
     float *apply_patches = nullptr;
+    // launches of the one-product call by (target, source): the arena only grows, so the items of a
+    // pair are placed once, not on each call
+    std::map<std::pair<int, int>, std::vector<mot::Step>> apply_steps;
     int apply_patch_cap = 0;
 };
 

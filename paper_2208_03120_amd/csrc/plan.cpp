@@ -2026,13 +2026,17 @@ int mot_apply_kernel(mot_plan P, int32_t t, int32_t s, const double *v, double *
     J.spec1 = slotjob.spec1;
     ProdJob *jd = P->jobs_dev + 2 * P->K;
     MOT_HIP(hipMemcpyAsync(jd, &J, sizeof(ProdJob), hipMemcpyHostToDevice, P->stream));
-    std::vector<Step> steps;
-    StepBuilder B{&P->arena, &steps};
-    std::vector<ProdJob> hj(2 * P->K + 1);
-    hj[2 * P->K] = J;
-    B.products(P->jobs_dev, hj, {2 * P->K});
-    MOT_TRY(B.finish());
-    MOT_TRY(run_steps(steps, P->stream));
+    auto known = P->apply_steps.find({t, s});
+    if (known == P->apply_steps.end()) {
+        std::vector<Step> steps;
+        StepBuilder B{&P->arena, &steps};
+        std::vector<ProdJob> hj(2 * P->K + 1);
+        hj[2 * P->K] = J;
+        B.products(P->jobs_dev, hj, {2 * P->K});
+        MOT_TRY(B.finish());
+        known = P->apply_steps.emplace(std::make_pair((int)t, (int)s), std::move(steps)).first;
+    }
+    MOT_TRY(run_steps(known->second, P->stream));
     MOT_HIP(launch_scatter_vec(P->apply_out, P->marg[t].perm, P->n[t], tmp + P->n[s], P->stream));
     MOT_HIP(hipMemcpyAsync(out, tmp + P->n[s], P->n[t] * sizeof(double),
                            ptr_kind == MOT_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost,
