@@ -590,6 +590,30 @@ double trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s,
     return best;
 }
 
+// The cost that the cells of an FP64 plan are chosen by.  It prices near pairs below their FP64 rate
+// (40 cycles while a run's scaled half-diagonal is at most 3, 66 beyond, up to four targets a
+// lane), which favours cells of several points: with trunc_cost_fp64 clouds wider in one
+// dimension than in the others got coarse cells (2-D, 9751 points, eta = 9e-4: 3 cells across
+// in place of 30, a sweep 2863 us in place of 1898; 4516 points, 6e-3: 1348 and 693) and cubes
+// finer ones, which leave out more of the sources beyond r_c.
+static double trunc_cells_cost_fp64(int d, double eta, const TruncParams &T, double lam)
+{
+    const double half = std::sqrt(1.4426950408889634 / eta) * T.h;
+    double best = -1.0;
+    for (int b : {1, 2, 3, 4, 6, 8, 12, 16}) {
+        if (b > T.nc) break;
+        double rows, src, runs;
+        trunc_run_sources(d, T, lam, b, &rows, &src, &runs);
+        const double pair = half * std::sqrt(0.25 * b * b + 0.25 * (d - 1)) > 3.0 ? 66.0 : 40.0;
+        for (int r : {1, 2, 4}) {
+            const double c = runs * expected_chunks(lam * b, 64 * r) *
+                             (rows * 100.0 + (src / 64.0 + rows) * 200.0 + src * r * pair);
+            if (best < 0 || c < best) best = c;
+        }
+    }
+    return best;
+}
+
 int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params *fs, double n_mean,
                   int precision, TruncParams *out)
 {
@@ -625,7 +649,8 @@ int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params
             Vb *= wc;
         }
         const double lam = std::max(n_mean, 1.0) * std::pow(C.h, d) / Vb;  // points per full cell
-        const double cost = trunc_choose_run(d, C, lam, lam, precision, &C.B, &C.R);
+        const double run = trunc_choose_run(d, C, lam, lam, precision, &C.B, &C.R);
+        const double cost = precision == MOT_PREC_FP64 ? trunc_cells_cost_fp64(d, eta, C, lam) : run;
         if (best < 0 || cost < best) {
             best = cost;
             *out = C;
