@@ -36,6 +36,13 @@
 // ms, of 5000 points at eta = 3e-4 0.12 -> 0.06 ms.  Bound by vector issue (about 160 cycles per
 // 16 x 16 pairs with the staging, 131 without); a bound of three or five blocks per CU measured
 // 2 % slower.
+// In 1-D and 2-D the contraction has one or two empty terms of four, and exponents of FP32
+// coordinate differences, scaled by sqrt(c) and relative to the run's centre, take fewer cycles than
+// the MFMA and the conversion; they are used for runs within a half-diagonal of 3, where rounding
+// the coordinates moves a term that counts by about 1e-7.  Sweeps of star trees, differences and
+// MFMA: 2-D, six marginals of 60000 points, eta = 3e-4 0.96 and 1.21 ms, 1e-3 2.23 and 2.88, 3e-3
+// 4.5 and 5.8; 1-D, four of 60000, 1e-4 0.81 and 1.24 ms.  (In 3-D, three differences: 44 cycles a
+// wavefront and source of 64 targets against 40 with the MFMA, which fills its tiles better.)
 // FP64: plain exp(-|x - y|^2 / eta) with FP64 sums in source order.
 #include <type_traits>
 
@@ -111,12 +118,13 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 constexpr int kSrcPitch = 64 + 8;  // staged component rows, in doubles (LDS banks)
 
-template <int D>
+// DIFF: exponents of FP32 coordinate differences (D < 3).
+template <int D, bool DIFF>
 __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const ProdJob *__restrict__ jobs,
                                                                           const int4 *__restrict__ items,
                                                                           int n_items)
 {
-    __shared__ double sw_all[kTruncWaves][4 * kSrcPitch];         // 2c y, -c |y|^2
+    __shared__ __align__(16) double sw_all[kTruncWaves][4 * kSrcPitch];  // 2c y, -c |y|^2
     __shared__ __align__(16) float sv_all[kTruncWaves][64];
     __shared__ int32_t ra_all[kTruncWaves][kMaxTruncRows];      // first sorted source of each row
     __shared__ int32_t rp_all[kTruncWaves][kMaxTruncRows + 1];  // sources before each row
@@ -162,6 +170,8 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
         wave_sync();
         // targets: 16-wide tile t, lane l has component l / 16 of target l % 16, and its -c |x|^2
         double xt[4], ax[4], acc[4];
+        float xf[4][2];  // DIFF: every component of target l % 16
+        const double sc = sqrt(c2);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             const bool act = 16 * t + li < cnt;
@@ -172,6 +182,7 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
             for (int c = 0; c < D; ++c) {
                 const double dx = act ? tgt[i * D + c] - ctr[c] : 0.0;
                 if (lk == c) xt[t] = dx;
+                if (DIFF && c < 2) xf[t][c] = (float)(dx * sc);
                 nrm += dx * dx;
             }
             ax[t] = -c2 * nrm;
@@ -192,12 +203,17 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
             }
         };
         // position of a source's value: the FP64 tile's register r of lane group g is source g + 4 r
-        const int vpos = (lane & 48) | ((lane & 3) << 2) | ((lane >> 2) & 3);
+        const int vpos = DIFF ? lane : (lane & 48) | ((lane & 3) << 2) | ((lane >> 2) & 3);
+        float *sf = reinterpret_cast<float *>(sw);  // DIFF: components of the stage's sources, 64 each
         auto scan = [&](auto NT) {
             for (int s0 = 0; s0 < total; s0 += 64) {
                 const int steps = (min(64, total - s0) + 15) >> 4;
                 wave_sync();
-                {
+                if constexpr (DIFF) {
+#pragma unroll
+                    for (int c = 0; c < D; ++c) sf[64 * c + lane] = (float)((ly[c] - ctr[c]) * sc);
+                    sv[vpos] = (float)ldexp(lv, -e);
+                } else {
                     // entries past the list's end have the value 0 and the place of the run's centre
                     // or of a source of before, whose exponents are finite
                     double nrm = 0.0;
@@ -215,7 +231,25 @@ __global__ __launch_bounds__(64 * kTruncWaves, 4) void trunc_mixed_kernel(const 
                 float part[NT];
 #pragma unroll
                 for (int t = 0; t < NT; ++t) part[t] = 0.0f;
-                for (int m = 0; m < steps; ++m) {
+                for (int m = 0; DIFF && m < steps; ++m) {
+                    const f32x4 w = reinterpret_cast<const f32x4 *>(sv)[4 * m + lk];
+                    f32x4 y[2];
+#pragma unroll
+                    for (int c = 0; c < D && c < 2; ++c) y[c] = reinterpret_cast<const f32x4 *>(sf + 64 * c)[4 * m + lk];
+#pragma unroll
+                    for (int t = 0; t < NT; ++t)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const float dx = xf[t][0] - y[0][r];
+                            float q = dx * dx;
+                            if (D > 1) {
+                                const float dy = xf[t][1] - y[1][r];
+                                q = fmaf(dy, dy, q);
+                            }
+                            part[t] = fmaf(w[r], __builtin_amdgcn_exp2f(-q), part[t]);
+                        }
+                }
+                for (int m = 0; !DIFF && m < steps; ++m) {
                     const double a = sw[lk * kSrcPitch + 16 * m + li];
                     const f32x4 w = reinterpret_cast<const f32x4 *>(sv)[4 * m + lk];
                     f64x4 g[NT];
@@ -313,7 +347,7 @@ __global__ __launch_bounds__(64) void trunc_fp64_kernel(const ProdJob *__restric
 }
 
 template <int D>
-static void launch_trunc_d(int precision, int R, const ProdJob *jobs, const int4 *items, int n_items, hipStream_t s)
+static void launch_trunc_d(int precision, int diff, int R, const ProdJob *jobs, const int4 *items, int n_items, hipStream_t s)
 {
     if (precision == MOT_PREC_FP64) {
         const dim3 grid(n_items < (1 << 20) ? n_items : (1 << 20)), block(64);
@@ -322,18 +356,24 @@ static void launch_trunc_d(int precision, int R, const ProdJob *jobs, const int4
     } else {
         const int blocks = (n_items + kTruncWaves - 1) / kTruncWaves;
         const dim3 grid(blocks < (1 << 20) ? blocks : (1 << 20)), block(64 * kTruncWaves);
-        hipLaunchKernelGGL(trunc_mixed_kernel<D>, grid, block, 0, s, jobs, items, n_items);
+        if constexpr (D < 3) {
+            if (!diff) {
+                hipLaunchKernelGGL((trunc_mixed_kernel<D, true>), grid, block, 0, s, jobs, items, n_items);
+                return;
+            }
+        }
+        hipLaunchKernelGGL((trunc_mixed_kernel<D, false>), grid, block, 0, s, jobs, items, n_items);
     }
 }
 
-hipError_t launch_trunc(int d, int precision, int R, const ProdJob *jobs_dev, const int4 *items, int n_items,
+hipError_t launch_trunc(int d, int precision, int diff, int R, const ProdJob *jobs_dev, const int4 *items, int n_items,
                         hipStream_t s)
 {
     if (n_items == 0) return hipSuccess;
     if (R != 1 && (R != 2 || precision != MOT_PREC_FP64)) return hipErrorInvalidValue;
-    if (d == 1) launch_trunc_d<1>(precision, R, jobs_dev, items, n_items, s);
-    if (d == 2) launch_trunc_d<2>(precision, R, jobs_dev, items, n_items, s);
-    if (d == 3) launch_trunc_d<3>(precision, R, jobs_dev, items, n_items, s);
+    if (d == 1) launch_trunc_d<1>(precision, diff, R, jobs_dev, items, n_items, s);
+    if (d == 2) launch_trunc_d<2>(precision, diff, R, jobs_dev, items, n_items, s);
+    if (d == 3) launch_trunc_d<3>(precision, diff, R, jobs_dev, items, n_items, s);
     return hipGetLastError();
 }
 

@@ -126,7 +126,7 @@ __device__ __forceinline__ void wave_sync()
 // (sorted) point order.
 struct ProdJob {
     int32_t d, path, precision;
-    int32_t diff;      // mixed direct path: exponent formed in FP64
+    int32_t diff;      // mixed direct and truncated paths: exponent formed in FP64
     // vectors
     const double *v;   // source vector, n_s entries
     // NFFT path, null: none.  The source is v times this; jobs of one launch that spread from the
@@ -233,7 +233,8 @@ int direct_source_split(int64_t nt, int64_t ns, int precision);
 constexpr int kMaxTruncRows = 400;  // neighbour rows per truncated work item, (2w + 1)^(d-1)
 // Truncated products: items int4 (job, first cell of a run of B cells of one row, first
 // sorted target, count | B << 16), count <= 64 * R; R = 1 or 2 (mixed precision: 1).
-hipError_t launch_trunc(int d, int precision, int R, const ProdJob *jobs_dev, const int4 *items, int n_items,
+// diff: the jobs' (mixed precision).
+hipError_t launch_trunc(int d, int precision, int diff, int R, const ProdJob *jobs_dev, const int4 *items, int n_items,
                         hipStream_t s);
 // diff != 0: mixed-precision pairs with the exponent formed in FP64 (small eta)
 hipError_t launch_direct(int d, const ProdJob *jobs_dev, const int4 *items, int n_items, const int2 *red_items,

@@ -561,29 +561,40 @@ static double trunc_cost_fp64(int d, const TruncParams &T, double lam_t, double 
 }
 
 // The same for a mixed product: per row ~100 and per 64-source stage ~300 of an item of up to
-// 64 targets, and per source ~8.2 for each tile of 16 targets (131 per 16 x 16 pairs).
-static double trunc_cost_mixed(int d, const TruncParams &T, double lam_t, double lam_s, int B)
+// 64 targets, and per source and tile of 16 targets ~8.2 (131 per 16 x 16 pairs) or, with
+// exponents of FP32 differences, ~5.3 in 1-D and ~6.4 in 2-D.  Those are taken in 1-D and 2-D while
+// a run's scaled half-diagonal is at most kTruncNear, which keeps an exponent's rounding near 1e-7
+// where its term counts.
+constexpr double kTruncNear = 3.0, kTruncNearPair[3] = {0.0, 5.3, 6.4};
+static double trunc_cost_mixed(int d, const TruncParams &T, double lam_t, double lam_s, int B, double pair)
 {
     double rows, src, runs;
     trunc_run_sources(d, T, lam_s, B, &rows, &src, &runs);
     return runs * (expected_chunks(lam_t * B, 64) * (rows * 100.0 + (src / 64.0 + 1.0) * 300.0) +
-                   expected_chunks(lam_t * B, 16) * src * 8.2);
+                   expected_chunks(lam_t * B, 16) * src * pair);
 }
 
-double trunc_choose_run(int d, const TruncParams &T, double lam_t, double lam_s, int precision, int *B, int *R)
+double trunc_choose_run(int d, const TruncParams &T, double eta, double lam_t, double lam_s, int precision, int *B,
+                        int *R, int32_t *diff)
 {
+    const double half = std::sqrt(1.4426950408889634 / eta) * T.h;
     double best = -1.0;
     *B = 1;
     *R = 1;
+    *diff = 0;
     for (int b : {1, 2, 3, 4, 6, 8, 12, 16}) {
         if (b > T.nc) break;
         for (int r = 1; r <= (precision == MOT_PREC_FP64 ? 2 : 1); ++r) {
-            const double c = precision == MOT_PREC_FP64 ? trunc_cost_fp64(d, T, lam_t, lam_s, b, r)
-                                                        : trunc_cost_mixed(d, T, lam_t, lam_s, b);
+            const bool near = precision != MOT_PREC_FP64 && d < 3 &&
+                              half * std::sqrt(0.25 * b * b + 0.25 * (d - 1)) <= kTruncNear;
+            const double c = precision == MOT_PREC_FP64
+                                 ? trunc_cost_fp64(d, T, lam_t, lam_s, b, r)
+                                 : trunc_cost_mixed(d, T, lam_t, lam_s, b, near ? kTruncNearPair[d] : 8.2);
             if (best < 0 || c < best) {
                 best = c;
                 *B = b;
                 *R = r;
+                *diff = precision != MOT_PREC_FP64 && !near;
             }
         }
     }
@@ -649,7 +660,8 @@ int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params
             Vb *= wc;
         }
         const double lam = std::max(n_mean, 1.0) * std::pow(C.h, d) / Vb;  // points per full cell
-        const double run = trunc_choose_run(d, C, lam, lam, precision, &C.B, &C.R);
+        int32_t diff = 0;
+        const double run = trunc_choose_run(d, C, eta, lam, lam, precision, &C.B, &C.R, &diff);
         const double cost = precision == MOT_PREC_FP64 ? trunc_cells_cost_fp64(d, eta, C, lam) : run;
         if (best < 0 || cost < best) {
             best = cost;

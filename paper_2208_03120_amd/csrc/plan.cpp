@@ -221,7 +221,7 @@ int run_steps(const std::vector<Step> &steps, hipStream_t s0, const Lanes *lanes
             MOT_HIP(launch_fill_int(st.fill_ptr, st.fill_value, st.fill_count, s));
             break;
         case ST_TRUNC:
-            MOT_HIP(launch_trunc(st.d, st.precision, st.trunc_r, (const ProdJob *)st.jobs,
+            MOT_HIP(launch_trunc(st.d, st.precision, st.diff, st.trunc_r, (const ProdJob *)st.jobs,
                                  (const int4 *)st.items, st.n_items, s));
             break;
         }
@@ -384,7 +384,7 @@ struct StepBuilder {
     {
         std::map<std::tuple<int, int, int, bool>, std::vector<int4>> direct;  // (d, precision, diff, small)
         std::map<std::tuple<int, int, int, bool>, std::vector<int2>> direct_red;  // range sums
-        std::map<std::tuple<int, int, int>, std::vector<std::pair<double, int4>>> trunc;  // (d, prec, R)
+        std::map<std::tuple<int, int, int, int>, std::vector<std::pair<double, int4>>> trunc;  // (d, prec, R, diff)
         std::map<int, std::vector<int2>> spread, fold, interp;   // d
         // 3-D spreading: jobs by the points they spread from (a binned marginal's rows)
         std::map<const float *, std::vector<int>> spread3_src;
@@ -419,7 +419,7 @@ struct StepBuilder {
             if (J.path == MOT_TRUNC) {
                 // items of at most 64 R targets from a run of B consecutive cells of one
                 // row (contiguous in the sorted order), costed by the sources they scan
-                auto &v = trunc[std::make_tuple(J.d, J.precision, J.trunc_r)];
+                auto &v = trunc[std::make_tuple(J.d, J.precision, J.trunc_r, J.diff)];
                 const std::vector<TruncRow> rows = trunc_rows(J.d, J.tw, J.q2);
                 int64_t nrow_cells = 1;
                 for (int c = 0; c < J.d - 1; ++c) nrow_cells *= J.nc;
@@ -522,6 +522,7 @@ struct StepBuilder {
             st.d = std::get<0>(kv.first);
             st.precision = std::get<1>(kv.first);
             st.trunc_r = std::get<2>(kv.first);
+            st.diff = std::get<3>(kv.first);
             st.jobs = jobs_dev;
             st.items = upload(its);
             st.n_items = (int)its.size();
@@ -1191,7 +1192,7 @@ int mot::make_prod_job(mot_plan_s *P, int t, int s, const double *v, int32_t *sl
         double cells = 1.0;  // full cells covering the cloud's box
         for (int c = 0; c < P->d; ++c) cells *= T.box_cells[c];
         const double lam_t = (double)Q.nt / cells, lam_s = (double)Q.ns / cells;
-        (void)trunc_choose_run(P->d, T, lam_t, lam_s, P->precision, &Q.trunc_b, &Q.trunc_r);
+        (void)trunc_choose_run(P->d, T, Q.eta, lam_t, lam_s, P->precision, &Q.trunc_b, &Q.trunc_r, &Q.diff);
         return MOT_OK;
     }
     if (P->path != MOT_NFFT) return MOT_OK;
