@@ -126,11 +126,11 @@ struct TruncRow {
     int del[2], wl;
 };
 std::vector<TruncRow> trunc_rows(int d, int w, double q2);
-// Cheapest launch shape of a product and its modelled cost: cells per run B and targets per
+// Cheapest launch shape of a product: cells per run B and targets per
 // lane R (1 in mixed precision, 1 or 2 in FP64); lam_t / lam_s: targets / sources per grid cell;
 // diff: mixed precision, whether the exponents are formed in FP64.
-double trunc_choose_run(int d, const TruncParams &T, double eta, double lam_t, double lam_s, int precision, int *B,
-                        int *R, int32_t *diff);
+void trunc_choose_run(int d, const TruncParams &T, double eta, double lam_t, double lam_s, int precision, int *B,
+                      int *R, int32_t *diff);
 void kappa_B_shifted(double eta, double tau, double eps_B, int p, std::vector<double> &q);
 double kappa_R(double r, double eta, double tau, double eps_B, const std::vector<double> &q);
 void kappa_hat_even(int d, int M, double eta, double tau, double eps_B, int p,

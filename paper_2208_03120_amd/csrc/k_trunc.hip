@@ -32,7 +32,7 @@
 // v_exp_f32 and an FMA, and targets come in tiles of 16 where one per lane left half of the
 // lanes idle in sparse cells.  Star trees in 3-D, time
 // per launch against FP32 coordinate differences with a target per lane: nine jobs of 1e5
-// points, eta = 1e-3 5.1 -> 5.0 ms, eta = 3e-4 2.0 -> 1.8 ms; three jobs of 20000 points 0.45 -> 0.27
+// points, eta = 1e-3 5.1 -> 5.0 ms, eta = 3e-4 2.0 -> 1.85 ms; three jobs of 20000 points 0.45 -> 0.27
 // ms, of 5000 points at eta = 3e-4 0.12 -> 0.06 ms.  Bound by vector issue (about 160 cycles per
 // 16 x 16 pairs with the staging, 131 without); a bound of three or five blocks per CU measured
 // 2 % slower.

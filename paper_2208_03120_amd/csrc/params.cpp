@@ -496,7 +496,7 @@ int resolve_params(int d, double eta, const Extent &ext, const mot_fastsum_param
 // by at most eps sum_j v_j.  For a uniform cloud of bounding-box volume V, a target at a
 // corner of the box sums about (pi eta)^(d/2) / (2^d V) of the total source weight, so
 // eps = target (pi eta)^(d/2) / (2^d V) keeps the relative error of such products near
-// the target.  The cell side h = r_c / q is chosen by a cost model of the kernel: one
+// the target.  The cell side h = r_c / q is chosen by a cost model (trunc_cells_cost): one
 // wavefront per item of at most 64 R targets from a run of B consecutive cells of a row,
 // scanning the rows of cells whose box distance to the run is at most r_c.
 int64_t trunc_cells(int d, const TruncParams &T)
@@ -574,8 +574,8 @@ static double trunc_cost_mixed(int d, const TruncParams &T, double lam_t, double
                    expected_chunks(lam_t * B, 16) * src * pair);
 }
 
-double trunc_choose_run(int d, const TruncParams &T, double eta, double lam_t, double lam_s, int precision, int *B,
-                        int *R, int32_t *diff)
+void trunc_choose_run(int d, const TruncParams &T, double eta, double lam_t, double lam_s, int precision, int *B,
+                      int *R, int32_t *diff)
 {
     const double half = std::sqrt(1.4426950408889634 / eta) * T.h;
     double best = -1.0;
@@ -598,16 +598,17 @@ double trunc_choose_run(int d, const TruncParams &T, double eta, double lam_t, d
             }
         }
     }
-    return best;
 }
 
-// The cost that the cells of an FP64 plan are chosen by.  It prices near pairs below their FP64 rate
-// (40 cycles while a run's scaled half-diagonal is at most 3, 66 beyond, up to four targets a
-// lane), which favours cells of several points: with trunc_cost_fp64 clouds wider in one
-// dimension than in the others got coarse cells (2-D, 9751 points, eta = 9e-4: 3 cells across
-// in place of 30, a sweep 2863 us in place of 1898; 4516 points, 6e-3: 1348 and 693) and cubes
-// finer ones, which leave out more of the sources beyond r_c.
-static double trunc_cells_cost_fp64(int d, double eta, const TruncParams &T, double lam)
+// The cost that a plan's cells are chosen by, in both precisions: 40 cycles a pair while a run's
+// scaled half-diagonal is at most 3 and 66 beyond, up to four targets a lane.  The cells decide
+// which sources beyond r_c are summed all the same, so their rule does not follow the kernels'
+// speed: the costs above choose finer ones (3-D, 5000 points, eta = 3e-4: 9 cells across in place
+// of 5, a sweep 90 us in place of 117; 60000 points 652 and 787, 1e5 points 3.54 and 3.71 ms),
+// with which ragged trees had targets out of every source's reach.  In FP64 they are also the
+// slower ones in clouds wider in one dimension than in the others (2-D, 9751 points, eta = 9e-4:
+// 3 cells across in place of 30, 2863 us and 1898; 4516 points, 6e-3: 1348 and 693).
+static double trunc_cells_cost(int d, double eta, const TruncParams &T, double lam)
 {
     const double half = std::sqrt(1.4426950408889634 / eta) * T.h;
     double best = -1.0;
@@ -640,7 +641,7 @@ int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params
     T.est_err = target;
     for (int c = 0; c < 3; ++c) T.glo[c] = c < d ? ext.lo[c] : 0.0;
     const int nc_max = d == 1 ? (1 << 20) : (d == 2 ? 2048 : 128);
-    double best = -1.0;
+    double best = -1.0, lam_out = 0.0;
     for (double q : {0.5, 0.75, 1.0, 1.5, 2.0, 3.0, 4.0, 6.0, 8.0}) {
         TruncParams C = T;
         C.h = T.rc / q;
@@ -660,15 +661,16 @@ int resolve_trunc(int d, double eta, const Extent &ext, const mot_fastsum_params
             Vb *= wc;
         }
         const double lam = std::max(n_mean, 1.0) * std::pow(C.h, d) / Vb;  // points per full cell
-        int32_t diff = 0;
-        const double run = trunc_choose_run(d, C, eta, lam, lam, precision, &C.B, &C.R, &diff);
-        const double cost = precision == MOT_PREC_FP64 ? trunc_cells_cost_fp64(d, eta, C, lam) : run;
+        const double cost = trunc_cells_cost(d, eta, C, lam);
         if (best < 0 || cost < best) {
             best = cost;
             *out = C;
+            lam_out = lam;
         }
     }
     if (best < 0) return MOT_EDOMAIN;
+    int32_t diff = 0;
+    trunc_choose_run(d, *out, eta, lam_out, lam_out, precision, &out->B, &out->R, &diff);
     return MOT_OK;
 }
 

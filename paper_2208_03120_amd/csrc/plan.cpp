@@ -1192,7 +1192,7 @@ int mot::make_prod_job(mot_plan_s *P, int t, int s, const double *v, int32_t *sl
         double cells = 1.0;  // full cells covering the cloud's box
         for (int c = 0; c < P->d; ++c) cells *= T.box_cells[c];
         const double lam_t = (double)Q.nt / cells, lam_s = (double)Q.ns / cells;
-        (void)trunc_choose_run(P->d, T, Q.eta, lam_t, lam_s, P->precision, &Q.trunc_b, &Q.trunc_r, &Q.diff);
+        trunc_choose_run(P->d, T, Q.eta, lam_t, lam_s, P->precision, &Q.trunc_b, &Q.trunc_r, &Q.diff);
         return MOT_OK;
     }
     if (P->path != MOT_NFFT) return MOT_OK;
