@@ -400,6 +400,8 @@ static double product_cost(int d, int64_t n_max, int n, int m, double box)
 // for twenty sweeps, 7.5 here; 2-D star of 50000 points 5.4 and 3.8); smaller chunks than this lose
 // to an item's own chain of lookups and to the patches (12 3-D marginals of 50000 points 3.67 ms
 // with 6000, 3.59 here, 3.99 with 25000; 2-D barycenter 6.1, 6.3 and 6.9).
+// 2-D tiles of 1 or 3 cells keep the most: a cell of theirs is folded from 29 or 256 tiles, chunk
+// after chunk (four marginals of 30000 points, tiles of 3: 413 us a sweep with chunks of 192).
 constexpr int64_t kChunkLoad = 12500;
 
 int resolve_params(int d, double eta, const Extent &ext, const mot_fastsum_params *fs,
@@ -485,7 +487,9 @@ int resolve_params(int d, double eta, const Extent &ext, const mot_fastsum_param
             }
         }
     if (best_cost < 0) return MOT_EDOMAIN;
-    const int stages = (int)std::min<int64_t>((n_max * products + kChunkLoad - 1) / kChunkLoad, d == 3 ? 8 : 32);
+    const int most = d == 3 ? 8 : 32;
+    const bool narrow = d == 2 && best.T < 4;
+    const int stages = narrow ? most : (int)std::min<int64_t>((n_max * products + kChunkLoad - 1) / kChunkLoad, most);
     best.chunk = F.chunk > 0 ? F.chunk : 64 * std::max(1, stages);
     *out = best;
     return MOT_OK;

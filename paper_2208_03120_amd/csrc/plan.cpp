@@ -464,9 +464,15 @@ struct StepBuilder {
             const int cells = lines * J.L[J.d - 1];
             // a workgroup that folds its own job waits once per cell of a thread and round of
             // chunks; beyond kPlaneRounds such waits the fold's own launch is faster, unless
-            // the jobs fill the chip
+            // the jobs fill the chip.  With tiles of 1 or 3 cells (2-D) a wait is that of 29 or 256
+            // patches one by one, and a second cell of a thread is too many (four marginals of
+            // 3000 points, 31 x 31 cells folded by their workgroups and before: 200 and 243 us
+            // with tiles of 3, 426 and 584 of 1; 46 x 46: 224 and 195, 954 and 622; 300 rows of a
+            // circle, 31 x 31: 479 and 450)
             const int waits = (cells + 1023) / 1024 * (J.d == 1 ? (J.src_tile_most + 3) / 4 : J.src_tile_most);
-            const bool plane_fold = plane && (waits <= kPlaneRounds || ids.size() >= 512);
+            const bool narrow = J.d == 2 && J.T < 4;
+            const bool plane_fold = plane && (narrow ? cells <= 1024 && ids.size() < 256 && waits <= kPlaneRounds
+                                                     : waits <= kPlaneRounds || ids.size() >= 512);
             if (!plane_fold)
                 for (int f = 0; f < cells; f += kFoldCellsPerItem) fold[J.d].push_back(make_int2(j, f));
             if (J.d < 3) {

@@ -47,3 +47,19 @@ def test_circle_rows(mot, n0, n, M):
     for a, b in zip(P, oracle.circle_marginals(inst.points, inst.eta, [np.ones(x) for x in inst.sizes])):
         assert rel_to_max(a, b) < 1e-5
     plan.close()
+
+
+@pytest.mark.parametrize("n", [64, 128])  # boxes of about 900 and 2000 cells, folded by the transform and before it
+@pytest.mark.parametrize("m", [7, 8])     # tiles of 3 and 1 cells
+@pytest.mark.parametrize("chunk", [0, 8])
+def test_narrow_tiles(mot, n, m, chunk):
+    r = rng(n + m)
+    inst = W.make_instance(r, 3, [900, 411, 17], 2, W.TREE, 0.08, parent=W.star_parent(3))
+    fs = mot.fastsum_params(M=16, n=n, m=m, p=4, tau=1.0, eps_B=0.25, chunk=chunk)
+    plan = mot.Plan(inst.points, inst.weights, W.TREE, inst.parent, inst.eta, path=mot.NFFT, fastsum=fs)
+    assert chunk or plan.info()["chunk"] == 2048
+    for t, s in [(0, 1), (1, 0), (2, 0), (0, 2)]:
+        v = r.uniform(0.0, 1.0, inst.sizes[s])
+        want = oracle.kernel_apply(inst.points[t], inst.points[s], v, inst.eta)
+        assert rel_to_max(plan.apply(t, s, v), want) < TOL
+    plan.close()
