@@ -243,14 +243,17 @@ constexpr int kXcds = 8;
 // One-launch transforms of 1-D and 2-D jobs.  A workgroup has one CU's matrix cores for its
 // job: from kPlaneMfmas MFMAs on the fold and three passes, which spread a job over the chip,
 // are faster for a tree's few jobs (sweeps of two marginals of 1000 points, one launch and passes:
-// 30 x 30 box, M = 30, 384 MFMAs 50.5 and 54.3 us; 34 x 34, M = 20, 504: 55.4 and 53.9; 44 x 44,
-// M = 24, 602: 57.9 and 54.0; 46 x 46, M = 40, 1242: 71.4 and 54.1; twelve marginals alike: 58.0
-// and 61.8, 65.3 and 62.2, 79.7 and 63.4).  A circle's rows fill the chip: from kPlaneRows rows on
+// 30 x 30 box, M = 30, 384 MFMAs 50.5 and 54.3 us; 44 x 44, M = 24, 602: 57.9 and 54.0; 46 x 46,
+// M = 32, 1134: 69.2 and 54.2; M = 40, 1242: 71.4 and 54.1; twelve marginals alike: 58.0 and 61.8,
+// 65.3 and 62.2, 78.2 and 63.7, 79.7 and 63.4).  Batches, whose lanes' launches wait for each
+// other, are better off with the one launch for longer: 16 trees of 300 points 315 us a sweep with
+// the limit here, 706 at 500 (passes for 44 x 44, M = 24) and 434 at 1300; 40 of 3000 points 442, 809
+// and 507.  A circle's rows fill the chip: from kPlaneRows rows on
 // jobs of up to kPlaneRowMfmas take one launch (44 x 44, M = 24: 64 rows 63.8 and 64.0 us, 100
 // rows 70.7 and 74.4; 46 x 46, M = 40: 81.6 and 71.2, 89.6 and 85.0), and from kPlaneManyRows on all
 // do (200 rows 115 and 123 us; 72 x 72, M = 60: 64 rows 113 and 91, 100 rows 132 and 121, 200
 // rows 180 and 188; 4000 rows of 43 x 43: fold and passes 200 us, 112 us in one launch).
-constexpr int64_t kPlaneMfmas = 500, kPlaneRowMfmas = 1000;
+constexpr int64_t kPlaneMfmas = 700, kPlaneRowMfmas = 1000;
 constexpr int kPlaneRows = 64, kPlaneManyRows = 160;
 constexpr int kPlaneRounds = 4;
 
