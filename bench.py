@@ -36,20 +36,20 @@ PEAK_FP32_TFLOPS = 157.3  # dense FP32 MFMA
 # for fold and the FFT passes also of plan.cpp, whose launch item order sets their traffic).
 COPY_MIB = 256
 TRAFFIC = {
-    "spread": {"bytes_per_launch": 231942389, "source": "k_nfft.hip",
+    "spread": {"bytes_per_launch": 231945726, "source": "k_nfft.hip",
              "sha256": "17eef7bd667c0c0f7ecd01bc4d7c49af4d1eb0cd26357e3ab824a6d2927ce40b"},
-    "spread_g3": {"bytes_per_launch": 110945509, "source": "k_nfft.hip",
+    "spread_g3": {"bytes_per_launch": 110943072, "source": "k_nfft.hip",
                 "sha256": "17eef7bd667c0c0f7ecd01bc4d7c49af4d1eb0cd26357e3ab824a6d2927ce40b"},
-    "interp": {"bytes_per_launch": 201620983, "source": "k_nfft.hip",
+    "interp": {"bytes_per_launch": 201256508, "source": "k_nfft.hip",
              "sha256": "17eef7bd667c0c0f7ecd01bc4d7c49af4d1eb0cd26357e3ab824a6d2927ce40b"},
-    "fold": {"bytes_per_launch": 61179650, "source": "k_nfft.hip+nfft_device.h+plan.cpp",
-           "sha256": "7c77194299bec5fb2e8d79474ca57459699211ba5a5093eb88968288fab497e9"},
-    "fft6": {"bytes_per_launch": 10820451, "source": "k_fft.hip+plan.cpp",
-           "sha256": "f054b15bde99422e3e3e1f0797dda550ffd5d5d1092cfb98a005e30c6c4c4e56"},
-    "fft5": {"bytes_per_launch": 26585797, "source": "k_fft.hip+plan.cpp",
-           "sha256": "f054b15bde99422e3e3e1f0797dda550ffd5d5d1092cfb98a005e30c6c4c4e56"},
-    "fft7": {"bytes_per_launch": 10818874, "source": "k_fft.hip+plan.cpp",
-           "sha256": "f054b15bde99422e3e3e1f0797dda550ffd5d5d1092cfb98a005e30c6c4c4e56"}
+    "fold": {"bytes_per_launch": 61180293, "source": "k_nfft.hip+nfft_device.h+plan.cpp",
+           "sha256": "92f49fdf45e32aca5347b68e62d7ff869d14498e5f133c5fe941d59da8e85c46"},
+    "fft6": {"bytes_per_launch": 10820644, "source": "k_fft.hip+plan.cpp",
+           "sha256": "1268a2ee2e21f4ee515f341cb5b27aa1a454e90e53f993a3920ea64f935efa70"},
+    "fft5": {"bytes_per_launch": 26585333, "source": "k_fft.hip+plan.cpp",
+           "sha256": "1268a2ee2e21f4ee515f341cb5b27aa1a454e90e53f993a3920ea64f935efa70"},
+    "fft7": {"bytes_per_launch": 10818852, "source": "k_fft.hip+plan.cpp",
+           "sha256": "1268a2ee2e21f4ee515f341cb5b27aa1a454e90e53f993a3920ea64f935efa70"}
 }
 
 
